@@ -197,6 +197,15 @@ void fill_model(const mppi_model_desc& d, mppi::ModelT<R>& D)
     D.l1 = (R)l1; D.m1 = (R)m1; D.k1 = (R)(m1 * l1 * l1 / 12.0);
     D.l2 = (R)l2; D.m2 = (R)m2; D.k2 = (R)(m2 * l2 * l2 / 12.0);
     D.mtot = (R)(m0 + 4.0 * (m1 + m2));
+    // a uniform rod's inertia about its centre is m L^2 / 12
+    D.leg_a1 = (R)(m1 / 12.0 + m1 / 4.0);
+    D.leg_a2 = (R)(m2 / 3.0 + m2);
+    D.leg_k1e = (R)(m1 * l1 * l1 / 12.0 + m1 * l1 * l1 / 4.0);
+    D.leg_kk = (R)(m2 * l2 * l2 / 12.0 + m2 * l2 * l2 / 4.0);
+    const double hx2 = (double)d.hip_x * d.hip_x, hy2 = (double)d.hip_y * d.hip_y, ml = 4.0 * (m1 + m2);
+    D.tr_Ix = (R)(m0 * (sy * sy + sz * sz) / 12.0 + ml * hy2);
+    D.tr_Iy = (R)(m0 * (sx * sx + sz * sz) / 12.0 + ml * hx2);
+    D.tr_Iz = (R)(m0 * (sx * sx + sy * sy) / 12.0 + ml * (hx2 + hy2));
     D.foot_r = (R)d.foot_r; D.g = (R)d.gravity;
     D.ck = (R)d.contact_k; D.cc = (R)d.contact_c; D.cmu = (R)d.friction_mu;
     D.inv_vs = (R)(1.0 / (double)d.slip_velocity);

@@ -46,6 +46,9 @@ struct ModelT {
     R hf_inv_cell, hf_x0, hf_y0;
     R sb_cx, sb_cy, sb_cz, sb_hx, sb_hy, sb_hz;                // static box
     R bx_hx, bx_hy, bx_hz, bx_m, bx_Ix, bx_Iy, bx_Iz;          // free box
+    // constants of the FP64 step's leg (mppi_step64.h): the rods' inertia factors, and the
+    // trunk's inertia with the legs' masses at their hips
+    R leg_a1, leg_a2, leg_k1e, leg_kk, tr_Ix, tr_Iy, tr_Iz;
     int scene, hf_nx, hf_ny, pad;
 };
 using DevModelF = ModelT<float>;

@@ -1,0 +1,472 @@
+// The FP64 dynamics step's leg: kinematics, mass-matrix and bias terms, foot contact and
+// the terms they add to the trunk's rows, for the lane-split and the quad kernels.
+//
+// What bounds the FP64 step is the number of instructions a wave issues (one or two waves
+// per SIMD, every value in registers), so the leg is written in the frame in which it has
+// the fewest: the LEG FRAME, the trunk frame turned about x by the abduction angle with
+// its origin at the hip.  There both links lie in the x-z plane, the flexion and knee axes
+// are the unit vector y and the abduction axis is x, so cross products with an axis cost
+// no arithmetic and about half of every product vanishes:
+//   * composite inertia: xz-plane bodies have no xy and yz entries, and yy = xx + zz;
+//   * the joint columns of the mass matrix hold 7 values instead of 18;
+//   * a link is a uniform rod, whose inertia about its centre is that of two point masses,
+//     so its inertial torque is d x (A d) with the same matrix A = [alpha x] + w w^T - |w|^2
+//     that gives its centre's acceleration: no separate gyroscopic terms.
+// Three 6-vectors (the joint rows), one wrench and 9 inertia values are then turned back
+// into the trunk frame.  Divisions, square roots and the elementary functions are written
+// out without branches (the device library's FP64 versions cost 2 to 4 times as many
+// instructions); the results stay within about an ulp of the library's.
+#pragma once
+#include "mppi_device.h"
+
+#ifndef __constant__
+#define __constant__
+#endif
+
+namespace mppi {
+namespace f64 {
+
+// Coefficients of the series below.  Read from constant memory where they are used, through
+// a pointer that the compiler cannot see through, they arrive by a few scalar loads in
+// scalar registers; as literals every one would be kept in two vector registers over the
+// whole step loop, which costs the step more in register moves than the loads.
+enum { kSin = 0, kCos = 7, kRed = 14, kExp = 20 };
+static __constant__ const double kTab[32] = {
+    // sin: r^15 .. r^3
+    -1.0 / 1307674368000.0, 1.0 / 6227020800.0, -1.0 / 39916800.0, 1.0 / 362880.0, -1.0 / 5040.0, 1.0 / 120.0, -1.0 / 6.0,
+    // cos: r^16 .. r^4
+    1.0 / 20922789888000.0, -1.0 / 87178291200.0, 1.0 / 479001600.0, -1.0 / 3628800.0, 1.0 / 40320.0, -1.0 / 720.0,
+    1.0 / 24.0,
+    // 2/pi, pi/2 in two parts; 1/ln 2, ln 2 in two parts
+    0.63661977236758134308, 1.57079632679489655800, 6.12323399573676603587e-17, 1.44269504088896340736,
+    0.69314718055994528623, 2.31904681384629955842e-17,
+    // exp - 1: r^13 .. r^3
+    1.0 / 6227020800.0, 1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0, 1.0 / 40320.0, 1.0 / 5040.0,
+    1.0 / 720.0, 1.0 / 120.0, 1.0 / 24.0, 1.0 / 6.0, 0.0};
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef const __attribute__((address_space(4))) double* TabPtr;
+__device__ __forceinline__ TabPtr fresh_table()
+{
+    TabPtr p = (TabPtr)(&kTab[0]);
+    asm volatile("" : "+s"(p));
+    return p;
+}
+#else
+__device__ __forceinline__ const double* fresh_table() { return kTab; }
+#endif
+
+// ------------------------------------------------------------------------------
+// elementary functions
+// ------------------------------------------------------------------------------
+// 1/sqrt(x) and 1/x from the hardware's estimates (relative error below 2^-22) and one
+// third-order step, which leaves the rounding of its own operations (about 1 ulp)
+__device__ __forceinline__ double rsq(double x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double y = __builtin_amdgcn_rsq(x);
+#else
+    const double y = 1.0 / sqrt(x);
+#endif
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+__device__ __forceinline__ double rcp(double x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double y = __builtin_amdgcn_rcp(x);
+#else
+    const double y = 1.0 / x;
+#endif
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+// sqrt of x >= 0, and 1/sqrt with 0 -> a large finite value
+__device__ __forceinline__ double rsq_pos(double x) { return rsq(m_max(x, 1e-300)); }
+
+// sine and cosine: x = k pi/2 + r with pi/2 in two parts (k pi/2's leading part leaves the
+// fused multiply-add exact before its rounding), then the Taylor series on |r| <= pi/4 up
+// to r^15 and r^16 (truncation below 6e-17 relative) and the quadrant's swap and signs.
+// Good to |x| of about 1e12, where the rounded quotient can miss its integer.
+__device__ __forceinline__ void sincos64(double x, double* sn, double* cs)
+{
+    const auto t = fresh_table();
+    const double k = rint(x * t[kRed]);
+    double r = fma(-k, t[kRed + 1], x);
+    r = fma(-k, t[kRed + 2], r);
+    const double z = r * r;
+    double sp = fma(z, t[kSin], t[kSin + 1]), cp = fma(z, t[kCos], t[kCos + 1]);
+#pragma unroll
+    for (int i = 2; i < 7; ++i) {
+        sp = fma(z, sp, t[kSin + i]);
+        cp = fma(z, cp, t[kCos + i]);
+    }
+    sp = fma(r * z, sp, r);
+    cp = fma(z, cp, -0.5);
+    cp = fma(z, cp, 1.0);
+    const int q = int(fma(-4.0, m_floor(0.25 * k), k));  // k mod 4
+    const double s0 = (q & 1) ? cp : sp, c0 = (q & 1) ? sp : cp;
+    *sn = (q & 2) ? -s0 : s0;
+    *cs = ((q + 1) & 2) ? -c0 : c0;
+}
+
+// tanh(s) / s for s >= 0 through e = exp(-2s) - 1: -2s = k ln 2 + r, exp(r) - 1 by its
+// Taylor series up to r^13 on |r| <= 0.35 (truncation below 1e-17), e = 2^k (exp(r) - 1) +
+// (2^k - 1), which keeps its relative accuracy at small s (k = 0), tanh(s) = -e / (2 + e).
+// Beyond s = 350 exp(-2s) is zero next to 1.
+__device__ __forceinline__ double tanh_ratio64(double s)
+{
+    const auto t = fresh_table();
+    const double x = -2.0 * m_min(s, 350.0);
+    const double k = rint(x * t[kRed + 3]);
+    double r = fma(-k, t[kRed + 4], x);
+    r = fma(-k, t[kRed + 5], r);
+    double p = fma(r, t[kExp], t[kExp + 1]);
+#pragma unroll
+    for (int i = 2; i < 11; ++i) p = fma(r, p, t[kExp + i]);
+    p = fma(r, p, 0.5);
+    p = fma(r * r, p, r);
+    const double p2 = ldexp(1.0, int(k));
+    const double e = fma(p2, p, p2 - 1.0);
+    const double den = (2.0 + e) * s, y = rcp(den);
+    const double q = -e * y;
+    const double v = fma(fma(-q, den, -e), y, q);
+    return s < 1e-8 ? 1.0 : v;
+}
+
+// quaternion update q <- normalize(q (x) exp(dt w / 2)): sin(a)/a and cos(a) of the half
+// angle a by their Taylor series in a^2 while a <= 1/2 (up to a^12 and a^14, truncation
+// below 5e-17: any |w| up to 1/dt), by sincos64 beyond
+__device__ __forceinline__ void quat_step64(double& qw, double& qx, double& qy, double& qz, V3<double> w, double dt)
+{
+    const V3<double> ph = (0.5 * dt) * w;
+    const double z = dot(ph, ph);
+    const auto t = fresh_table();
+    double sc = fma(z, t[kSin + 1], t[kSin + 2]), dw = fma(z, t[kCos + 1], t[kCos + 2]);
+#pragma unroll
+    for (int i = 3; i < 7; ++i) {
+        sc = fma(z, sc, t[kSin + i]);
+        dw = fma(z, dw, t[kCos + i]);
+    }
+    sc = fma(z, sc, 1.0);
+    dw = fma(z, dw, -0.5);
+    dw = fma(z, dw, 1.0);
+    if (!(z <= 0.25)) {
+        const double a = sqrt(z);
+        double s;
+        sincos64(a, &s, &dw);
+        sc = s / a;
+    }
+    const double dx = sc * ph.x, dy = sc * ph.y, dz = sc * ph.z;
+    const double nw = qw * dw - qx * dx - qy * dy - qz * dz;
+    const double nx = qw * dx + qx * dw + qy * dz - qz * dy;
+    const double ny = qw * dy - qx * dz + qy * dw + qz * dx;
+    const double nz = qw * dz + qx * dy - qy * dx + qz * dw;
+    const double inv = rsq(nw * nw + nx * nx + ny * ny + nz * nz);
+    qw = nw * inv; qx = nx * inv; qy = ny * inv; qz = nz * inv;
+}
+
+// the penalty law of contact_law in FP64
+__device__ __forceinline__ void contact_law64(const ModelT<double>& M, double delta, V3<double> n, V3<double> vrel,
+                                              V3<double>& F, double& eta)
+{
+    const double vn = dot(n, vrel);
+    const double Fn = M.ck * delta - M.cc * vn;
+    const V3<double> vt = vrel - vn * n;
+    const double v2 = dot(vt, vt);
+    const double s = v2 * rsq_pos(v2) * M.inv_vs;
+    eta = M.cmu * m_max(Fn, 0.0) * M.inv_vs * tanh_ratio64(s);
+    F = Fn * n - eta * vt;
+}
+
+// terrain below a sphere (r > 0) or point (r = 0), as terrain<> of the device header
+template <int SCENE>
+__device__ __forceinline__ bool terrain64(const ModelT<double>& M, const float* __restrict__ hf, V3<double> c,
+                                          double r, double& delta, V3<double>& n)
+{
+    if constexpr (SCENE != 1) {
+        n = v3(0.0, 0.0, 1.0);
+        delta = r - c.z;
+        return delta > 0.0;
+    } else {
+        const int nx = M.hf_nx, ny = M.hf_ny;
+        const double ux = (c.x - M.hf_x0) * M.hf_inv_cell, uy = (c.y - M.hf_y0) * M.hf_inv_cell;
+        const double fx = m_min(m_max(ux, 0.0), double(nx - 1)), fy = m_min(m_max(uy, 0.0), double(ny - 1));
+        int i0 = (int)m_floor(fx), j0 = (int)m_floor(fy);
+        i0 = max(0, min(i0, nx - 2));
+        j0 = max(0, min(j0, ny - 2));
+        const double tx = fx - double(i0), ty = fy - double(j0);
+        const double h00 = hf[j0 * nx + i0], h10 = hf[j0 * nx + i0 + 1];
+        const double h01 = hf[(j0 + 1) * nx + i0], h11 = hf[(j0 + 1) * nx + i0 + 1];
+        const double dx0 = h10 - h00, dx1 = h11 - h01, dy0 = h01 - h00;
+        const double dxy = dx1 - dx0;
+        const double h = h00 + tx * dx0 + ty * (dy0 + tx * dxy);
+        // outside the grid the height is held, so its slope across the edge is zero; NaN
+        // coordinates keep a zero slope as well
+        const double gx = (fx == ux) ? (dx0 + ty * dxy) * M.hf_inv_cell : 0.0;
+        const double gy = (fy == uy) ? (dy0 + tx * dxy) * M.hf_inv_cell : 0.0;
+        const double inv = rsq(gx * gx + gy * gy + 1.0);
+        n = v3(-gx * inv, -gy * inv, inv);
+        delta = (h + r - c.z) * n.z;
+        return delta > 0.0;
+    }
+}
+
+// sphere against an axis-aligned box, as sphere_aabox of the device header
+__device__ __forceinline__ bool sphere_aabox64(V3<double> l, double r, V3<double> bh, double& delta, V3<double>& n)
+{
+    const V3<double> q = v3(m_min(m_max(l.x, -bh.x), bh.x), m_min(m_max(l.y, -bh.y), bh.y),
+                            m_min(m_max(l.z, -bh.z), bh.z));
+    const V3<double> e = l - q;
+    const double d2 = dot(e, e);
+    const bool inside = m_abs(l.x) <= bh.x && m_abs(l.y) <= bh.y && m_abs(l.z) <= bh.z;
+    if (!inside && !(d2 < r * r)) return false;
+    const double id = rsq_pos(d2);
+    const double dx = bh.x - m_abs(l.x), dy = bh.y - m_abs(l.y), dz = bh.z - m_abs(l.z);
+    double depth = dx;
+    V3<double> nf = v3(l.x >= 0.0 ? 1.0 : -1.0, 0.0, 0.0);
+    if (dy < depth) { depth = dy; nf = v3(0.0, l.y >= 0.0 ? 1.0 : -1.0, 0.0); }
+    if (dz < depth) { depth = dz; nf = v3(0.0, 0.0, l.z >= 0.0 ? 1.0 : -1.0); }
+    delta = inside ? r + depth : r - d2 * id;
+    n = inside ? nf : id * e;
+    return true;
+}
+
+// a contact's damping block and force on a 6x6 body system (base_contact_folded)
+__device__ __forceinline__ void body_terms(double eta, double c, V3<double> r, V3<double> n, V3<double> F, double dt,
+                                           double* Q, double* rb)
+{
+    base_contact_folded(eta, c, r, n, F, dt, Q, rb);
+}
+
+// ------------------------------------------------------------------------------
+// 6x6 system: L D L^T of the packed upper triangle, solving Q x = r in place (Q is
+// overwritten).  Reciprocals of the pivots instead of square roots.
+// ------------------------------------------------------------------------------
+__device__ __forceinline__ void ldl6_solve(double* Q, double* r)
+{
+    double inv[6];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        inv[j] = rcp(Q[s6(j, j)]);
+        double l[6];
+#pragma unroll
+        for (int i = j + 1; i < 6; ++i) l[i] = Q[s6(j, i)] * inv[j];
+#pragma unroll
+        for (int i = j + 1; i < 6; ++i) {
+#pragma unroll
+            for (int k = i; k < 6; ++k) Q[s6(i, k)] -= l[i] * Q[s6(j, k)];
+            r[i] -= l[i] * r[j];
+        }
+#pragma unroll
+        for (int i = j + 1; i < 6; ++i) Q[s6(j, i)] = l[i];
+    }
+#pragma unroll
+    for (int i = 5; i >= 0; --i) {
+        double s = r[i] * inv[i];
+#pragma unroll
+        for (int k = i + 1; k < 6; ++k) s -= Q[s6(i, k)] * r[k];
+        r[i] = s;
+    }
+}
+
+// 3x3 symmetric system, factored once and solved for several right sides
+struct Ldl3 {
+    double l10, l20, l21, i0, i1, i2;
+};
+__device__ __forceinline__ Ldl3 ldl3(double a00, double a10, double a11, double a20, double a21, double a22)
+{
+    Ldl3 f;
+    f.i0 = rcp(a00);
+    f.l10 = a10 * f.i0;
+    f.l20 = a20 * f.i0;
+    f.i1 = rcp(a11 - f.l10 * a10);
+    const double t = a21 - f.l20 * a10;
+    f.l21 = t * f.i1;
+    f.i2 = rcp(a22 - f.l20 * a20 - f.l21 * t);
+    return f;
+}
+__device__ __forceinline__ void solve3(const Ldl3& f, double& b0, double& b1, double& b2)
+{
+    const double y1 = b1 - f.l10 * b0;
+    const double y2 = b2 - f.l20 * b0 - f.l21 * y1;
+    b2 = y2 * f.i2;
+    b1 = y1 * f.i1 - f.l21 * b2;
+    b0 = b0 * f.i0 - f.l10 * b1 - f.l20 * b2;
+}
+
+// ------------------------------------------------------------------------------
+// the leg
+// ------------------------------------------------------------------------------
+struct LegFrame {
+    double sa, ca;             // abduction
+    double hx, hy;             // hip in the trunk frame (z = 0)
+    double kx, kz, fx, fz;     // knee and foot in the leg frame (y = 0)
+    V3<double> w1;             // angular velocity of the thigh, leg frame
+    V3<double> vh;             // velocity of the hip, leg frame
+    double dk;                 // knee rate
+};
+__device__ __forceinline__ V3<double> to_leg(const LegFrame& G, V3<double> v)
+{
+    return v3(v.x, G.ca * v.y + G.sa * v.z, G.ca * v.z - G.sa * v.y);
+}
+__device__ __forceinline__ V3<double> to_trunk(const LegFrame& G, V3<double> v)
+{
+    return v3(v.x, G.ca * v.y - G.sa * v.z, G.sa * v.y + G.ca * v.z);
+}
+// foot centre in the trunk frame
+__device__ __forceinline__ V3<double> foot_trunk(const LegFrame& G)
+{
+    return v3(G.hx + G.fx, G.hy - G.sa * G.fz, G.ca * G.fz);
+}
+
+// the leg's rows of the implicit system: A (joints), C (joints x trunk: angular, linear,
+// in the leg frame about the hip until rows_to_trunk), right side rl
+struct LegRows {
+    double A00, A01, A02, A11, A12, A22;
+    V3<double> L[3], P[3];
+    double rl[3];
+};
+
+// Mass-matrix, bias and joint-torque terms.  Q, rb receive the leg's share of the trunk
+// rows (Q overwritten; the linear block and the hip offsets' own inertia, which are
+// constant, are in the model's totals leg_I*).
+__device__ __forceinline__ void leg_terms(const ModelT<double>& M, int leg, double sa, double ca, double sf, double cf,
+                                          double s12, double c12, const double* qd, const double* tau, double dt,
+                                          double dtkd, V3<double> w, V3<double> vb, V3<double> gb, LegFrame& G,
+                                          LegRows& S, double* Q, double* rb)
+{
+    const double hx = (leg < 2) ? M.hip_x : -M.hip_x, hy = (leg & 1) ? -M.hip_y : M.hip_y;
+    G.sa = sa; G.ca = ca; G.hx = hx; G.hy = hy;
+    const double kx = -M.l1 * sf, kz = -M.l1 * cf;
+    const double rx = (-0.5 * M.l2) * s12, rz = (-0.5 * M.l2) * c12;  // calf centre from the knee
+    const double cx = kx + rx, cz = kz + rz;                          // calf centre from the hip
+    G.kx = kx; G.kz = kz;
+    G.fx = cx + rx; G.fz = cz + rz;
+    const double da = qd[0], df = qd[1], dk = qd[2];
+    G.dk = dk;
+
+    // hip: velocity and acceleration less gravity
+    const V3<double> u = v3(-w.z * hy, w.z * hx, w.x * hy - w.y * hx);
+    G.vh = to_leg(G, vb + u);
+    const V3<double> a = to_leg(G, cross(w, u) - gb);
+    const V3<double> wl = to_leg(G, w);
+    const V3<double> w1 = v3(wl.x + da, wl.y + df, wl.z);
+    G.w1 = w1;
+    const V3<double> al1 = v3(-df * wl.z, da * wl.z, df * w1.x - da * wl.y);
+    // columns x and z of [alpha x] + w w^T - |w|^2 for thigh (1) and calf (2)
+    const double yy1 = w1.y * w1.y, xz1 = w1.x * w1.z;
+    const V3<double> X1 = v3(-(w1.z * w1.z + yy1), w1.x * w1.y + al1.z, xz1 - al1.y);
+    const V3<double> Z1 = v3(xz1 + al1.y, w1.y * w1.z - al1.x, -(w1.x * w1.x + yy1));
+    const double w2y = w1.y + dk, a2x = al1.x - dk * w1.z, a2z = al1.z + dk * w1.x, yy2 = w2y * w2y;
+    const V3<double> X2 = v3(-(w1.z * w1.z + yy2), w1.x * w2y + a2z, xz1 - al1.y);
+    const V3<double> Z2 = v3(xz1 + al1.y, w2y * w1.z - a2x, -(w1.x * w1.x + yy2));
+    const V3<double> E1 = kx * X1 + kz * Z1, E2 = rx * X2 + rz * Z2;
+    // inertial forces: thigh F1, calf F2; G1, G2 carry the rods' own inertia as well
+    const V3<double> m1a = M.m1 * a, ma = M.m2 * (a + E1);
+    const V3<double> F1 = m1a + (0.5 * M.m1) * E1, G1 = 0.5 * m1a + M.leg_a1 * E1;
+    const V3<double> F2 = ma + M.m2 * E2, G2 = ma + M.leg_a2 * E2;
+    const V3<double> Fs = G1 + F2;
+    const V3<double> Tk = v3(-rz * G2.y, rz * G2.x - rx * G2.z, rx * G2.y);
+    const V3<double> Th = v3(Tk.x - kz * Fs.y, Tk.y + kz * Fs.x - kx * Fs.z, Tk.z + kx * Fs.y);
+    S.rl[0] = dt * (tau[0] - Th.x);
+    S.rl[1] = dt * (tau[1] - Th.y);
+    S.rl[2] = dt * (tau[2] - Tk.y);
+    {
+        const V3<double> F = to_trunk(G, F1 + F2), T = to_trunk(G, Th);
+        rb[0] = -dt * (T.x + hy * F.z);
+        rb[1] = -dt * (T.y - hx * F.z);
+        rb[2] = -dt * (T.z + hx * F.y - hy * F.x);
+        rb[3] = -dt * F.x; rb[4] = -dt * F.y; rb[5] = -dt * F.z;
+    }
+
+    // composite inertia and first moment about the hip, leg frame
+    const double k1c = M.leg_k1e * cf, k1s = M.leg_k1e * sf, k2c = M.k2 * c12, k2s = M.k2 * s12;
+    const double mcx = M.m2 * cx, mcz = M.m2 * cz;
+    const double xx = k1c * cf + k2c * c12 + mcz * cz;
+    const double zz = k1s * sf + k2s * s12 + mcx * cx;
+    const double xz = -(k1s * cf + k2s * c12 + mcx * cz);
+    const double yy = xx + zz;
+    const double lx = 0.5 * M.m1 * kx + mcx, lz = 0.5 * M.m1 * kz + mcz;
+    const double bx = M.m2 * rx, bz = M.m2 * rz, Lk = M.k2 + cx * bx + cz * bz;
+    S.L[0] = v3(xx, 0.0, xz);
+    S.P[0] = v3(0.0, -lz, 0.0);
+    S.L[1] = v3(0.0, yy, 0.0);
+    S.P[1] = v3(lz, 0.0, -lx);
+    S.L[2] = v3(0.0, Lk, 0.0);
+    S.P[2] = v3(bz, 0.0, -bx);
+    S.A00 = xx + dtkd; S.A01 = 0.0; S.A02 = 0.0;
+    S.A11 = yy + dtkd; S.A12 = Lk; S.A22 = M.leg_kk + dtkd;
+
+    // the trunk's rows: turned, then moved from the hip to the trunk's centre
+    const double s2 = sa * sa, c2 = ca * ca;
+    const double ly = -sa * lz, l2 = ca * lz;
+    const double hl = hx * lx, hm = hy * ly;
+    Q[s6(0, 0)] = xx + 2.0 * hm;
+    Q[s6(0, 1)] = -sa * xz - (hx * ly + hy * lx);
+    Q[s6(0, 2)] = ca * xz - hx * l2;
+    Q[s6(1, 1)] = c2 * yy + s2 * zz + 2.0 * hl;
+    Q[s6(1, 2)] = (ca * sa) * (yy - zz) - hy * l2;
+    Q[s6(2, 2)] = s2 * yy + c2 * zz + 2.0 * (hl + hm);
+    Q[s6(0, 3)] = 0.0; Q[s6(0, 4)] = -l2; Q[s6(0, 5)] = ly;
+    Q[s6(1, 3)] = l2;  Q[s6(1, 4)] = 0.0; Q[s6(1, 5)] = -lx;
+    Q[s6(2, 3)] = -ly; Q[s6(2, 4)] = lx;  Q[s6(2, 5)] = 0.0;
+#pragma unroll
+    for (int i = 15; i < 21; ++i) Q[i] = 0.0;
+}
+
+// A contact on the foot with weight wgt (1: applied, 0: nothing added): nt the normal
+// toward the robot and vo the other body's velocity, both in the trunk frame.  Adds the
+// terms of the joint rows and of the trunk's rows; returns force (trunk frame) and secant.
+__device__ __forceinline__ void foot_contact(const ModelT<double>& M, const LegFrame& G, double delta, V3<double> nt,
+                                             V3<double> vo, double dt, double wgt, LegRows& S, double* Q, double* rb,
+                                             V3<double>& Ft, double& eta)
+{
+    const V3<double> n = to_leg(G, nt);
+    const V3<double> r = v3(G.fx - M.foot_r * n.x, -M.foot_r * n.y, G.fz - M.foot_r * n.z);
+    const double px = r.x - G.kx, pz = r.z - G.kz;
+    const V3<double> vl = G.vh - to_leg(G, vo) + cross(G.w1, r);
+    V3<double> F;
+    contact_law64(M, delta, n, v3(vl.x + G.dk * pz, vl.y, vl.z - G.dk * px), F, eta);
+    F = wgt * F;
+    eta = wgt * eta;
+    const double c = wgt * M.cc;
+    const double de = dt * eta, dce = dt * (c - eta);
+    Ft = to_trunk(G, F);
+    body_terms(eta, c, foot_trunk(G) - M.foot_r * nt, nt, Ft, dt, Q, rb);
+    // the joints' columns at the contact: abduction (0, -rz, ry), flexion (rz, 0, -rx),
+    // knee (pz, 0, -px); D j = de j + dce (j . n) n
+    const double gA = r.y * n.z - r.z * n.y, gF = r.z * n.x - r.x * n.z, gK = pz * n.x - px * n.z;
+    const double ex = de * r.x, ey = de * r.y, ez = de * r.z, fx = de * px, fz = de * pz;
+    const double hA = dce * gA, hF = dce * gF, hK = dce * gK;
+    const V3<double> DA = v3(hA * n.x, hA * n.y - ez, hA * n.z + ey);
+    const V3<double> DF = v3(hF * n.x + ez, hF * n.y, hF * n.z - ex);
+    const V3<double> DK = v3(hK * n.x + fz, hK * n.y, hK * n.z - fx);
+    S.A00 += r.y * DA.z - r.z * DA.y;
+    S.A01 += r.z * DA.x - r.x * DA.z;
+    S.A02 += pz * DA.x - px * DA.z;
+    S.A11 += r.z * DF.x - r.x * DF.z;
+    S.A12 += pz * DF.x - px * DF.z;
+    S.A22 += pz * DK.x - px * DK.z;
+    S.rl[0] += dt * (r.y * F.z - r.z * F.y);
+    S.rl[1] += dt * (r.z * F.x - r.x * F.z);
+    S.rl[2] += dt * (pz * F.x - px * F.z);
+    S.L[0] = S.L[0] + cross(r, DA); S.P[0] = S.P[0] + DA;
+    S.L[1] = S.L[1] + cross(r, DF); S.P[1] = S.P[1] + DF;
+    S.L[2] = S.L[2] + cross(r, DK); S.P[2] = S.P[2] + DK;
+}
+
+// the joint rows over the trunk's six velocities, trunk frame about its centre
+__device__ __forceinline__ void rows_to_trunk(const LegFrame& G, const LegRows& S, double C[3][6])
+{
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const V3<double> P = to_trunk(G, S.P[j]), L = to_trunk(G, S.L[j]);
+        C[j][0] = L.x + G.hy * P.z;
+        C[j][1] = L.y - G.hx * P.z;
+        C[j][2] = L.z + G.hx * P.y - G.hy * P.x;
+        C[j][3] = P.x; C[j][4] = P.y; C[j][5] = P.z;
+    }
+}
+
+}  // namespace f64
+}  // namespace mppi

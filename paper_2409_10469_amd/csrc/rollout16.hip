@@ -24,6 +24,7 @@
 // type R (the state is FP32 between steps); only summation orders differ.
 #include "mppi_device.h"
 #include "mppi_launch.h"
+#include "mppi_step64.h"
 
 namespace mppi {
 namespace r16 {
@@ -546,6 +547,386 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
     }
 }
 
+// ------------------------------------------------------------------------------
+// The step in FP64: the same lanes, sums and discretisation as step16, arranged for fewer
+// instructions (a step's time on a SIMD with one wave is its instruction stream):
+//   * the leg is written in its own frame (mppi_step64.h), with divisions, square roots and
+//     elementary functions without branches;
+//   * lane `sub` of a leg eliminates two columns of the trunk's system, sub and sub + 4 (the
+//     fifth and sixth velocity, the right side, and a zero column), where step16 eliminates
+//     all seven in each of the four lanes; the back-substitution adds the four lanes' parts;
+//   * the leg's own terms and the eliminated parts go to the sum from where they are: one
+//     lane writes a leg's 28 values, each lane its two columns, so lane g adds 4 legs where
+//     step16 adds 16 lanes, most of them zeros;
+//   * corner contacts of the trunk are rare (a fallen robot, the box against the trunk):
+//     their 16-lane sum runs only in steps in which some lane of the wave has one, and the
+//     tests of trunk against box only while their bounding spheres overlap;
+//   * in the pushing scene each lane reads the sums of the one body whose 6x6 system it solves.
+// Per call, step16 / here (MI355X): heightfield walk K = 1024, H = 50: 318 / 216 us; box push
+// K = 4096, H = 60: 560 / 367 us; flat walk K = 64, H = 25, whole control step: 135 / 102 us.
+// LDS per sample in doubles: [0, 560) a region used in turn for the trunk corners' rows
+// (27 x kPitch), then the legs' values (4 x kLegPitch) and eliminated columns (4 x
+// kElimPitch); in the pushing scene the box's rows follow at kBoxRow (27 x kPitch).
+// ------------------------------------------------------------------------------
+constexpr int kLegPitch = 28, kElimPitch = 50, kElimRow = 4 * kLegPitch, kBoxRow = 28 * kPitch;
+
+// where lane g's summed values g and g + 16 of the trunk's 28 (21 + 6 + torque^2) stand in a
+// leg's eliminated columns (6 rows x 8 columns; column 6 is the right side, 7 zeros)
+__device__ __forceinline__ int elim_slot(int e)
+{
+    if (e >= 27) return 7;
+    if (e >= 21) return (e - 21) * 8 + 6;
+    int i = 0, first = 0;
+    while (e - first >= 6 - i) first += 6 - i++;
+    return i * 8 + i + (e - first);
+}
+
+// the model in LDS through an offset (always zero) that the compiler cannot see through, so
+// that a step reads its constants where it uses them instead of keeping about 35 doubles in
+// registers over the whole step loop
+__device__ __forceinline__ const ModelT<double>& fresh_model(const ModelT<double>* m)
+{
+    int o = 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(o));
+#endif
+    return m[o];
+}
+
+template <int SCENE>
+__device__ __forceinline__ void step16_64(const ModelT<double>& M, const float* __restrict__ hf, double dt, double kp,
+                                          double kd, int g, int eo0, int eo1, Base<double>& b, Leg<double>& lg,
+                                          BoxS<double>& bx, double uj, double* red, double* sred, double& tau2)
+{
+    using namespace f64;
+    const int leg = g >> 2, sub = g & 3;
+    const bool sub1 = (sub & 1) != 0, sub2 = (sub & 2) != 0;
+    const M33<double> Rm = quat_R(b.qw, b.qx, b.qy, b.qz);
+    const V3<double> w = b.w;
+    const V3<double> vb = mulT(Rm, b.vw);
+    const V3<double> zero = v3(0.0, 0.0, 0.0), up = v3(0.0, 0.0, 1.0);
+    [[maybe_unused]] M33<double> Rb;
+    if constexpr (SCENE == 3) Rb = quat_R(bx.qw, bx.qx, bx.qy, bx.qz);
+
+    // ---- trunk corner g (g < 8) or box corner g - 8 (g >= 8), first, so that their terms leave
+    // the registers before the leg's: the trunk's through a sum of their own where there are
+    // any, the box's as rows of the sum below
+    double c0 = 0.0, c1 = 0.0;  // the trunk corners' part of the values this lane sums
+    {
+        double Qc[21], rc[6];
+#pragma unroll
+        for (int i = 0; i < 21; ++i) Qc[i] = 0.0;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) rc[i] = 0.0;
+        bool corner;
+        V3<double> F;
+        double eta;
+        if constexpr (SCENE != 3) {
+            const V3<double> rloc = v3((g & 1 ? 0.5 : -0.5) * M.tsx, (g & 2 ? 0.5 : -0.5) * M.tsy,
+                                       (g & 4 ? 0.5 : -0.5) * M.tsz);
+            const V3<double> pw = b.p + mul(Rm, rloc);
+            double dT, dB = 0.0;
+            V3<double> nT, nB = zero;
+            const bool hitT = terrain64<SCENE>(M, hf, pw, 0.0, dT, nT) && g < 8;
+            bool hitB = false;
+            if constexpr (SCENE == 2)
+                hitB = point_aabox(pw - v3(M.sb_cx, M.sb_cy, M.sb_cz), v3(M.sb_hx, M.sb_hy, M.sb_hz), dB, nB) && g < 8;
+            corner = __builtin_amdgcn_ballot_w64(hitT || hitB) != 0;
+            if (corner) {
+                const V3<double> vc = vb + cross(w, rloc);
+                if (hitT) {
+                    const V3<double> n = mulT(Rm, nT);
+                    contact_law64(M, dT, n, vc, F, eta);
+                    body_terms(eta, M.cc, rloc, n, F, dt, Qc, rc);
+                }
+                if (hitB) {
+                    const V3<double> n = mulT(Rm, nB);
+                    contact_law64(M, dB, n, vc, F, eta);
+                    body_terms(eta, M.cc, rloc, n, F, dt, Qc, rc);
+                }
+            }
+        } else {
+            const bool own_trunk = g < 8;
+            const int ci = g & 7;
+            const V3<double> th = v3(0.5 * M.tsx, 0.5 * M.tsy, 0.5 * M.tsz), bh = v3(M.bx_hx, M.bx_hy, M.bx_hz);
+            const V3<double> hP = selv(own_trunk, th, bh);
+            const V3<double> cl = v3(ci & 1 ? hP.x : -hP.x, ci & 2 ? hP.y : -hP.y, ci & 4 ? hP.z : -hP.z);
+            const V3<double> x = selv(own_trunk, b.p + mul(Rm, cl), bx.p + mul(Rb, cl));
+            const double dG = -x.z;  // the corner against the ground
+            const bool hitG = dG > 0.0;
+            // the corner inside the other body, only while the bounding spheres can overlap
+            bool hitP = false;
+            double dP = 0.0;
+            V3<double> lq = zero, nlq = zero;
+            const V3<double> dc = b.p - bx.p;
+            if (__builtin_amdgcn_ballot_w64(dot(dc, dc) <= 2.0 * (dot(th, th) + dot(bh, bh)))) {
+                lq = selv(own_trunk, mulT(Rb, x - bx.p), mulT(Rm, x - b.p));
+                hitP = point_aabox(lq, selv(own_trunk, bh, th), dP, nlq);
+            }
+            double Qb[21], rbx[6];
+#pragma unroll
+            for (int i = 0; i < 21; ++i) Qb[i] = 0.0;
+#pragma unroll
+            for (int i = 0; i < 6; ++i) rbx[i] = 0.0;
+            // the box's corners against the ground
+            if (__builtin_amdgcn_ballot_w64(hitG && !own_trunk)) {
+                const double wgt = hitG && !own_trunk ? 1.0 : 0.0;
+                const V3<double> n = v3(Rb.m[6], Rb.m[7], Rb.m[8]);  // up, box frame
+                const V3<double> vc = mulT(Rb, bx.vw) + cross(bx.w, cl);
+                contact_law64(M, wgt * dG, n, wgt * vc, F, eta);
+                body_terms(wgt * eta, wgt * M.cc, cl, n, wgt * F, dt, Qb, rbx);
+            }
+            // rare: the trunk's corners against the ground, and either body's in the other
+            corner = __builtin_amdgcn_ballot_w64(hitP || (hitG && own_trunk)) != 0;
+            if (corner) {
+                const V3<double> lt = own_trunk ? cl : mulT(Rm, x - b.p), lb = own_trunk ? mulT(Rb, x - bx.p) : cl;
+                const V3<double> vtr = b.vw + mul(Rm, cross(w, lt)), vbx = bx.vw + mul(Rb, cross(bx.w, lb));
+                if (hitG && own_trunk) {
+                    const V3<double> n = v3(Rm.m[6], Rm.m[7], Rm.m[8]);
+                    contact_law64(M, dG, n, mulT(Rm, vtr), F, eta);
+                    body_terms(eta, M.cc, lt, n, F, dt, Qc, rc);
+                }
+                if (hitP) {
+                    // force +F on the corner's body, -F on the other
+                    const V3<double> n = selv(own_trunk, mul(Rb, nlq), mul(Rm, nlq));
+                    contact_law64(M, dP, n, selv(own_trunk, vtr - vbx, vbx - vtr), F, eta);
+                    const double st = own_trunk ? 1.0 : -1.0;
+                    body_terms(eta, M.cc, lt, mulT(Rm, n), st * mulT(Rm, F), dt, Qc, rc);
+                    body_terms(eta, M.cc, lb, mulT(Rb, n), (-st) * mulT(Rb, F), dt, Qb, rbx);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 21; ++e) red[kBoxRow + e * kPitch + g] = Qb[e];
+#pragma unroll
+            for (int e = 0; e < 6; ++e) red[kBoxRow + (21 + e) * kPitch + g] = rbx[e];
+        }
+        if (corner) {
+#pragma unroll
+            for (int e = 0; e < 21; ++e) red[e * kPitch + g] = Qc[e];
+#pragma unroll
+            for (int e = 0; e < 6; ++e) red[(21 + e) * kPitch + g] = rc[e];
+            __syncthreads();
+            c0 = sum16(red + g * kPitch);
+            if (g < 11) c1 = sum16(red + (g + 16) * kPitch);
+            __syncthreads();
+        }
+    }
+
+    // ---- the leg: torques, kinematics, mass-matrix and bias terms
+    const double u[3] = {dpp<0x00>(uj), dpp<0x55>(uj), dpp<0xAA>(uj)};
+    double tau[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) tau[j] = kp * (u[j] - lg.q[j]) - kd * lg.qd[j];
+    const V3<double> gb = (-M.g) * v3(Rm.m[6], Rm.m[7], Rm.m[8]);
+    LegFrame G;
+    LegRows S;
+    {
+        double Q[21], rb[6];
+        double sn, cs;
+        const double ang = (sub == 0) ? lg.q[0] : (sub == 1) ? lg.q[1] : lg.q[1] + lg.q[2];
+        sincos64(ang, &sn, &cs);
+        leg_terms(M, leg, dpp<0x00>(sn), dpp<0x00>(cs), dpp<0x55>(sn), dpp<0x55>(cs), dpp<0xAA>(sn), dpp<0xAA>(cs),
+                  lg.qd, tau, dt, dt * kd, w, vb, gb, G, S, Q, rb);
+
+        // its foot against terrain and the static or free box: the first contact (terrain if
+        // touched, else the box) in line, with zero weight where there is none; the second
+        // (a foot that touches both) and the box's share in blocks that are rarely entered
+        const V3<double> pfw = b.p + mul(Rm, foot_trunk(G));
+        double dT, dB = 0.0;
+        V3<double> nT, nB = zero;
+        const bool hitT = terrain64<SCENE>(M, hf, pfw, M.foot_r, dT, nT);
+        bool hitB = false;
+        if constexpr (SCENE == 2)
+            hitB = sphere_aabox64(pfw - v3(M.sb_cx, M.sb_cy, M.sb_cz), M.foot_r, v3(M.sb_hx, M.sb_hy, M.sb_hz), dB, nB);
+        if constexpr (SCENE == 3) {
+            // outside the sphere around the box there is no contact ((r + |h|)^2 <= 2 (r^2 + |h|^2))
+            const V3<double> d = pfw - bx.p;
+            const V3<double> bh = v3(M.bx_hx, M.bx_hy, M.bx_hz);
+            if (__builtin_amdgcn_ballot_w64(dot(d, d) <= 2.0 * (M.foot_r * M.foot_r + dot(bh, bh)))) {
+                V3<double> nl = up;
+                hitB = sphere_aabox64(mulT(Rb, d), M.foot_r, bh, dB, nl);
+                nB = mul(Rb, nl);  // box -> foot (world)
+            }
+        }
+        // the box at the contact point: its velocity there, and its share of the contact added
+        // to this lane's row of the box's sum (once per leg)
+        [[maybe_unused]] auto box_velocity = [&](V3<double> nw) {
+            return mulT(Rm, bx.vw + mul(Rb, cross(bx.w, mulT(Rb, pfw - M.foot_r * nw - bx.p))));
+        };
+        [[maybe_unused]] auto box_share = [&](double wgt, V3<double> nw, V3<double> F, double eta) {
+            double Qf[21], rf[6];
+#pragma unroll
+            for (int i = 0; i < 21; ++i) Qf[i] = 0.0;
+#pragma unroll
+            for (int i = 0; i < 6; ++i) rf[i] = 0.0;
+            const double wb = sub == 0 ? wgt : 0.0;
+            body_terms(wb * eta, wb * M.cc, mulT(Rb, pfw - M.foot_r * nw - bx.p), mulT(Rb, nw),
+                       mulT(Rb, (-wb) * mul(Rm, F)), dt, Qf, rf);
+#pragma unroll
+            for (int e = 0; e < 21; ++e) red[kBoxRow + e * kPitch + g] += Qf[e];
+#pragma unroll
+            for (int e = 0; e < 6; ++e) red[kBoxRow + (21 + e) * kPitch + g] += rf[e];
+        };
+        V3<double> F;
+        double eta;
+        {
+            const bool on = hitT || hitB, isB = !hitT && hitB;
+            const double wgt = on ? 1.0 : 0.0;
+            V3<double> n, vo = zero;
+            if constexpr (SCENE == 0) {
+                n = v3(Rm.m[6], Rm.m[7], Rm.m[8]);
+                foot_contact(M, G, on ? dT : 0.0, n, vo, dt, wgt, S, Q, rb, F, eta);
+            } else {
+                const V3<double> nw = isB ? nB : nT;
+                if constexpr (SCENE == 3) {
+                    if (__builtin_amdgcn_ballot_w64(isB)) vo = selv(isB, box_velocity(nw), zero);
+                }
+                n = mulT(Rm, nw);
+                foot_contact(M, G, on ? (isB ? dB : dT) : 0.0, n, vo, dt, wgt, S, Q, rb, F, eta);
+                if constexpr (SCENE == 3) {
+                    if (__builtin_amdgcn_ballot_w64(isB)) box_share(isB ? 1.0 : 0.0, nw, F, eta);
+                }
+            }
+        }
+        // the leg's values to the sum
+        double* o = red + leg * kLegPitch;
+        if (sub == 0) {
+#pragma unroll
+            for (int e = 0; e < 21; ++e) o[e] = Q[e];
+#pragma unroll
+            for (int e = 0; e < 6; ++e) o[21 + e] = rb[e];
+            o[27] = tau[0] * tau[0] + tau[1] * tau[1] + tau[2] * tau[2];
+        }
+        if constexpr (SCENE == 2 || SCENE == 3) {
+            const bool both = hitT && hitB;
+            if (__builtin_amdgcn_ballot_w64(both)) {
+                const double wgt = both ? 1.0 : 0.0;
+                const V3<double> nw = both ? nB : up;
+                V3<double> vo = zero;
+                if constexpr (SCENE == 3) vo = selv(both, box_velocity(nw), zero);
+#pragma unroll
+                for (int i = 0; i < 21; ++i) Q[i] = 0.0;
+#pragma unroll
+                for (int i = 0; i < 6; ++i) rb[i] = 0.0;
+                foot_contact(M, G, both ? dB : 0.0, mulT(Rm, nw), vo, dt, wgt, S, Q, rb, F, eta);
+                if (sub == 0) {
+#pragma unroll
+                    for (int e = 0; e < 21; ++e) o[e] += Q[e];
+#pragma unroll
+                    for (int e = 0; e < 6; ++e) o[21 + e] += rb[e];
+                }
+                if constexpr (SCENE == 3) box_share(wgt, nw, F, eta);
+            }
+        }
+    }
+
+    // ---- its elimination: lane `sub` solves columns sub and sub + 4
+    double W0[3], W1[3];
+    {
+        double C[3][6];
+        rows_to_trunk(G, S, C);
+        const Ldl3 f3 = ldl3(S.A00, S.A01, S.A11, S.A02, S.A12, S.A22);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            W0[j] = sel(sub2, sel(sub1, C[j][3], C[j][2]), sel(sub1, C[j][1], C[j][0]));
+            W1[j] = sel(sub2, sel(sub1, 0.0, S.rl[j]), sel(sub1, C[j][5], C[j][4]));
+        }
+        f64::solve3(f3, W0[0], W0[1], W0[2]);
+        f64::solve3(f3, W1[0], W1[1], W1[2]);
+        double* o = red + kElimRow + leg * kElimPitch + sub;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            if (i < 4) o[8 * i] = C[0][i] * W0[0] + C[1][i] * W0[1] + C[2][i] * W0[2];
+            o[8 * i + 4] = C[0][i] * W1[0] + C[1][i] * W1[1] + C[2][i] * W1[2];
+        }
+    }
+    __syncthreads();
+    {
+        const double* v = red + g;
+        const double* x = red + kElimRow;
+        double s0 = c0, s1 = c1;
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            s0 += v[l * kLegPitch] - x[l * kElimPitch + eo0];
+            if (g < 12) s1 += v[l * kLegPitch + 16] - x[l * kElimPitch + eo1];
+        }
+        sred[g] = s0;
+        if (g < 12) sred[g + 16] = s1;
+        if constexpr (SCENE == 3) {
+            sred[28 + g] = sum16(red + kBoxRow + g * kPitch);
+            if (g < 11) sred[28 + 16 + g] = sum16(red + kBoxRow + (g + 16) * kPitch);
+        }
+    }
+    __syncthreads();
+
+    // ---- the body's system: sums, own inertia, mass, gyroscopic and gravity bias; one 6x6
+    // solve per lane (the trunk's, on odd lanes of the pushing scene the box's)
+    tau2 = sred[27];
+    const bool odd = SCENE == 3 && sub1;
+    double dv[6];
+    {
+        double Q[21];
+        const double* s = sred + (odd ? 28 : 0);
+#pragma unroll
+        for (int i = 0; i < 21; ++i) Q[i] = s[i];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) dv[i] = s[21 + i];
+        V3<double> I = v3(M.I0x, M.I0y, M.I0z), It = v3(M.tr_Ix, M.tr_Iy, M.tr_Iz), wo = w, go = gb;
+        double m0 = M.m0, mt = M.mtot;
+        if constexpr (SCENE == 3) {
+            const V3<double> Ib = v3(M.bx_Ix, M.bx_Iy, M.bx_Iz);
+            I = selv(odd, Ib, I);
+            It = selv(odd, Ib, It);
+            m0 = sel(odd, M.bx_m, m0);
+            mt = sel(odd, M.bx_m, mt);
+            wo = selv(odd, bx.w, w);
+            go = selv(odd, (-M.g) * v3(Rb.m[6], Rb.m[7], Rb.m[8]), gb);
+        }
+        Q[s6(0, 0)] += It.x; Q[s6(1, 1)] += It.y; Q[s6(2, 2)] += It.z;
+        Q[s6(3, 3)] += mt; Q[s6(4, 4)] += mt; Q[s6(5, 5)] += mt;
+        const V3<double> gy = cross(wo, v3(I.x * wo.x, I.y * wo.y, I.z * wo.z));
+        const double dm = dt * m0;
+        dv[0] -= dt * gy.x; dv[1] -= dt * gy.y; dv[2] -= dt * gy.z;
+        dv[3] += dm * go.x; dv[4] += dm * go.y; dv[5] += dm * go.z;
+        ldl6_solve(Q, dv);
+    }
+    [[maybe_unused]] double db[6];
+    if constexpr (SCENE == 3) {
+        // lanes 0 and 1 of every quad hold the trunk's and the box's increments
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            db[i] = dpp<0x55>(dv[i]);
+            dv[i] = dpp<0x00>(dv[i]);
+        }
+    }
+
+    // ---- back-substitute the leg (each lane its two columns, added over the quad) and integrate
+    {
+        const double x0 = sel(sub2, sel(sub1, dv[3], dv[2]), sel(sub1, dv[1], dv[0]));
+        const double x1 = sel(sub2, sel(sub1, 0.0, -1.0), sel(sub1, dv[5], dv[4]));
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            lg.qd[j] -= quad_sum(W0[j] * x0 + W1[j] * x1);
+            lg.q[j] += dt * lg.qd[j];
+        }
+    }
+    b.w = w + v3(dv[0], dv[1], dv[2]);
+    b.vw = b.vw + mul(Rm, v3(dv[3], dv[4], dv[5]));
+    b.p = b.p + dt * b.vw;
+    if constexpr (SCENE != 3) {
+        quat_step64(b.qw, b.qx, b.qy, b.qz, b.w, dt);
+    } else {
+        bx.w = bx.w + v3(db[0], db[1], db[2]);
+        bx.vw = bx.vw + mul(Rb, v3(db[3], db[4], db[5]));
+        bx.p = bx.p + dt * bx.vw;
+        // one quaternion step per lane: the trunk's on even lanes, the box's on odd lanes
+        double q[4] = {sel(odd, bx.qw, b.qw), sel(odd, bx.qx, b.qx), sel(odd, bx.qy, b.qy), sel(odd, bx.qz, b.qz)};
+        quat_step64(q[0], q[1], q[2], q[3], selv(odd, bx.w, b.w), dt);
+        b.qw = dpp<0x00>(q[0]); b.qx = dpp<0x00>(q[1]); b.qy = dpp<0x00>(q[2]); b.qz = dpp<0x00>(q[3]);
+        bx.qw = dpp<0x55>(q[0]); bx.qx = dpp<0x55>(q[1]); bx.qy = dpp<0x55>(q[2]); bx.qz = dpp<0x55>(q[3]);
+    }
+}
+
 }  // namespace r16
 
 // ------------------------------------------------------------------------------
@@ -645,6 +1026,7 @@ __global__ __launch_bounds__(64) void rollout16_kernel(ModelT<R> Mr, ModelT<S> M
     S* my_red = red + grp * NV * r16::kPitch;
     S* my_sum = sred + grp * r16::kSumPitch;
     const S dt = P.dt, kp = P.kp, kd = P.kd;
+    [[maybe_unused]] const int eo0 = r16::elim_slot(g), eo1 = r16::elim_slot(g + 16);
     R L = R(0);
     for (int k = 0; k < P.H; ++k) {
         R uj = R(0);
@@ -665,7 +1047,10 @@ __global__ __launch_bounds__(64) void rollout16_kernel(ModelT<R> Mr, ModelT<S> M
                 if (i < nk) uj += R(gB[k * nk + i]) * th[i];
         }
         R tau2;
-        r16::step16<SCENE, R, S>(MR, MS, sHF, dt, kp, kd, g, b, lg, bx, uj, my_red, my_sum, tau2);
+        if constexpr (sizeof(R) == 8)
+            r16::step16_64<SCENE>(r16::fresh_model(&sMs), sHF, dt, kp, kd, g, eo0, eo1, b, lg, bx, uj, my_red, my_sum, tau2);
+        else
+            r16::step16<SCENE, R, S>(MR, MS, sHF, dt, kp, kd, g, b, lg, bx, uj, my_red, my_sum, tau2);
         round_state(b, lg);
         if constexpr (SCENE == 3) round_box(bx);
         L += R(dt) * stage_cost<SCENE>(P, b, bx, tau2);
