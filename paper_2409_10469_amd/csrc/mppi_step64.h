@@ -26,10 +26,11 @@
 namespace mppi {
 namespace f64 {
 
-// Coefficients of the series below.  Read from constant memory where they are used, through
-// a pointer that the compiler cannot see through, they arrive by a few scalar loads in
-// scalar registers; as literals every one would be kept in two vector registers over the
-// whole step loop, which costs the step more in register moves than the loads.
+// Coefficients of the series below.  Read from constant memory in every step, through a
+// pointer that the compiler takes to depend on the step's number k, they arrive by a few
+// scalar loads in scalar registers; as literals every one would be kept in two vector
+// registers over the whole step loop, which costs the step more in register moves.  Each USE
+// of the table loads for itself, so that its coefficients do not stay from one to the next.
 enum { kSin = 0, kCos = 7, kRed = 14, kExp = 20 };
 static __constant__ const double kTab[32] = {
     // sin: r^15 .. r^3
@@ -45,15 +46,34 @@ static __constant__ const double kTab[32] = {
     1.0 / 720.0, 1.0 / 120.0, 1.0 / 24.0, 1.0 / 6.0, 0.0};
 #if defined(__HIP_DEVICE_COMPILE__)
 typedef const __attribute__((address_space(4))) double* TabPtr;
-__device__ __forceinline__ TabPtr fresh_table()
+template <int USE>
+__device__ __forceinline__ TabPtr fresh_table(int k)
 {
     TabPtr p = (TabPtr)(&kTab[0]);
-    asm volatile("" : "+s"(p));
+    asm("; %2" : "+s"(p) : "s"(k), "i"(USE));
     return p;
 }
 #else
-__device__ __forceinline__ const double* fresh_table() { return kTab; }
+typedef const double* TabPtr;
+template <int USE>
+__device__ __forceinline__ TabPtr fresh_table(int)
+{
+    return kTab;
+}
 #endif
+
+// a x + c with the coefficient c in scalar registers (the compiler would move it to vector
+// registers first to use the two-operand form)
+__device__ __forceinline__ double horner(double a, double x, double c)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(x), "s"(c));
+    return d;
+#else
+    return fma(a, x, c);
+#endif
+}
 
 // ------------------------------------------------------------------------------
 // elementary functions
@@ -87,9 +107,8 @@ __device__ __forceinline__ double rsq_pos(double x) { return rsq(m_max(x, 1e-300
 // fused multiply-add exact before its rounding), then the Taylor series on |r| <= pi/4 up
 // to r^15 and r^16 (truncation below 6e-17 relative) and the quadrant's swap and signs.
 // Good to |x| of about 1e12, where the rounded quotient can miss its integer.
-__device__ __forceinline__ void sincos64(double x, double* sn, double* cs)
+__device__ __forceinline__ void sincos64(TabPtr t, double x, double* sn, double* cs)
 {
-    const auto t = fresh_table();
     const double k = rint(x * t[kRed]);
     double r = fma(-k, t[kRed + 1], x);
     r = fma(-k, t[kRed + 2], r);
@@ -97,8 +116,8 @@ __device__ __forceinline__ void sincos64(double x, double* sn, double* cs)
     double sp = fma(z, t[kSin], t[kSin + 1]), cp = fma(z, t[kCos], t[kCos + 1]);
 #pragma unroll
     for (int i = 2; i < 7; ++i) {
-        sp = fma(z, sp, t[kSin + i]);
-        cp = fma(z, cp, t[kCos + i]);
+        sp = horner(z, sp, t[kSin + i]);
+        cp = horner(z, cp, t[kCos + i]);
     }
     sp = fma(r * z, sp, r);
     cp = fma(z, cp, -0.5);
@@ -113,16 +132,15 @@ __device__ __forceinline__ void sincos64(double x, double* sn, double* cs)
 // Taylor series up to r^13 on |r| <= 0.35 (truncation below 1e-17), e = 2^k (exp(r) - 1) +
 // (2^k - 1), which keeps its relative accuracy at small s (k = 0), tanh(s) = -e / (2 + e).
 // Beyond s = 350 exp(-2s) is zero next to 1.
-__device__ __forceinline__ double tanh_ratio64(double s)
+__device__ __forceinline__ double tanh_ratio64(TabPtr t, double s)
 {
-    const auto t = fresh_table();
     const double x = -2.0 * m_min(s, 350.0);
     const double k = rint(x * t[kRed + 3]);
     double r = fma(-k, t[kRed + 4], x);
     r = fma(-k, t[kRed + 5], r);
     double p = fma(r, t[kExp], t[kExp + 1]);
 #pragma unroll
-    for (int i = 2; i < 11; ++i) p = fma(r, p, t[kExp + i]);
+    for (int i = 2; i < 11; ++i) p = horner(r, p, t[kExp + i]);
     p = fma(r, p, 0.5);
     p = fma(r * r, p, r);
     const double p2 = ldexp(1.0, int(k));
@@ -136,16 +154,16 @@ __device__ __forceinline__ double tanh_ratio64(double s)
 // quaternion update q <- normalize(q (x) exp(dt w / 2)): sin(a)/a and cos(a) of the half
 // angle a by their Taylor series in a^2 while a <= 1/2 (up to a^12 and a^14, truncation
 // below 5e-17: any |w| up to 1/dt), by sincos64 beyond
-__device__ __forceinline__ void quat_step64(double& qw, double& qx, double& qy, double& qz, V3<double> w, double dt)
+__device__ __forceinline__ void quat_step64(TabPtr t, double& qw, double& qx, double& qy, double& qz, V3<double> w,
+                                            double dt)
 {
     const V3<double> ph = (0.5 * dt) * w;
     const double z = dot(ph, ph);
-    const auto t = fresh_table();
     double sc = fma(z, t[kSin + 1], t[kSin + 2]), dw = fma(z, t[kCos + 1], t[kCos + 2]);
 #pragma unroll
     for (int i = 3; i < 7; ++i) {
-        sc = fma(z, sc, t[kSin + i]);
-        dw = fma(z, dw, t[kCos + i]);
+        sc = horner(z, sc, t[kSin + i]);
+        dw = horner(z, dw, t[kCos + i]);
     }
     sc = fma(z, sc, 1.0);
     dw = fma(z, dw, -0.5);
@@ -153,7 +171,7 @@ __device__ __forceinline__ void quat_step64(double& qw, double& qx, double& qy, 
     if (!(z <= 0.25)) {
         const double a = sqrt(z);
         double s;
-        sincos64(a, &s, &dw);
+        sincos64(t, a, &s, &dw);
         sc = s / a;
     }
     const double dx = sc * ph.x, dy = sc * ph.y, dz = sc * ph.z;
@@ -166,15 +184,15 @@ __device__ __forceinline__ void quat_step64(double& qw, double& qx, double& qy, 
 }
 
 // the penalty law of contact_law in FP64
-__device__ __forceinline__ void contact_law64(const ModelT<double>& M, double delta, V3<double> n, V3<double> vrel,
-                                              V3<double>& F, double& eta)
+__device__ __forceinline__ void contact_law64(TabPtr t, const ModelT<double>& M, double delta, V3<double> n,
+                                              V3<double> vrel, V3<double>& F, double& eta)
 {
     const double vn = dot(n, vrel);
     const double Fn = M.ck * delta - M.cc * vn;
     const V3<double> vt = vrel - vn * n;
     const double v2 = dot(vt, vt);
     const double s = v2 * rsq_pos(v2) * M.inv_vs;
-    eta = M.cmu * m_max(Fn, 0.0) * M.inv_vs * tanh_ratio64(s);
+    eta = M.cmu * m_max(Fn, 0.0) * M.inv_vs * tanh_ratio64(t, s);
     F = Fn * n - eta * vt;
 }
 
@@ -417,8 +435,8 @@ __device__ __forceinline__ void leg_terms(const ModelT<double>& M, int leg, doub
 // A contact on the foot with weight wgt (1: applied, 0: nothing added): nt the normal
 // toward the robot and vo the other body's velocity, both in the trunk frame.  Adds the
 // terms of the joint rows and of the trunk's rows; returns force (trunk frame) and secant.
-__device__ __forceinline__ void foot_contact(const ModelT<double>& M, const LegFrame& G, double delta, V3<double> nt,
-                                             V3<double> vo, double dt, double wgt, LegRows& S, double* Q, double* rb,
+__device__ __forceinline__ void foot_contact(TabPtr t, const ModelT<double>& M, const LegFrame& G, double delta,
+                                             V3<double> nt, V3<double> vo, double dt, double wgt, LegRows& S, double* Q, double* rb,
                                              V3<double>& Ft, double& eta)
 {
     const V3<double> n = to_leg(G, nt);
@@ -426,7 +444,7 @@ __device__ __forceinline__ void foot_contact(const ModelT<double>& M, const LegF
     const double px = r.x - G.kx, pz = r.z - G.kz;
     const V3<double> vl = G.vh - to_leg(G, vo) + cross(G.w1, r);
     V3<double> F;
-    contact_law64(M, delta, n, v3(vl.x + G.dk * pz, vl.y, vl.z - G.dk * px), F, eta);
+    contact_law64(t, M, delta, n, v3(vl.x + G.dk * pz, vl.y, vl.z - G.dk * px), F, eta);
     F = wgt * F;
     eta = wgt * eta;
     const double c = wgt * M.cc;

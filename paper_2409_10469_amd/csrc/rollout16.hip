@@ -562,8 +562,8 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
 //     their 16-lane sum runs only in steps in which some lane of the wave has one, and the
 //     tests of trunk against box only while their bounding spheres overlap;
 //   * in the pushing scene each lane reads the sums of the one body whose 6x6 system it solves.
-// Per call, step16 / here (MI355X): heightfield walk K = 1024, H = 50: 318 / 216 us; box push
-// K = 4096, H = 60: 560 / 367 us; flat walk K = 64, H = 25, whole control step: 135 / 102 us.
+// Per call, step16 / here (MI355X): heightfield walk K = 1024, H = 50: 318 / 197 us; box push
+// K = 4096, H = 60: 560 / 343 us; flat walk K = 64, H = 25, whole control step: 135 / 96 us.
 // LDS per sample in doubles: [0, 560) a region used in turn for the trunk corners' rows
 // (27 x kPitch), then the legs' values (4 x kLegPitch) and eliminated columns (4 x
 // kElimPitch); in the pushing scene the box's rows follow at kBoxRow (27 x kPitch).
@@ -581,22 +581,22 @@ __device__ __forceinline__ int elim_slot(int e)
     return i * 8 + i + (e - first);
 }
 
-// the model in LDS through an offset (always zero) that the compiler cannot see through, so
-// that a step reads its constants where it uses them instead of keeping about 35 doubles in
-// registers over the whole step loop
-__device__ __forceinline__ const ModelT<double>& fresh_model(const ModelT<double>* m)
+// the model in LDS through an offset (always zero) that the compiler takes to depend on the
+// step's number, so that a step reads its constants where it uses them instead of keeping
+// about 35 doubles in registers over the whole step loop
+__device__ __forceinline__ const ModelT<double>& fresh_model(const ModelT<double>* m, int k)
 {
     int o = 0;
 #if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("" : "+v"(o));
+    asm("" : "+v"(o) : "s"(k));
 #endif
     return m[o];
 }
 
 template <int SCENE>
-__device__ __forceinline__ void step16_64(const ModelT<double>& M, const float* __restrict__ hf, double dt, double kp,
-                                          double kd, int g, int eo0, int eo1, Base<double>& b, Leg<double>& lg,
-                                          BoxS<double>& bx, double uj, double* red, double* sred, double& tau2)
+__device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const float* __restrict__ hf, double dt,
+                                          double kp, double kd, int g, int eo0, int eo1, Base<double>& b,
+                                          Leg<double>& lg, BoxS<double>& bx, double uj, double* red, double* sred, double& tau2)
 {
     using namespace f64;
     const int leg = g >> 2, sub = g & 3;
@@ -636,12 +636,12 @@ __device__ __forceinline__ void step16_64(const ModelT<double>& M, const float* 
                 const V3<double> vc = vb + cross(w, rloc);
                 if (hitT) {
                     const V3<double> n = mulT(Rm, nT);
-                    contact_law64(M, dT, n, vc, F, eta);
+                    contact_law64(fresh_table<3>(k), M, dT, n, vc, F, eta);
                     body_terms(eta, M.cc, rloc, n, F, dt, Qc, rc);
                 }
                 if (hitB) {
                     const V3<double> n = mulT(Rm, nB);
-                    contact_law64(M, dB, n, vc, F, eta);
+                    contact_law64(fresh_table<3>(k), M, dB, n, vc, F, eta);
                     body_terms(eta, M.cc, rloc, n, F, dt, Qc, rc);
                 }
             }
@@ -673,7 +673,7 @@ __device__ __forceinline__ void step16_64(const ModelT<double>& M, const float* 
                 const double wgt = hitG && !own_trunk ? 1.0 : 0.0;
                 const V3<double> n = v3(Rb.m[6], Rb.m[7], Rb.m[8]);  // up, box frame
                 const V3<double> vc = mulT(Rb, bx.vw) + cross(bx.w, cl);
-                contact_law64(M, wgt * dG, n, wgt * vc, F, eta);
+                contact_law64(fresh_table<3>(k), M, wgt * dG, n, wgt * vc, F, eta);
                 body_terms(wgt * eta, wgt * M.cc, cl, n, wgt * F, dt, Qb, rbx);
             }
             // rare: the trunk's corners against the ground, and either body's in the other
@@ -683,13 +683,13 @@ __device__ __forceinline__ void step16_64(const ModelT<double>& M, const float* 
                 const V3<double> vtr = b.vw + mul(Rm, cross(w, lt)), vbx = bx.vw + mul(Rb, cross(bx.w, lb));
                 if (hitG && own_trunk) {
                     const V3<double> n = v3(Rm.m[6], Rm.m[7], Rm.m[8]);
-                    contact_law64(M, dG, n, mulT(Rm, vtr), F, eta);
+                    contact_law64(fresh_table<3>(k), M, dG, n, mulT(Rm, vtr), F, eta);
                     body_terms(eta, M.cc, lt, n, F, dt, Qc, rc);
                 }
                 if (hitP) {
                     // force +F on the corner's body, -F on the other
                     const V3<double> n = selv(own_trunk, mul(Rb, nlq), mul(Rm, nlq));
-                    contact_law64(M, dP, n, selv(own_trunk, vtr - vbx, vbx - vtr), F, eta);
+                    contact_law64(fresh_table<3>(k), M, dP, n, selv(own_trunk, vtr - vbx, vbx - vtr), F, eta);
                     const double st = own_trunk ? 1.0 : -1.0;
                     body_terms(eta, M.cc, lt, mulT(Rm, n), st * mulT(Rm, F), dt, Qc, rc);
                     body_terms(eta, M.cc, lb, mulT(Rb, n), (-st) * mulT(Rb, F), dt, Qb, rbx);
@@ -707,7 +707,7 @@ __device__ __forceinline__ void step16_64(const ModelT<double>& M, const float* 
             for (int e = 0; e < 6; ++e) red[(21 + e) * kPitch + g] = rc[e];
             __syncthreads();
             c0 = sum16(red + g * kPitch);
-            if (g < 11) c1 = sum16(red + (g + 16) * kPitch);
+            c1 = sel(g < 11, sum16(red + min(g + 16, 26) * kPitch), 0.0);
             __syncthreads();
         }
     }
@@ -724,7 +724,7 @@ __device__ __forceinline__ void step16_64(const ModelT<double>& M, const float* 
         double Q[21], rb[6];
         double sn, cs;
         const double ang = (sub == 0) ? lg.q[0] : (sub == 1) ? lg.q[1] : lg.q[1] + lg.q[2];
-        sincos64(ang, &sn, &cs);
+        sincos64(fresh_table<0>(k), ang, &sn, &cs);
         leg_terms(M, leg, dpp<0x00>(sn), dpp<0x00>(cs), dpp<0x55>(sn), dpp<0x55>(cs), dpp<0xAA>(sn), dpp<0xAA>(cs),
                   lg.qd, tau, dt, dt * kd, w, vb, gb, G, S, Q, rb);
 
@@ -775,14 +775,14 @@ __device__ __forceinline__ void step16_64(const ModelT<double>& M, const float* 
             V3<double> n, vo = zero;
             if constexpr (SCENE == 0) {
                 n = v3(Rm.m[6], Rm.m[7], Rm.m[8]);
-                foot_contact(M, G, on ? dT : 0.0, n, vo, dt, wgt, S, Q, rb, F, eta);
+                foot_contact(fresh_table<1>(k), M, G, on ? dT : 0.0, n, vo, dt, wgt, S, Q, rb, F, eta);
             } else {
                 const V3<double> nw = isB ? nB : nT;
                 if constexpr (SCENE == 3) {
                     if (__builtin_amdgcn_ballot_w64(isB)) vo = selv(isB, box_velocity(nw), zero);
                 }
                 n = mulT(Rm, nw);
-                foot_contact(M, G, on ? (isB ? dB : dT) : 0.0, n, vo, dt, wgt, S, Q, rb, F, eta);
+                foot_contact(fresh_table<1>(k), M, G, on ? (isB ? dB : dT) : 0.0, n, vo, dt, wgt, S, Q, rb, F, eta);
                 if constexpr (SCENE == 3) {
                     if (__builtin_amdgcn_ballot_w64(isB)) box_share(isB ? 1.0 : 0.0, nw, F, eta);
                 }
@@ -808,7 +808,7 @@ __device__ __forceinline__ void step16_64(const ModelT<double>& M, const float* 
                 for (int i = 0; i < 21; ++i) Q[i] = 0.0;
 #pragma unroll
                 for (int i = 0; i < 6; ++i) rb[i] = 0.0;
-                foot_contact(M, G, both ? dB : 0.0, mulT(Rm, nw), vo, dt, wgt, S, Q, rb, F, eta);
+                foot_contact(fresh_table<1>(k), M, G, both ? dB : 0.0, mulT(Rm, nw), vo, dt, wgt, S, Q, rb, F, eta);
                 if (sub == 0) {
 #pragma unroll
                     for (int e = 0; e < 21; ++e) o[e] += Q[e];
@@ -845,16 +845,23 @@ __device__ __forceinline__ void step16_64(const ModelT<double>& M, const float* 
         const double* v = red + g;
         const double* x = red + kElimRow;
         double s0 = c0, s1 = c1;
+        // every lane reads (lanes past the last value a valid one, unused), so that the reads
+        // wait together
 #pragma unroll
         for (int l = 0; l < 4; ++l) {
             s0 += v[l * kLegPitch] - x[l * kElimPitch + eo0];
-            if (g < 12) s1 += v[l * kLegPitch + 16] - x[l * kElimPitch + eo1];
+            s1 += v[l * kLegPitch + 16] - x[l * kElimPitch + eo1];
+        }
+        [[maybe_unused]] double b0, b1;
+        if constexpr (SCENE == 3) {
+            b0 = sum16(red + kBoxRow + g * kPitch);
+            b1 = sum16(red + kBoxRow + min(g + 16, 26) * kPitch);
+            sred[28 + g] = b0;
         }
         sred[g] = s0;
-        if (g < 12) sred[g + 16] = s1;
-        if constexpr (SCENE == 3) {
-            sred[28 + g] = sum16(red + kBoxRow + g * kPitch);
-            if (g < 11) sred[28 + 16 + g] = sum16(red + kBoxRow + (g + 16) * kPitch);
+        if (g < 12) {
+            sred[g + 16] = s1;
+            if constexpr (SCENE == 3) sred[28 + 16 + min(g, 10)] = b1;
         }
     }
     __syncthreads();
@@ -914,14 +921,14 @@ __device__ __forceinline__ void step16_64(const ModelT<double>& M, const float* 
     b.vw = b.vw + mul(Rm, v3(dv[3], dv[4], dv[5]));
     b.p = b.p + dt * b.vw;
     if constexpr (SCENE != 3) {
-        quat_step64(b.qw, b.qx, b.qy, b.qz, b.w, dt);
+        quat_step64(fresh_table<2>(k), b.qw, b.qx, b.qy, b.qz, b.w, dt);
     } else {
         bx.w = bx.w + v3(db[0], db[1], db[2]);
         bx.vw = bx.vw + mul(Rb, v3(db[3], db[4], db[5]));
         bx.p = bx.p + dt * bx.vw;
         // one quaternion step per lane: the trunk's on even lanes, the box's on odd lanes
         double q[4] = {sel(odd, bx.qw, b.qw), sel(odd, bx.qx, b.qx), sel(odd, bx.qy, b.qy), sel(odd, bx.qz, b.qz)};
-        quat_step64(q[0], q[1], q[2], q[3], selv(odd, bx.w, b.w), dt);
+        quat_step64(fresh_table<2>(k), q[0], q[1], q[2], q[3], selv(odd, bx.w, b.w), dt);
         b.qw = dpp<0x00>(q[0]); b.qx = dpp<0x00>(q[1]); b.qy = dpp<0x00>(q[2]); b.qz = dpp<0x00>(q[3]);
         bx.qw = dpp<0x55>(q[0]); bx.qx = dpp<0x55>(q[1]); bx.qy = dpp<0x55>(q[2]); bx.qz = dpp<0x55>(q[3]);
     }
@@ -1026,6 +1033,14 @@ __global__ __launch_bounds__(64) void rollout16_kernel(ModelT<R> Mr, ModelT<S> M
     S* my_red = red + grp * NV * r16::kPitch;
     S* my_sum = sred + grp * r16::kSumPitch;
     const S dt = P.dt, kp = P.kp, kd = P.kd;
+    // the spline basis' row of the coming step, read before the cost of the last one: its
+    // scalar loads make one round trip to memory together and behind that work, where reading
+    // them knot by knot at their use made one after the other
+    [[maybe_unused]] double brow[kMaxKnots];
+    if constexpr (!DIRECT) {
+#pragma unroll
+        for (int i = 0; i < kMaxKnots; ++i) brow[i] = gB[min(i, nk - 1)];
+    }
     [[maybe_unused]] const int eo0 = r16::elim_slot(g), eo1 = r16::elim_slot(g + 16);
     R L = R(0);
     for (int k = 0; k < P.H; ++k) {
@@ -1042,15 +1057,21 @@ __global__ __launch_bounds__(64) void rollout16_kernel(ModelT<R> Mr, ModelT<S> M
             }
             uj = R(mu[d]) + (ns ? sigma * e : R(0));
         } else {
+            // every term (those past the last knot are zero), from the row read a step ago
 #pragma unroll
-            for (int i = 0; i < kMaxKnots; ++i)
-                if (i < nk) uj += R(gB[k * nk + i]) * th[i];
+            for (int i = 0; i < kMaxKnots; ++i) uj += R(brow[i]) * th[i];
         }
         R tau2;
         if constexpr (sizeof(R) == 8)
-            r16::step16_64<SCENE>(r16::fresh_model(&sMs), sHF, dt, kp, kd, g, eo0, eo1, b, lg, bx, uj, my_red, my_sum, tau2);
+            r16::step16_64<SCENE>(k, r16::fresh_model(&sMs, k), sHF, dt, kp, kd, g, eo0, eo1, b, lg, bx, uj, my_red,
+                                  my_sum, tau2);
         else
             r16::step16<SCENE, R, S>(MR, MS, sHF, dt, kp, kd, g, b, lg, bx, uj, my_red, my_sum, tau2);
+        if constexpr (!DIRECT) {
+            const double* nrow = gB + min(k + 1, P.H - 1) * nk;
+#pragma unroll
+            for (int i = 0; i < kMaxKnots; ++i) brow[i] = nrow[min(i, nk - 1)];
+        }
         round_state(b, lg);
         if constexpr (SCENE == 3) round_box(bx);
         L += R(dt) * stage_cost<SCENE>(P, b, bx, tau2);
