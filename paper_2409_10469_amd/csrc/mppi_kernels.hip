@@ -8,6 +8,7 @@
 //   sim_step_kernel - one dynamics step of many states (closed-loop plant)
 #include "mppi_device.h"
 #include "mppi_launch.h"
+#include "mppi_step64.h"
 
 namespace mppi {
 
@@ -38,6 +39,42 @@ __global__ __launch_bounds__(256) void sample_kernel(DevParams P, int D, float* 
     }
 }
 
+// the step of the arithmetic: FP64 from the model in constant memory (mppi_step64.h), else the
+// device header's
+template <typename R>
+struct ModelRef {
+    typedef const ModelT<R>* Ptr;
+};
+template <>
+struct ModelRef<double> {
+    typedef f64::ConstModel* Ptr;
+};
+template <typename R>
+__device__ __forceinline__ typename ModelRef<R>::Ptr model_ref(const ModelT<R>* m)
+{
+    return (typename ModelRef<R>::Ptr)m;
+}
+// a kernel's first argument (the model, at the start of the argument segment)
+template <typename R>
+__device__ __forceinline__ typename ModelRef<R>::Ptr model_arg(const ModelT<R>& m)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (sizeof(R) == 8) return (f64::ConstModel*)__builtin_amdgcn_kernarg_segment_ptr();
+    else return &m;
+#else
+    return &m;
+#endif
+}
+template <int SCENE, typename R>
+__device__ __forceinline__ void step_of(int k, typename ModelRef<R>::Ptr M, const float* hf, R dt, R kp, R kd, int leg,
+                                        Base<R>& b, Leg<R>& lg, BoxS<R>& bx, const R u[3], R& tau2)
+{
+    if constexpr (sizeof(R) == 8)
+        f64::quad_step64<SCENE>(k, f64::fresh_const_model(M, k), hf, dt, kp, kd, leg, b, lg, bx, u, tau2);
+    else
+        quad_step<SCENE, R>(*M, hf, dt, kp, kd, leg, b, lg, bx, u, tau2);
+}
+
 // ---------------------------------------------------------------------------------
 // Rollout of the samples of one workgroup: quad q of the block handles sample
 // n = n_base + q.  sB (spline basis, type R) and sHF (heightfield) are in LDS.
@@ -46,7 +83,7 @@ __global__ __launch_bounds__(256) void sample_kernel(DevParams P, int D, float* 
 // The state is rounded to FP32 after every step; the step itself runs in R.
 // ---------------------------------------------------------------------------------
 template <int SCENE, typename R>
-__device__ __forceinline__ void rollout_samples(const ModelT<R>& M, const DevParams& P, const R* sB, const float* sHF,
+__device__ __forceinline__ void rollout_samples(typename ModelRef<R>::Ptr M, const DevParams& P, const R* sB, const float* sHF,
                                                 R* sTh,
                                                 const float* __restrict__ mu, const float* __restrict__ x0,
                                                 const float* __restrict__ eps_in, int eps_sn, int eps_sd,
@@ -68,6 +105,7 @@ __device__ __forceinline__ void rollout_samples(const ModelT<R>& M, const DevPar
     for (int j = 0; j < 3; ++j)
 #pragma unroll
         for (int i = 0; i < kMaxKnots; ++i) {
+            R v = R(0);
             if (i < nk) {
                 const int d = (3 * leg + j) * nk + i;
                 R e;
@@ -77,8 +115,9 @@ __device__ __forceinline__ void rollout_samples(const ModelT<R>& M, const DevPar
                     e = gauss_elem<R>(P, (uint32_t)ns, (uint32_t)d);
                     if (valid && eps_out) eps_out[(size_t)d * P.K + n] = (float)e;
                 }
-                th[j * kMaxKnots + i] = R(mu[d]) + (ns ? sigma * e : R(0));
+                v = R(mu[d]) + (ns ? sigma * e : R(0));
             }
+            th[j * kMaxKnots + i] = v;
         }
 
     Base<R> b;
@@ -95,17 +134,20 @@ __device__ __forceinline__ void rollout_samples(const ModelT<R>& M, const DevPar
     const R dt = P.dt, kp = P.kp, kd = P.kd;
     R L = R(0);
     for (int k = 0; k < P.H; ++k) {
-        R u[3];
+        // all eight terms (those past the last knot are zero), so that the reads wait together
+        // instead of knot by knot
+        R u[3], bk[kMaxKnots];
+#pragma unroll
+        for (int i = 0; i < kMaxKnots; ++i) bk[i] = sB[k * nk + min(i, nk - 1)];
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
             R s = R(0);
 #pragma unroll
-            for (int i = 0; i < kMaxKnots; ++i)
-                if (i < nk) s += sB[k * nk + i] * th[j * kMaxKnots + i];
+            for (int i = 0; i < kMaxKnots; ++i) s += bk[i] * th[j * kMaxKnots + i];
             u[j] = s;
         }
         R tau2;
-        quad_step<SCENE, R>(M, sHF, dt, kp, kd, leg, b, lg, bx, u, tau2);
+        step_of<SCENE, R>(k, M, sHF, dt, kp, kd, leg, b, lg, bx, u, tau2);
         round_state(b, lg);
         if constexpr (SCENE == 3) round_box(bx);
         L += dt * stage_cost<SCENE>(P, b, bx, tau2);
@@ -142,7 +184,7 @@ __global__ __launch_bounds__(256) void rollout_kernel(ModelT<R> M, DevParams P, 
     float* sHF = reinterpret_cast<float*>(sTh + blockDim.x * 3 * kMaxKnots);
     stage_lds(P, SCENE, M.hf_nx * M.hf_ny, gB, ghf, sB, sHF);
     __syncthreads();
-    rollout_samples<SCENE, R>(M, P, sB, sHF, sTh, mu, x0, eps_in, eps_sn, eps_sd, eps_out, costs, traj,
+    rollout_samples<SCENE, R>(model_arg(M), P, sB, sHF, sTh, mu, x0, eps_in, eps_sn, eps_sd, eps_out, costs, traj,
                               blockIdx.x * (blockDim.x >> 2));
 }
 
@@ -333,7 +375,7 @@ __global__ __launch_bounds__(256) void sim_step_kernel(ModelT<R> M, int nstate, 
         tauv[j] = R(kp) * (uu[j] - lg.q[j]) - R(kd) * lg.qd[j];
     }
     R tau2;
-    quad_step<SCENE, R>(M, sHF, R(dt), R(kp), R(kd), leg, b, lg, bx, uu, tau2);
+    step_of<SCENE, R>(0, model_arg(M), sHF, R(dt), R(kp), R(kd), leg, b, lg, bx, uu, tau2);
     if (!valid) return;
     store_state(xo + (size_t)n * nx, leg, b, lg);
     if (SCENE == 3 && leg == 0) store_box(xo + (size_t)n * nx, bx);
@@ -365,7 +407,7 @@ __device__ __forceinline__ float wave_min(float v)
 }
 
 template <int SCENE, typename R>
-__device__ __forceinline__ void plant_step(const ModelT<R>& M, const DevParams& P, const float* sHF, float* x,
+__device__ __forceinline__ void plant_step(typename ModelRef<R>::Ptr M, const DevParams& P, const float* sHF, float* x,
                                            const float* u0, float* cost_acc)
 {
     const int leg = threadIdx.x & 3;
@@ -376,7 +418,7 @@ __device__ __forceinline__ void plant_step(const ModelT<R>& M, const DevParams& 
     if constexpr (SCENE == 3) load_box(x, bx);
     R u[3] = {R(u0[3 * leg]), R(u0[3 * leg + 1]), R(u0[3 * leg + 2])};
     R tau2;
-    quad_step<SCENE, R>(M, sHF, R(P.dt), R(P.kp), R(P.kd), leg, b, lg, bx, u, tau2);
+    step_of<SCENE, R>(0, M, sHF, R(P.dt), R(P.kp), R(P.kd), leg, b, lg, bx, u, tau2);
     const R l = stage_cost<SCENE>(P, b, bx, tau2);
     __syncthreads();  // every lane has read x
     if (threadIdx.x < 4) {
@@ -387,7 +429,7 @@ __device__ __forceinline__ void plant_step(const ModelT<R>& M, const DevParams& 
 }
 
 template <int SCENE, typename R>
-__device__ __forceinline__ void instance_tail(const InstDesc& I, const DevParams& P, const ModelT<R>& M, const float* sHF,
+__device__ __forceinline__ void instance_tail(const InstDesc& I, const DevParams& P, typename ModelRef<R>::Ptr M, const float* sHF,
                               float* sMup)
 {
     const int t = threadIdx.x, K = P.K, nk = P.nk, D = 12 * nk;
@@ -438,7 +480,7 @@ __device__ __forceinline__ void instance_tail(const InstDesc& I, const DevParams
 // one tile of one instance: stage its basis (and heightfield) in LDS, roll out its 16
 // samples; the workgroup that completes the instance's last tile runs its tail
 template <int SCENE, typename R>
-__device__ __forceinline__ void batch_tile(const InstDesc& I, const ModelT<R>& M, int n_base, unsigned char* lds,
+__device__ __forceinline__ void batch_tile(const InstDesc& I, typename ModelRef<R>::Ptr M, int n_base, unsigned char* lds,
                                            float* sMup, int* s_last)
 {
     DevParams P = I.P;
@@ -496,7 +538,7 @@ __global__ __launch_bounds__(64) void batch_kernel(BatchArgs<R> a)
         const InstDesc& I = a.inst[i];
         DevParams P = I.P;
         P.step = I.step[0];
-        const ModelT<R>& M = a.models[__builtin_amdgcn_readfirstlane(I.model)];
+        const auto M = model_ref(&a.models[__builtin_amdgcn_readfirstlane(I.model)]);
         R* sB = reinterpret_cast<R*>(lds_raw);
         R* sTh = sB + P.H * P.nk;
         float* sHF = reinterpret_cast<float*>(sTh + 64 * 3 * kMaxKnots);
@@ -547,7 +589,7 @@ __global__ __launch_bounds__(64, sizeof(R) == 4 ? 2 : 1) void batch_kernel_all(B
         if (t >= total) break;
         const int packed = __builtin_amdgcn_readfirstlane(a.tile_map[t]);
         const InstDesc& I = a.inst[packed >> 8];
-        const ModelT<R>& M = a.models[__builtin_amdgcn_readfirstlane(I.model)];
+        const auto M = model_ref(&a.models[__builtin_amdgcn_readfirstlane(I.model)]);
         const int n_base = (packed & 255) * kTileSamples;
         switch (__builtin_amdgcn_readfirstlane(I.scene)) {
         case 0: batch_tile<0, R>(I, M, n_base, lds_raw, sMup, &s_last); break;

@@ -184,7 +184,8 @@ __device__ __forceinline__ void quat_step64(TabPtr t, double& qw, double& qx, do
 }
 
 // the penalty law of contact_law in FP64
-__device__ __forceinline__ void contact_law64(TabPtr t, const ModelT<double>& M, double delta, V3<double> n,
+template <typename MD>
+__device__ __forceinline__ void contact_law64(TabPtr t, const MD& M, double delta, V3<double> n,
                                               V3<double> vrel, V3<double>& F, double& eta)
 {
     const double vn = dot(n, vrel);
@@ -197,8 +198,8 @@ __device__ __forceinline__ void contact_law64(TabPtr t, const ModelT<double>& M,
 }
 
 // terrain below a sphere (r > 0) or point (r = 0), as terrain<> of the device header
-template <int SCENE>
-__device__ __forceinline__ bool terrain64(const ModelT<double>& M, const float* __restrict__ hf, V3<double> c,
+template <int SCENE, typename MD>
+__device__ __forceinline__ bool terrain64(const MD& M, const float* __restrict__ hf, V3<double> c,
                                           double r, double& delta, V3<double>& n)
 {
     if constexpr (SCENE != 1) {
@@ -348,7 +349,8 @@ struct LegRows {
 // Mass-matrix, bias and joint-torque terms.  Q, rb receive the leg's share of the trunk
 // rows (Q overwritten; the linear block and the hip offsets' own inertia, which are
 // constant, are in the model's totals leg_I*).
-__device__ __forceinline__ void leg_terms(const ModelT<double>& M, int leg, double sa, double ca, double sf, double cf,
+template <typename MD>
+__device__ __forceinline__ void leg_terms(const MD& M, int leg, double sa, double ca, double sf, double cf,
                                           double s12, double c12, const double* qd, const double* tau, double dt,
                                           double dtkd, V3<double> w, V3<double> vb, V3<double> gb, LegFrame& G,
                                           LegRows& S, double* Q, double* rb)
@@ -435,7 +437,8 @@ __device__ __forceinline__ void leg_terms(const ModelT<double>& M, int leg, doub
 // A contact on the foot with weight wgt (1: applied, 0: nothing added): nt the normal
 // toward the robot and vo the other body's velocity, both in the trunk frame.  Adds the
 // terms of the joint rows and of the trunk's rows; returns force (trunk frame) and secant.
-__device__ __forceinline__ void foot_contact(TabPtr t, const ModelT<double>& M, const LegFrame& G, double delta,
+template <typename MD>
+__device__ __forceinline__ void foot_contact(TabPtr t, const MD& M, const LegFrame& G, double delta,
                                              V3<double> nt, V3<double> vo, double dt, double wgt, LegRows& S, double* Q, double* rb,
                                              V3<double>& Ft, double& eta)
 {
@@ -483,6 +486,275 @@ __device__ __forceinline__ void rows_to_trunk(const LegFrame& G, const LegRows& 
         C[j][1] = L.y - G.hx * P.z;
         C[j][2] = L.z + G.hx * P.y - G.hy * P.x;
         C[j][3] = P.x; C[j][4] = P.y; C[j][5] = P.z;
+    }
+}
+
+// ------------------------------------------------------------------------------
+// the step of one sample on a quad of lanes (this lane owns leg `leg`), as quad_step: same
+// contacts and discretisation.  M: the model in constant memory (ConstModel), read in every
+// step k where it is used.  With the chip full (batched serving) the time is the instruction
+// count and the waves a SIMD holds: the step is arranged so that few values live long (two
+// waves per SIMD need 256 registers), robot first, then the box, with the contacts that are
+// rare (trunk corners, the box against the robot) in blocks entered only where a lane of the
+// wave has one.
+// ------------------------------------------------------------------------------
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef const __attribute__((address_space(4))) ModelT<double> ConstModel;
+__device__ __forceinline__ ConstModel& fresh_const_model(ConstModel* m, int k)
+{
+    asm("" : "+s"(m) : "s"(k));
+    return *m;
+}
+#else
+typedef const ModelT<double> ConstModel;
+__device__ __forceinline__ ConstModel& fresh_const_model(ConstModel* m, int) { return *m; }
+#endif
+
+__device__ __forceinline__ V3<double> pick(bool c, V3<double> a, V3<double> b)
+{
+    return v3(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z);
+}
+
+template <int SCENE>
+__device__ __forceinline__ void quad_step64(int k, ConstModel& M, const float* __restrict__ hf, double dt, double kp,
+                                            double kd, int leg, Base<double>& b, Leg<double>& lg, BoxS<double>& bx,
+                                            const double u[3], double& tau2)
+{
+    double tau[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) tau[j] = kp * (u[j] - lg.q[j]) - kd * lg.qd[j];
+
+    const M33<double> Rm = quat_R(b.qw, b.qx, b.qy, b.qz);
+    const V3<double> w = b.w, zero = v3(0.0, 0.0, 0.0), up = v3(0.0, 0.0, 1.0);
+    const V3<double> vb = mulT(Rm, b.vw);
+    [[maybe_unused]] M33<double> Rb;
+    [[maybe_unused]] V3<double> bh, th;
+    [[maybe_unused]] bool near_box = false;  // the trunk's and the box's bounding spheres can overlap
+    if constexpr (SCENE == 3) {
+        Rb = quat_R(bx.qw, bx.qx, bx.qy, bx.qz);
+        bh = v3<double>(M.bx_hx, M.bx_hy, M.bx_hz);
+        th = v3<double>(0.5 * M.tsx, 0.5 * M.tsy, 0.5 * M.tsz);
+        const V3<double> dc = b.p - bx.p;
+        near_box = dot(dc, dc) <= 2.0 * (dot(th, th) + dot(bh, bh));
+    }
+    [[maybe_unused]] auto box_vel = [&](V3<double> x) { return bx.vw + mul(Rb, cross(bx.w, mulT(Rb, x - bx.p))); };
+
+    double Q[21], rb[6], W[3][6], y0, y1, y2;
+    V3<double> F;
+    double eta;
+    // the foot's contact with the box, for the box's system below
+    [[maybe_unused]] V3<double> fb_x = zero, fb_n = up, fb_F = zero;
+    [[maybe_unused]] double fb_eta = 0.0, fb_c = 0.0;
+    [[maybe_unused]] bool fb = false;
+    {
+        LegFrame G;
+        LegRows S;
+        {
+            const V3<double> gb = (-M.g) * v3(Rm.m[6], Rm.m[7], Rm.m[8]);
+            double sa, ca, sf, cf, s12, c12;
+            const TabPtr t = fresh_table<0>(k);
+            sincos64(t, lg.q[0], &sa, &ca);
+            sincos64(t, lg.q[1], &sf, &cf);
+            sincos64(t, lg.q[1] + lg.q[2], &s12, &c12);
+            leg_terms(M, leg, sa, ca, sf, cf, s12, c12, lg.qd, tau, dt, dt * kd, w, vb, gb, G, S, Q, rb);
+        }
+        const V3<double> pfw = b.p + mul(Rm, foot_trunk(G));
+        double dT, dB = 0.0;
+        V3<double> nT, nB = zero;
+        const bool hitT = terrain64<SCENE>(M, hf, pfw, M.foot_r, dT, nT);
+        bool hitB = false;
+        if constexpr (SCENE == 2)
+            hitB = sphere_aabox64(pfw - v3<double>(M.sb_cx, M.sb_cy, M.sb_cz), M.foot_r,
+                                  v3<double>(M.sb_hx, M.sb_hy, M.sb_hz), dB, nB);
+        if constexpr (SCENE == 3) {
+            // outside the sphere around the box there is no contact ((r + |h|)^2 <= 2 (r^2 + |h|^2))
+            const V3<double> d = pfw - bx.p;
+            if (dot(d, d) <= 2.0 * (M.foot_r * M.foot_r + dot(bh, bh))) {
+                V3<double> nl = up;
+                hitB = sphere_aabox64(mulT(Rb, d), M.foot_r, bh, dB, nl);
+                nB = mul(Rb, nl);  // box -> foot (world)
+            }
+        }
+        // first contact: terrain if touched, else the box
+        const bool on = hitT || hitB, isB = !hitT && hitB;
+        if (on) {
+            V3<double> n, vo = zero;
+            if constexpr (SCENE == 0) {
+                n = v3(Rm.m[6], Rm.m[7], Rm.m[8]);
+            } else {
+                const V3<double> nw = pick(isB, nB, nT);
+                if constexpr (SCENE == 3) {
+                    if (isB) vo = mulT(Rm, box_vel(pfw - M.foot_r * nw));
+                }
+                n = mulT(Rm, nw);
+            }
+            foot_contact(fresh_table<1>(k), M, G, isB ? dB : dT, n, vo, dt, 1.0, S, Q, rb, F, eta);
+        }
+        if constexpr (SCENE == 2 || SCENE == 3) {
+            if (hitT && hitB) {
+                V3<double> vo = zero;
+                if constexpr (SCENE == 3) vo = mulT(Rm, box_vel(pfw - M.foot_r * nB));
+                foot_contact(fresh_table<4>(k), M, G, dB, mulT(Rm, nB), vo, dt, 1.0, S, Q, rb, F, eta);
+            }
+            if constexpr (SCENE == 3) {
+                if (hitB) {
+                    fb = true;
+                    fb_x = pfw - M.foot_r * nB;
+                    fb_n = nB;
+                    fb_F = -1.0 * mul(Rm, F);
+                    fb_eta = eta;
+                    fb_c = M.cc;
+                }
+            }
+        }
+        // eliminate the leg
+        double C[3][6];
+        rows_to_trunk(G, S, C);
+        const Ldl3 f3 = ldl3(S.A00, S.A01, S.A11, S.A02, S.A12, S.A22);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            double x0 = C[0][i], x1 = C[1][i], x2 = C[2][i];
+            f64::solve3(f3, x0, x1, x2);
+            W[0][i] = x0; W[1][i] = x1; W[2][i] = x2;
+#pragma unroll
+            for (int j = 0; j <= i; ++j) Q[s6(j, i)] -= C[0][j] * x0 + C[1][j] * x1 + C[2][j] * x2;
+        }
+        y0 = S.rl[0]; y1 = S.rl[1]; y2 = S.rl[2];
+        f64::solve3(f3, y0, y1, y2);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) rb[i] -= C[0][i] * y0 + C[1][i] * y1 + C[2][i] * y2;
+    }
+    // ---- two trunk corners per lane against terrain, static box and free box, and two box
+    // corners against the trunk (its side of the contact)
+#pragma unroll 1
+    for (int cc = 0; cc < 2; ++cc) {
+        const int ci = 2 * leg + cc;
+        const V3<double> r = v3((ci & 1 ? 0.5 : -0.5) * M.tsx, (ci & 2 ? 0.5 : -0.5) * M.tsy,
+                                (ci & 4 ? 0.5 : -0.5) * M.tsz);
+        const V3<double> pw = b.p + mul(Rm, r);
+        double delta;
+        V3<double> nw;
+        if (terrain64<SCENE>(M, hf, pw, 0.0, delta, nw)) {
+            const V3<double> n = mulT(Rm, nw);
+            contact_law64(fresh_table<3>(k), M, delta, n, vb + cross(w, r), F, eta);
+            body_terms(eta, M.cc, r, n, F, dt, Q, rb);
+        }
+        if constexpr (SCENE == 2) {
+            if (point_aabox(pw - v3<double>(M.sb_cx, M.sb_cy, M.sb_cz), v3<double>(M.sb_hx, M.sb_hy, M.sb_hz), delta,
+                            nw)) {
+                const V3<double> n = mulT(Rm, nw);
+                contact_law64(fresh_table<3>(k), M, delta, n, vb + cross(w, r), F, eta);
+                body_terms(eta, M.cc, r, n, F, dt, Q, rb);
+            }
+        }
+        if constexpr (SCENE == 3) {
+            if (near_box) {
+                V3<double> nl;
+                if (point_aabox(mulT(Rb, pw - bx.p), bh, delta, nl)) {
+                    const V3<double> n = mulT(Rm, mul(Rb, nl));
+                    contact_law64(fresh_table<3>(k), M, delta, n, vb + cross(w, r) - mulT(Rm, box_vel(pw)), F, eta);
+                    body_terms(eta, M.cc, r, n, F, dt, Q, rb);
+                }
+                const V3<double> cl = v3(ci & 1 ? bh.x : -bh.x, ci & 2 ? bh.y : -bh.y, ci & 4 ? bh.z : -bh.z);
+                const V3<double> xw = bx.p + mul(Rb, cl), lt = mulT(Rm, xw - b.p);
+                if (point_aabox(lt, th, delta, nl)) {  // nl: trunk face normal, toward the box corner
+                    contact_law64(fresh_table<3>(k), M, delta, -1.0 * nl, vb + cross(w, lt) - mulT(Rm, box_vel(xw)), F,
+                                  eta);
+                    body_terms(eta, M.cc, lt, -1.0 * nl, F, dt, Q, rb);
+                }
+            }
+        }
+    }
+
+    // ---- sum over the four legs, the trunk's own terms, solve
+#pragma unroll
+    for (int i = 0; i < 21; ++i) Q[i] = quad_sum(Q[i]);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) rb[i] = quad_sum(rb[i]);
+    tau2 = quad_sum(tau[0] * tau[0] + tau[1] * tau[1] + tau[2] * tau[2]);
+    Q[s6(0, 0)] += M.tr_Ix; Q[s6(1, 1)] += M.tr_Iy; Q[s6(2, 2)] += M.tr_Iz;
+    Q[s6(3, 3)] += M.mtot; Q[s6(4, 4)] += M.mtot; Q[s6(5, 5)] += M.mtot;
+    {
+        const V3<double> gy = cross(w, v3(M.I0x * w.x, M.I0y * w.y, M.I0z * w.z));
+        const double dm = -dt * M.m0 * M.g;
+        rb[0] -= dt * gy.x; rb[1] -= dt * gy.y; rb[2] -= dt * gy.z;
+        rb[3] += dm * Rm.m[6]; rb[4] += dm * Rm.m[7]; rb[5] += dm * Rm.m[8];
+    }
+    ldl6_solve(Q, rb);
+    double dq[3] = {y0, y1, y2};
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) dq[j] -= W[j][i] * rb[i];
+        lg.qd[j] += dq[j];
+        lg.q[j] += dt * lg.qd[j];
+    }
+    const V3<double> dw = v3(rb[0], rb[1], rb[2]), dvw = mul(Rm, v3(rb[3], rb[4], rb[5]));
+
+    // ---- the box: its corners on the ground, its side of the contacts above, its system
+    if constexpr (SCENE == 3) {
+        double Qb[21], rx[6];
+#pragma unroll
+        for (int i = 0; i < 21; ++i) Qb[i] = 0.0;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) rx[i] = 0.0;
+        const V3<double> nz = v3(Rb.m[6], Rb.m[7], Rb.m[8]), vl = mulT(Rb, bx.vw);
+        if (fb) body_terms(fb_eta, fb_c, mulT(Rb, fb_x - bx.p), mulT(Rb, fb_n), mulT(Rb, fb_F), dt, Qb, rx);
+#pragma unroll 1
+        for (int cc = 0; cc < 2; ++cc) {
+            const int ci = 2 * leg + cc;
+            const V3<double> cl = v3(ci & 1 ? bh.x : -bh.x, ci & 2 ? bh.y : -bh.y, ci & 4 ? bh.z : -bh.z);
+            const V3<double> xw = bx.p + mul(Rb, cl);
+            if (-xw.z > 0.0) {
+                contact_law64(fresh_table<5>(k), M, -xw.z, nz, vl + cross(bx.w, cl), F, eta);
+                body_terms(eta, M.cc, cl, nz, F, dt, Qb, rx);
+            }
+            if (near_box) {
+                const V3<double> r = v3((ci & 1 ? 0.5 : -0.5) * M.tsx, (ci & 2 ? 0.5 : -0.5) * M.tsy,
+                                        (ci & 4 ? 0.5 : -0.5) * M.tsz);
+                const V3<double> pw = b.p + mul(Rm, r), lb = mulT(Rb, pw - bx.p);
+                double delta;
+                V3<double> nl;
+                if (point_aabox(lb, bh, delta, nl)) {
+                    const V3<double> n = mulT(Rm, mul(Rb, nl));
+                    contact_law64(fresh_table<5>(k), M, delta, n, vb + cross(w, r) - mulT(Rm, box_vel(pw)), F, eta);
+                    body_terms(eta, M.cc, lb, nl, mulT(Rb, -1.0 * mul(Rm, F)), dt, Qb, rx);
+                }
+                const V3<double> lt = mulT(Rm, xw - b.p);
+                if (point_aabox(lt, th, delta, nl)) {
+                    contact_law64(fresh_table<5>(k), M, delta, -1.0 * nl, vb + cross(w, lt) - mulT(Rm, box_vel(xw)), F,
+                                  eta);
+                    body_terms(eta, M.cc, cl, mulT(Rb, mul(Rm, nl)), mulT(Rb, -1.0 * mul(Rm, F)), dt, Qb, rx);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 21; ++i) Qb[i] = quad_sum(Qb[i]);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) rx[i] = quad_sum(rx[i]);
+        Qb[s6(0, 0)] += M.bx_Ix; Qb[s6(1, 1)] += M.bx_Iy; Qb[s6(2, 2)] += M.bx_Iz;
+        Qb[s6(3, 3)] += M.bx_m; Qb[s6(4, 4)] += M.bx_m; Qb[s6(5, 5)] += M.bx_m;
+        const V3<double> gy = cross(bx.w, v3(M.bx_Ix * bx.w.x, M.bx_Iy * bx.w.y, M.bx_Iz * bx.w.z));
+        const double dm = -dt * M.bx_m * M.g;
+        rx[0] -= dt * gy.x; rx[1] -= dt * gy.y; rx[2] -= dt * gy.z;
+        rx[3] += dm * nz.x; rx[4] += dm * nz.y; rx[5] += dm * nz.z;
+        ldl6_solve(Qb, rx);
+        bx.w = bx.w + v3(rx[0], rx[1], rx[2]);
+        bx.vw = bx.vw + mul(Rb, v3(rx[3], rx[4], rx[5]));
+        bx.p = bx.p + dt * bx.vw;
+    }
+    b.w = w + dw;
+    b.vw = b.vw + dvw;
+    b.p = b.p + dt * b.vw;
+    if constexpr (SCENE != 3) {
+        quat_step64(fresh_table<2>(k), b.qw, b.qx, b.qy, b.qz, b.w, dt);
+    } else {
+        // one quaternion step per lane: the trunk's on even lanes, the box's on odd lanes
+        const bool odd = (leg & 1) != 0;
+        double q0 = odd ? bx.qw : b.qw, q1 = odd ? bx.qx : b.qx, q2 = odd ? bx.qy : b.qy, q3 = odd ? bx.qz : b.qz;
+        quat_step64(fresh_table<2>(k), q0, q1, q2, q3, pick(odd, bx.w, b.w), dt);
+        b.qw = dpp<0x00>(q0); b.qx = dpp<0x00>(q1); b.qy = dpp<0x00>(q2); b.qz = dpp<0x00>(q3);
+        bx.qw = dpp<0x55>(q0); bx.qx = dpp<0x55>(q1); bx.qy = dpp<0x55>(q2); bx.qz = dpp<0x55>(q3);
     }
 }
 
