@@ -188,10 +188,12 @@ void drop_graph(mppi_batch* b)
     b->cap_policy_ws = nullptr;
 }
 
+// LDS of a tile: the spline basis and the lanes' knots.  The heightfield is read from
+// global memory (16 KiB of it in LDS held FP64 to four workgroups a CU, one wave per SIMD).
 size_t batch_lds(const mppi_batch* b)
 {
     const size_t rb = b->arith == 1 ? sizeof(float) : sizeof(double);
-    return rb * ((size_t)b->max_H * MPPI_MAX_KNOTS + 64 * 3 * MPPI_MAX_KNOTS) + sizeof(float) * (size_t)b->max_hf;
+    return rb * ((size_t)b->max_H * MPPI_MAX_KNOTS + 64 * 3 * MPPI_MAX_KNOTS);
 }
 
 // rebuild the table and the per-scene tile maps in the pinned mirrors; queue the upload
@@ -411,7 +413,8 @@ mppi_status mppi_batch_create(int max_instances, int max_horizon, int max_hf_cel
     b->max_H = max_horizon;
     b->max_hf = max_hf_cells;
     b->arith = arith;
-    if (batch_lds(b) > 65536) {
+    // the documented limit counts the heightfield as well
+    if (batch_lds(b) + sizeof(float) * (size_t)b->max_hf > 65536) {
         delete b;
         return bfail(nullptr, MPPI_EINVAL, "max_horizon and max_hf_cells exceed the 64 KiB LDS stage");
     }

@@ -77,7 +77,8 @@ __device__ __forceinline__ void step_of(int k, typename ModelRef<R>::Ptr M, cons
 
 // ---------------------------------------------------------------------------------
 // Rollout of the samples of one workgroup: quad q of the block handles sample
-// n = n_base + q.  sB (spline basis, type R) and sHF (heightfield) are in LDS.
+// n = n_base + q.  sB (spline basis, type R) is in LDS; sHF (heightfield) too, or in global
+// memory (batched serving).
 // eps addressing: eps_in[n * eps_sn + d * eps_sd] when given; otherwise Philox noise,
 // stored to eps_out[d * K + n] (dimension-major for the update's coalesced reads).
 // The state is rounded to FP32 after every step; the step itself runs in R.
@@ -162,12 +163,9 @@ __device__ __forceinline__ void rollout_samples(typename ModelRef<R>::Ptr M, con
 }
 
 template <typename R>
-__device__ __forceinline__ void stage_lds(const DevParams& P, int scene, int hf_cells, const double* __restrict__ gB,
-                                          const float* __restrict__ ghf, R* sB, float* sHF)
+__device__ __forceinline__ void stage_basis(const DevParams& P, const double* __restrict__ gB, R* sB)
 {
     for (int i = threadIdx.x; i < P.H * P.nk; i += blockDim.x) sB[i] = (R)gB[i];
-    if (scene == 1)
-        for (int i = threadIdx.x; i < hf_cells; i += blockDim.x) sHF[i] = ghf[i];
 }
 
 // standalone rollout: block of 4*SPB lanes handles SPB consecutive samples
@@ -182,7 +180,9 @@ __global__ __launch_bounds__(256) void rollout_kernel(ModelT<R> M, DevParams P, 
     R* sB = reinterpret_cast<R*>(lds_raw);
     R* sTh = sB + P.H * P.nk;
     float* sHF = reinterpret_cast<float*>(sTh + blockDim.x * 3 * kMaxKnots);
-    stage_lds(P, SCENE, M.hf_nx * M.hf_ny, gB, ghf, sB, sHF);
+    stage_basis(P, gB, sB);
+    if constexpr (SCENE == 1)
+        for (int i = threadIdx.x; i < M.hf_nx * M.hf_ny; i += blockDim.x) sHF[i] = ghf[i];
     __syncthreads();
     rollout_samples<SCENE, R>(model_arg(M), P, sB, sHF, sTh, mu, x0, eps_in, eps_sn, eps_sd, eps_out, costs, traj,
                               blockIdx.x * (blockDim.x >> 2));
@@ -351,14 +351,10 @@ __global__ __launch_bounds__(256) void sim_step_kernel(ModelT<R> M, int nstate, 
                                                        float* __restrict__ xo, float* __restrict__ tau_out,
                                                        const float* __restrict__ ghf)
 {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    float* sHF = reinterpret_cast<float*>(lds_raw);
+    // the heightfield stays in global memory: a state reads 4 values of it for each foot and
+    // trunk corner, where staging it would read every value (4096 in the terrain workload) in
+    // every workgroup of 16 states
     const int tid = threadIdx.x;
-    if constexpr (SCENE == 1) {
-        const int nhf = M.hf_nx * M.hf_ny;
-        for (int i = tid; i < nhf; i += blockDim.x) sHF[i] = ghf[i];
-    }
-    __syncthreads();
     const int leg = tid & 3;
     const int n = blockIdx.x * (blockDim.x >> 2) + (tid >> 2);
     const bool valid = n < nstate;
@@ -375,7 +371,7 @@ __global__ __launch_bounds__(256) void sim_step_kernel(ModelT<R> M, int nstate, 
         tauv[j] = R(kp) * (uu[j] - lg.q[j]) - R(kd) * lg.qd[j];
     }
     R tau2;
-    step_of<SCENE, R>(0, model_arg(M), sHF, R(dt), R(kp), R(kd), leg, b, lg, bx, uu, tau2);
+    step_of<SCENE, R>(0, model_arg(M), ghf, R(dt), R(kp), R(kd), leg, b, lg, bx, uu, tau2);
     if (!valid) return;
     store_state(xo + (size_t)n * nx, leg, b, lg);
     if (SCENE == 3 && leg == 0) store_box(xo + (size_t)n * nx, bx);
@@ -428,6 +424,8 @@ __device__ __forceinline__ void plant_step(typename ModelRef<R>::Ptr M, const De
     }
 }
 
+constexpr int kTailDims = 6, kTailUnroll = 4;
+
 template <int SCENE, typename R>
 __device__ __forceinline__ void instance_tail(const InstDesc& I, const DevParams& P, typename ModelRef<R>::Ptr M, const float* sHF,
                               float* sMup)
@@ -449,12 +447,40 @@ __device__ __forceinline__ void instance_tail(const InstDesc& I, const DevParams
     }
     s = wave_sum(s);
     __syncthreads();  // weights visible to the whole workgroup (one wave)
-    for (int d = 0; d < D; ++d) {
-        float acc = 0.f;
-        for (int n = t; n < K; n += 64)
-            if (n > 0) acc += I.w[n] * I.eps[(size_t)d * K + n];
-        acc = wave_sum(acc);
-        if (t == 0) sMup[d] = none ? I.mu[d] : I.mu[d] + P.sigma * (acc / s);
+    // kTailDims dimensions (12 nk of them) over kTailUnroll samples per lane at a time, all
+    // their loads issued before any is used: the walk over the noise is one wave's, and it is
+    // bound by the round trips it makes one after the other.  Each lane still adds its samples
+    // in increasing order, dimension by dimension.  The last instances' tails end a batch step:
+    // with the heightfield left out of LDS and this walk, a step of 48 mixed controllers went
+    // from 2317 to 1326 us in FP64 and from 2380 to 1165 us in FP32.
+    for (int d0 = 0; d0 < D; d0 += kTailDims) {
+        float acc[kTailDims];
+#pragma unroll
+        for (int q = 0; q < kTailDims; ++q) acc[q] = 0.f;
+        const float* __restrict__ eps = I.eps + (size_t)d0 * K;
+        for (int n0 = t; n0 < K; n0 += 64 * kTailUnroll) {
+            float wv[kTailUnroll], ev[kTailUnroll][kTailDims];
+#pragma unroll
+            for (int v = 0; v < kTailUnroll; ++v) {
+                const int n = n0 + 64 * v, nr = min(n, K - 1);
+                wv[v] = I.w[nr];
+#pragma unroll
+                for (int q = 0; q < kTailDims; ++q) ev[v][q] = eps[(size_t)q * K + nr];
+            }
+#pragma unroll
+            for (int v = 0; v < kTailUnroll; ++v) {
+                const int n = n0 + 64 * v;
+                if (n > 0 && n < K) {
+#pragma unroll
+                    for (int q = 0; q < kTailDims; ++q) acc[q] += wv[v] * ev[v][q];
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kTailDims; ++q) {
+            const float r = wave_sum(acc[q]);
+            if (t == 0) sMup[d0 + q] = none ? I.mu[d0 + q] : I.mu[d0 + q] + P.sigma * (r / s);
+        }
     }
     __syncthreads();
     if (t < 12) I.u0[t] = sMup[t * nk];
@@ -477,7 +503,7 @@ __device__ __forceinline__ void instance_tail(const InstDesc& I, const DevParams
     }
 }
 
-// one tile of one instance: stage its basis (and heightfield) in LDS, roll out its 16
+// one tile of one instance: stage its basis in LDS, roll out its 16
 // samples; the workgroup that completes the instance's last tile runs its tail
 template <int SCENE, typename R>
 __device__ __forceinline__ void batch_tile(const InstDesc& I, typename ModelRef<R>::Ptr M, int n_base, unsigned char* lds,
@@ -487,12 +513,11 @@ __device__ __forceinline__ void batch_tile(const InstDesc& I, typename ModelRef<
     P.step = I.step[0];
     R* sB = reinterpret_cast<R*>(lds);
     R* sTh = sB + P.H * P.nk;
-    float* sHF = reinterpret_cast<float*>(sTh + 64 * 3 * kMaxKnots);
-    stage_lds(P, SCENE, I.hf_cells, I.B, I.hf, sB, sHF);
+    stage_basis(P, I.B, sB);
     __syncthreads();
     // Philox noise drawn here and stored for the tail, or the given dimension-major noise
     const float* ein = I.explicit_eps ? I.eps : nullptr;
-    rollout_samples<SCENE, R>(M, P, sB, sHF, sTh, I.mu, I.x, ein, 1, P.K, ein ? nullptr : I.eps, I.costs, nullptr,
+    rollout_samples<SCENE, R>(M, P, sB, I.hf, sTh, I.mu, I.x, ein, 1, P.K, ein ? nullptr : I.eps, I.costs, nullptr,
                               n_base);
     __threadfence();
     __syncthreads();
@@ -500,7 +525,7 @@ __device__ __forceinline__ void batch_tile(const InstDesc& I, typename ModelRef<
     __syncthreads();
     if (*s_last) {
         __threadfence();
-        instance_tail<SCENE, R>(I, P, M, sHF, sMup);
+        instance_tail<SCENE, R>(I, P, M, I.hf, sMup);
         __threadfence();
     }
     __syncthreads();
@@ -519,9 +544,10 @@ __device__ __forceinline__ void batch_exit(const BatchArgs<R>& a)
     }
 }
 
-// one persistent kernel per scene: its own queue of that scene's tiles
+// one persistent kernel per scene: its own queue of that scene's tiles (two waves per SIMD in
+// FP32, which fits, one in FP64, as below)
 template <int SCENE, typename R>
-__global__ __launch_bounds__(64) void batch_kernel(BatchArgs<R> a)
+__global__ __launch_bounds__(64, sizeof(R) == 4 ? 2 : 1) void batch_kernel(BatchArgs<R> a)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     __shared__ int s_tile, s_last;
@@ -541,13 +567,12 @@ __global__ __launch_bounds__(64) void batch_kernel(BatchArgs<R> a)
         const auto M = model_ref(&a.models[__builtin_amdgcn_readfirstlane(I.model)]);
         R* sB = reinterpret_cast<R*>(lds_raw);
         R* sTh = sB + P.H * P.nk;
-        float* sHF = reinterpret_cast<float*>(sTh + 64 * 3 * kMaxKnots);
-        stage_lds(P, SCENE, I.hf_cells, I.B, I.hf, sB, sHF);
+        stage_basis(P, I.B, sB);
         __syncthreads();
         const int n_base = (t - I.tile0) * kTileSamples;
         // Philox noise drawn here and stored for the tail, or the given dimension-major noise
         const float* ein = I.explicit_eps ? I.eps : nullptr;
-        rollout_samples<SCENE, R>(M, P, sB, sHF, sTh, I.mu, I.x, ein, 1, P.K, ein ? nullptr : I.eps, I.costs, nullptr,
+        rollout_samples<SCENE, R>(M, P, sB, I.hf, sTh, I.mu, I.x, ein, 1, P.K, ein ? nullptr : I.eps, I.costs, nullptr,
                                   n_base);
         __threadfence();
         __syncthreads();
@@ -555,7 +580,7 @@ __global__ __launch_bounds__(64) void batch_kernel(BatchArgs<R> a)
         __syncthreads();
         if (s_last) {
             __threadfence();
-            instance_tail<SCENE, R>(I, P, M, sHF, sMup);
+            instance_tail<SCENE, R>(I, P, M, I.hf, sMup);
             __threadfence();
         }
         __syncthreads();
@@ -573,7 +598,8 @@ __global__ __launch_bounds__(64) void batch_kernel(BatchArgs<R> a)
 // row and the tile's index inside its instance (row << 8 | tile); each tile branches to
 // its scene's code (uniform over the workgroup).  In FP32 the four scenes' code together
 // needs a few registers more than half the file; it is held to two waves per SIMD (the
-// per-scene FP32 kernels' occupancy), in FP64 to one.
+// per-scene FP32 kernels' occupancy).  FP64 takes one: held to two, its pushing scene spills
+// 1.1 KB a lane and a step of 48 mixed controllers takes 2659 us against 1326.
 template <typename R>
 __global__ __launch_bounds__(64, sizeof(R) == 4 ? 2 : 1) void batch_kernel_all(BatchArgs<R> a)
 {
@@ -660,9 +686,8 @@ static hipError_t launch_sim_step_t(const ModelT<R>& M, int n, int nx, const flo
 {
     const int spb = 16;
     const int blocks = (n + spb - 1) / spb;
-    const size_t lds = (M.scene == 1) ? (size_t)M.hf_nx * M.hf_ny * sizeof(float) : 0;
 #define MPPI_LAUNCH_SIM(S)                                                                                      \
-    hipLaunchKernelGGL((sim_step_kernel<S, R>), dim3(blocks), dim3(4 * spb), lds, st, M, n, nx, x, u, kp, kd, dt, \
+    hipLaunchKernelGGL((sim_step_kernel<S, R>), dim3(blocks), dim3(4 * spb), 0, st, M, n, nx, x, u, kp, kd, dt, \
                        xo, tau, hf)
     switch (M.scene) {
     case 0: MPPI_LAUNCH_SIM(0); break;
