@@ -226,7 +226,13 @@ __device__ __forceinline__ constexpr int s6(int i, int j)
 template <int CTRL>
 __device__ __forceinline__ int dpp_i(int v)
 {
+#if defined(__HIP_DEVICE_COMPILE__)
+    // no value for lanes without a source (a quad permute has none): one instruction, or part
+    // of the operation that uses it, where a given value costs a move of its own
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
+#else
     return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+#endif
 }
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v)
@@ -696,11 +702,10 @@ __device__ __forceinline__ void box_share(const ModelT<R>& M, const BoxS<R>& bx,
     base_contact(eta, M.cc, mulT(bf.Rb, x - bx.p), mulT(bf.Rb, nw), mulT(bf.Rb, Fw), dt, Qb, rbx);
 }
 // quaternion update q <- normalize(q (x) exp(dt w / 2)) (body-frame angular velocity)
+// by the half-angle vector ph = dt w / 2 of length a
 template <typename R>
-__device__ __forceinline__ void quat_step(R& qw, R& qx, R& qy, R& qz, V3<R> w, R dt)
+__device__ __forceinline__ void quat_turn(R& qw, R& qx, R& qy, R& qz, V3<R> ph, R a)
 {
-    const V3<R> ph = (R(0.5) * dt) * w;
-    const R a = m_sqrt(dot(ph, ph));
     R sc, dw;
     quat_exp(a, &sc, &dw);
     const R dx = sc * ph.x, dy = sc * ph.y, dz = sc * ph.z;
@@ -710,6 +715,13 @@ __device__ __forceinline__ void quat_step(R& qw, R& qx, R& qy, R& qz, V3<R> w, R
     const R nz = qw * dz + qx * dy - qy * dx + qz * dw;
     const R inv = R(1) / m_sqrt(nw * nw + nx * nx + ny * ny + nz * nz);
     qw = nw * inv; qx = nx * inv; qy = ny * inv; qz = nz * inv;
+}
+
+template <typename R>
+__device__ __forceinline__ void quat_step(R& qw, R& qx, R& qy, R& qz, V3<R> w, R dt)
+{
+    const V3<R> ph = (R(0.5) * dt) * w;
+    quat_turn(qw, qx, qy, qz, ph, m_sqrt(dot(ph, ph)));
 }
 
 // ------------------------------------------------------------------------------

@@ -535,7 +535,7 @@ __device__ __forceinline__ void quad_step64(int k, ConstModel& M, const float* _
         bh = v3<double>(M.bx_hx, M.bx_hy, M.bx_hz);
         th = v3<double>(0.5 * M.tsx, 0.5 * M.tsy, 0.5 * M.tsz);
         const V3<double> dc = b.p - bx.p;
-        near_box = dot(dc, dc) <= 2.0 * (dot(th, th) + dot(bh, bh));
+        near_box = dot(dc, dc) <= 2.001 * (dot(th, th) + dot(bh, bh));
     }
     [[maybe_unused]] auto box_vel = [&](V3<double> x) { return bx.vw + mul(Rb, cross(bx.w, mulT(Rb, x - bx.p))); };
 
@@ -567,9 +567,10 @@ __device__ __forceinline__ void quad_step64(int k, ConstModel& M, const float* _
             hitB = sphere_aabox64(pfw - v3<double>(M.sb_cx, M.sb_cy, M.sb_cz), M.foot_r,
                                   v3<double>(M.sb_hx, M.sb_hy, M.sb_hz), dB, nB);
         if constexpr (SCENE == 3) {
-            // outside the sphere around the box there is no contact ((r + |h|)^2 <= 2 (r^2 + |h|^2))
+            // outside the sphere around the box there is no contact ((r + |h|)^2 <= 2 (r^2 + |h|^2),
+            // with a margin for the rounding)
             const V3<double> d = pfw - bx.p;
-            if (dot(d, d) <= 2.0 * (M.foot_r * M.foot_r + dot(bh, bh))) {
+            if (dot(d, d) <= 2.001 * (M.foot_r * M.foot_r + dot(bh, bh))) {
                 V3<double> nl = up;
                 hitB = sphere_aabox64(mulT(Rb, d), M.foot_r, bh, dB, nl);
                 nB = mul(Rb, nl);  // box -> foot (world)

@@ -29,6 +29,10 @@
 namespace mppi {
 namespace r16 {
 
+struct alignas(16) Quad {
+    float v[4];
+};
+
 constexpr int kSamples = 4;     // samples per workgroup (one wave)
 constexpr int kNVMax = 55;      // summed values: trunk system 21 + 6, torque^2, box system 21 + 6
 constexpr int kPitch = 20;      // LDS row pitch of one summed value over the 16 lanes (16 used)
@@ -40,6 +44,25 @@ __device__ __forceinline__ constexpr int n_summed()
     return SCENE == 3 ? 55 : 28;
 }
 
+// LDS per sample (values of type S): [0, kBoxRow) a region used in turn for the trunk corners'
+// rows (27 x kPitch) and for the legs' values (4 x kLegPitch) and eliminated columns (4 x
+// kElimPitch); in the pushing scene the box's rows follow at kBoxRow (27 x kPitch)
+constexpr int kLegPitch = 28, kElimPitch = 50, kElimRow = 4 * kLegPitch, kBoxRow = 28 * kPitch;
+
+// where lane g's summed values g and g + 16 of the trunk's 28 (21 + 6 + torque^2) stand in a
+// leg's eliminated columns (6 rows x 8 columns; column 6 is the right side, 7 zeros)
+__device__ __forceinline__ int elim_slot(int e)
+{
+    if (e >= 27) return 7;
+    if (e >= 21) return (e - 21) * 8 + 6;
+    int i = 0, first = 0;
+    while (e - first >= 6 - i) first += 6 - i++;
+    return i * 8 + i + (e - first);
+}
+
+// bounding spheres of two bodies: (r1 + r2)^2 <= 2 (r1^2 + r2^2), with a margin for the rounding
+constexpr double kNear = 2.001;
+
 // fixed-order sum of the 16 partials of one value
 template <typename R>
 __device__ __forceinline__ R sum16(const R* p)
@@ -49,6 +72,16 @@ __device__ __forceinline__ R sum16(const R* p)
     for (int i = 0; i < 8; ++i) a[i] = p[2 * i] + p[2 * i + 1];
 #pragma unroll
     for (int i = 0; i < 4; ++i) a[i] = a[2 * i] + a[2 * i + 1];
+    return (a[0] + a[1]) + (a[2] + a[3]);
+}
+
+// the same for 8 of them
+template <typename R>
+__device__ __forceinline__ R sum8(const R* p)
+{
+    R a[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = p[2 * i] + p[2 * i + 1];
     return (a[0] + a[1]) + (a[2] + a[3]);
 }
 
@@ -92,6 +125,15 @@ template <typename T, typename U>
 __device__ __forceinline__ V3<T> cv(V3<U> a)
 {
     return V3<T>{T(a.x), T(a.y), T(a.z)};
+}
+
+// A a with the products added in a stated order: the compiler's choice of the products it
+// fuses would otherwise move FP32 roundings when the code around it changes
+template <typename R>
+__device__ __forceinline__ V3<R> mul_ordered(const M33<R>& A, V3<R> a)
+{
+    return v3(R(fma(A.m[2], a.z, fma(A.m[1], a.y, A.m[0] * a.x))), R(fma(A.m[5], a.z, fma(A.m[4], a.y, A.m[3] * a.x))),
+              R(fma(A.m[8], a.z, fma(A.m[7], a.y, A.m[6] * a.x))));
 }
 
 // a contact on the leg's calf with weight wgt (1: applied, 0: nothing added).  The contact
@@ -154,8 +196,8 @@ __device__ __forceinline__ void body_contact(R eta, R c, V3<R> r, V3<R> n, V3<R>
 // ------------------------------------------------------------------------------
 template <int SCENE, typename R, typename S>
 __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS, const float* __restrict__ hf, S dt,
-                                       S kp, S kd, int g, Base<R>& b, Leg<R>& lg, BoxS<R>& bx, R uj, S* red,
-                                       S* sred, R& tau2)
+                                       S kp, S kd, int g, int eo0, int eo1, Base<R>& b, Leg<R>& lg, BoxS<R>& bx,
+                                       R uj, S* red, S* sred, R& tau2)
 {
     const int leg = g >> 2, sub = g & 3;
     const R dtr = R(dt);
@@ -274,21 +316,17 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
     L.A00 += dt * kd; L.A11 += dt * kd; L.A22 += dt * kd;
 
     [[maybe_unused]] BoxFrame<R> bf;
-    [[maybe_unused]] S Qb[21], rbx[6];
     const V3<R> zero = v3(R(0), R(0), R(0));
     V3<R> F;
     R eta;
-    if constexpr (SCENE == 3) {
-        bf.Rb = quat_R(bx.qw, bx.qx, bx.qy, bx.qz);
-#pragma unroll
-        for (int i = 0; i < 21; ++i) Qb[i] = S(0);
-#pragma unroll
-        for (int i = 0; i < 6; ++i) rbx[i] = S(0);
-    }
+    if constexpr (SCENE == 3) bf.Rb = quat_R(bx.qw, bx.qx, bx.qy, bx.qz);
 
     // ---- the leg's foot against terrain and the static or free box.  Each lane lists its
     // foot's contacts (terrain, box) and the wave runs one contact body per listed entry:
     // usually one pass, a second only where a foot touches both.
+    [[maybe_unused]] bool foot_box = false;   // some lane of the wave has its foot on the box
+    [[maybe_unused]] R fb_eta = R(0), fb_c = R(0);
+    [[maybe_unused]] V3<R> fb_r = zero, fb_n = zero, fb_F = zero;  // this lane's share for the box's system
     {
         const V3<R> pfw = b.p + mul(Rm, G.pf);
         R dT, dB = R(0);
@@ -300,9 +338,13 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
                                 dB, nB);
         }
         if constexpr (SCENE == 3) {
-            V3<R> nl = v3(R(0), R(0), R(1));  // left as is when the foot misses the box
-            hitB = sphere_aabox(mulT(bf.Rb, pfw - bx.p), MR.foot_r, v3(MR.bx_hx, MR.bx_hy, MR.bx_hz), dB, nl);
-            nB = mul(bf.Rb, nl);  // box -> foot (world)
+            // outside the sphere around the box there is no contact
+            const V3<R> d = pfw - bx.p, bh = v3(MR.bx_hx, MR.bx_hy, MR.bx_hz);
+            if (__builtin_amdgcn_ballot_w64(dot(d, d) <= R(kNear) * (MR.foot_r * MR.foot_r + dot(bh, bh)))) {
+                V3<R> nl = v3(R(0), R(0), R(1));  // left as is when the foot misses the box
+                hitB = sphere_aabox(mulT(bf.Rb, d), MR.foot_r, bh, dB, nl);
+                nB = mul(bf.Rb, nl);  // box -> foot (world)
+            }
         }
         const int cnt = int(hitT) + int(hitB);
 #pragma unroll
@@ -317,203 +359,313 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
             const V3<R> nw = on ? selv(isB, nB, nT) : v3(R(0), R(0), R(1));
             const V3<R> n = mulT(Rm, nw);
             V3<R> vo = zero;
+            // the box's velocity and its share of the contact, only while a foot of the wave
+            // touches it
             [[maybe_unused]] V3<R> pcw;
+            [[maybe_unused]] bool box_pass = false;
             if constexpr (SCENE == 3) {
-                pcw = pfw - MR.foot_r * nw;
-                vo = selv(isB && on, mulT(Rm, box_point_vel(bx, bf, pcw)), zero);
+                box_pass = __builtin_amdgcn_ballot_w64(isB && on) != 0;
+                if (box_pass) {
+                    pcw = pfw - MR.foot_r * nw;
+                    vo = selv(isB && on, mulT(Rm, box_point_vel(bx, bf, pcw)), zero);
+                }
             }
             leg_contact_w(MR, G, vb, w, lg.qd, delta, n, G.pf - MR.foot_r * n, vo, dt, wgt, Q, rb, L, F, eta);
             if constexpr (SCENE == 3) {
-                // the box's share in its frame (zero weight for the terrain contact)
-                const R wb = isB ? wgt : R(0);
-                body_contact(wb * eta, wb * MR.cc, mulT(bf.Rb, pcw - bx.p), mulT(bf.Rb, nw),
-                             mulT(bf.Rb, (-wb) * mul(Rm, F)), dt, Qb, rbx);
-            }
-        }
-    }
-
-    // ---- eliminate the leg: W = A_ll^-1 A_l0, y = A_ll^-1 r_l
-    const Chol3<S> L3 = chol3(L.A00, L.A01, L.A11, L.A02, L.A12, L.A22);
-    S W[3][6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        S x0 = L.C[0][i], x1 = L.C[1][i], x2 = L.C[2][i];
-        solve3(L3, x0, x1, x2);
-        W[0][i] = x0; W[1][i] = x1; W[2][i] = x2;
-    }
-    S y0 = L.rl[0], y1 = L.rl[1], y2 = L.rl[2];
-    solve3(L3, y0, y1, y2);
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-#pragma unroll
-        for (int j = i; j < 6; ++j) Q[s6(i, j)] -= L.C[0][i] * W[0][j] + L.C[1][i] * W[1][j] + L.C[2][i] * W[2][j];
-        rb[i] -= L.C[0][i] * y0 + L.C[1][i] * y1 + L.C[2][i] * y2;
-    }
-
-    // the leg's terms are the same in its four lanes: only sub-lane 0's copy is summed
-    const bool keep = sub == 0;
-#pragma unroll
-    for (int i = 0; i < 21; ++i) Q[i] = sel(keep, Q[i], S(0));
-#pragma unroll
-    for (int i = 0; i < 6; ++i) rb[i] = sel(keep, rb[i], S(0));
-    if constexpr (SCENE == 3) {
-#pragma unroll
-        for (int i = 0; i < 21; ++i) Qb[i] = sel(keep, Qb[i], S(0));
-#pragma unroll
-        for (int i = 0; i < 6; ++i) rbx[i] = sel(keep, rbx[i], S(0));
-    }
-
-    // ---- one corner per lane: trunk corner g (g < 8), free-box corner g - 8 (g >= 8)
-    if constexpr (SCENE != 3) {
-        if (g < 8) {
-            const V3<R> rloc = v3((g & 1 ? R(0.5) : R(-0.5)) * MR.tsx, (g & 2 ? R(0.5) : R(-0.5)) * MR.tsy,
-                                  (g & 4 ? R(0.5) : R(-0.5)) * MR.tsz);
-            const V3<R> pw = b.p + mul(Rm, rloc);
-            R delta;
-            V3<R> nw;
-            if (terrain<SCENE>(MR, hf, pw, R(0), delta, nw)) {
-                const V3<R> n = mulT(Rm, nw);
-                contact_law(MR, delta, n, vb + cross(w, rloc), F, eta);
-                body_contact(eta, MR.cc, rloc, n, F, dt, Q, rb);
-            }
-            if constexpr (SCENE == 2) {
-                if (point_aabox(pw - v3(MR.sb_cx, MR.sb_cy, MR.sb_cz), v3(MR.sb_hx, MR.sb_hy, MR.sb_hz), delta, nw)) {
-                    const V3<R> n = mulT(Rm, nw);
-                    contact_law(MR, delta, n, vb + cross(w, rloc), F, eta);
-                    body_contact(eta, MR.cc, rloc, n, F, dt, Q, rb);
+                if (box_pass) {
+                    // the box's share in its frame (added below; a lane has one box contact at most)
+                    foot_box = true;
+                    const bool mine = isB && on;
+                    const R wb = isB ? wgt : R(0);
+                    fb_eta = sel(mine, eta, fb_eta);
+                    fb_c = sel(mine, MR.cc, fb_c);
+                    fb_r = selv(mine, mulT(bf.Rb, pcw - bx.p), fb_r);
+                    fb_n = selv(mine, mulT(bf.Rb, nw), fb_n);
+                    fb_F = selv(mine, mulT(bf.Rb, (-wb) * mul(Rm, F)), fb_F);
                 }
             }
         }
-    } else {
-        // A corner of body P (the trunk on lanes 0-7, the box on lanes 8-15) against the
-        // other body Q (a point inside Q's box, normal out of Q's nearest face) and against
-        // the terrain.  The same code serves both roles: each contact adds its terms to the
-        // trunk's and the box's 6x6 systems in their own frames, with zero weight where a
-        // body is not part of the contact.
-        const bool own_trunk = g < 8;
-        const int ci = g & 7;
-        Pose<R> PT, PB;
-        PT.Rt = Rm; PT.p = b.p; PT.vw = b.vw; PT.w = b.w;
-        PB.Rt = bf.Rb; PB.p = bx.p; PB.vw = bx.vw; PB.w = bx.w;
-        const Pose<R> own = sel_pose(own_trunk, PT, PB), oth = sel_pose(own_trunk, PB, PT);
-        const V3<R> th = v3(R(0.5) * MR.tsx, R(0.5) * MR.tsy, R(0.5) * MR.tsz), bh = v3(MR.bx_hx, MR.bx_hy, MR.bx_hz);
-        const V3<R> hP = selv(own_trunk, th, bh), hQ = selv(own_trunk, bh, th);
-        const V3<R> cl = v3(ci & 1 ? hP.x : -hP.x, ci & 2 ? hP.y : -hP.y, ci & 4 ? hP.z : -hP.z);
-        const V3<R> x = own.p + mul(own.Rt, cl);
-        const V3<R> lq = mulT(oth.Rt, x - oth.p);
-        R dP = R(0), dG;
-        V3<R> nlq = zero, nG;
-        const bool hitP = point_aabox(lq, hQ, dP, nlq);  // nlq: Q's face normal toward the corner
-        const bool hitG = terrain<SCENE>(MR, hf, x, R(0), dG, nG);
-        const int cnt = int(hitP) + int(hitG);
-        if (__builtin_amdgcn_ballot_w64(cnt > 0)) {
-            const V3<R> vP = pose_point_vel(own, x), vQ = pose_point_vel(oth, x);
-            const V3<R> nPw = mul(oth.Rt, nlq);
-#pragma unroll
-            for (int it = 0; it < 2; ++it) {
-                if (!__builtin_amdgcn_ballot_w64(it < cnt)) break;
-                const bool pair = (it == 0) && hitP;  // pass 0: the pair if touching, else the terrain
-                // a lane without a contact in this pass takes a neutral one (zero depth and
-                // velocity, zero weight), so nothing it adds can be non-finite
-                const bool on = it < cnt;
-                const R wgt = on ? R(1) : R(0);
-                const R wq = pair ? wgt : R(0);
-                const V3<R> n = on ? selv(pair, nPw, nG) : v3(R(0), R(0), R(1));
-                contact_law(MR, on ? (pair ? dP : dG) : R(0), n, on ? selv(pair, vP - vQ, vP) : zero, F, eta);
-                F = wgt * F;
-                eta = wgt * eta;
-                // P's side in P's frame (force +F), Q's side in Q's frame (force -F)
-                const V3<R> nP = mulT(own.Rt, n), FP = mulT(own.Rt, F);
-                const V3<R> FQ = R(-1) * mulT(oth.Rt, F);
-                const R cP = wgt * MR.cc, cQ = wq * MR.cc, eQ = wq * eta;
-                body_contact(sel(own_trunk, eta, eQ), sel(own_trunk, cP, cQ), selv(own_trunk, cl, lq),
-                             selv(own_trunk, nP, nlq), selv(own_trunk, FP, wq * FQ), dt, Q, rb);
-                body_contact(sel(own_trunk, eQ, eta), sel(own_trunk, cQ, cP), selv(own_trunk, lq, cl),
-                             selv(own_trunk, nlq, nP), selv(own_trunk, wq * FQ, FP), dt, Qb, rbx);
-            }
-        }
     }
+
+    // ---- one corner per lane: trunk corner g (g < 8), free-box corner g - 8 (g >= 8).  Contacts
+    // with the trunk (a fallen robot, the box against the robot) are rare: without one, and
+    // with no foot on the box, the sums below take the short way (`plain`).
+    bool hitG = false, hitP = false, plain = true;
+    R dG = R(0), dP = R(0);
+    V3<R> nG = zero, nlq = zero, cl = zero, x = zero;
+    [[maybe_unused]] V3<R> lq = zero, rloc = zero;
+    [[maybe_unused]] const bool own_trunk = g < 8;
+    [[maybe_unused]] Pose<R> PT, PB;
+    PT.Rt = Rm; PT.p = b.p; PT.vw = b.vw; PT.w = b.w;
+    if constexpr (SCENE != 3) {
+        rloc = v3((g & 1 ? R(0.5) : R(-0.5)) * MR.tsx, (g & 2 ? R(0.5) : R(-0.5)) * MR.tsy,
+                  (g & 4 ? R(0.5) : R(-0.5)) * MR.tsz);
+        const V3<R> pw = b.p + mul(Rm, rloc);
+        hitG = terrain<SCENE>(MR, hf, pw, R(0), dG, nG) && g < 8;
+        if constexpr (SCENE == 2)
+            hitP = point_aabox(pw - v3(MR.sb_cx, MR.sb_cy, MR.sb_cz), v3(MR.sb_hx, MR.sb_hy, MR.sb_hz), dP, nlq) &&
+                   g < 8;
+        plain = __builtin_amdgcn_ballot_w64(hitG || hitP) == 0;
+    } else {
+        PB.Rt = bf.Rb; PB.p = bx.p; PB.vw = bx.vw; PB.w = bx.w;
+        const int ci = g & 7;
+        const V3<R> th = v3(R(0.5) * MR.tsx, R(0.5) * MR.tsy, R(0.5) * MR.tsz), bh = v3(MR.bx_hx, MR.bx_hy, MR.bx_hz);
+        const V3<R> hP = selv(own_trunk, th, bh);
+        cl = v3(ci & 1 ? hP.x : -hP.x, ci & 2 ? hP.y : -hP.y, ci & 4 ? hP.z : -hP.z);
+        x = selv(own_trunk, b.p + mul(Rm, cl), bx.p + mul(bf.Rb, cl));
+        hitG = terrain<SCENE>(MR, hf, x, R(0), dG, nG);
+        // the corner inside the other body, only while the bounding spheres can overlap
+        const V3<R> dc = b.p - bx.p;
+        if (__builtin_amdgcn_ballot_w64(dot(dc, dc) <= R(kNear) * (dot(th, th) + dot(bh, bh)))) {
+            lq = selv(own_trunk, mulT(bf.Rb, x - bx.p), mulT(Rm, x - b.p));
+            hitP = point_aabox(lq, selv(own_trunk, bh, th), dP, nlq);  // nlq: Q's face normal toward the corner
+        }
+        plain = __builtin_amdgcn_ballot_w64(hitP || (hitG && own_trunk)) == 0 && !foot_box;
+    }
+
+    // ---- eliminate the leg, A_ll^-1 [A_l0 | r_l]: lane `sub` solves columns sub and sub + 4 (the
+    // fifth and sixth velocity, the right side, and a zero column)
+    const Chol3<S> L3 = chol3(L.A00, L.A01, L.A11, L.A02, L.A12, L.A22);
+    S W0[3], W1[3];
+    const bool sub1 = (sub & 1) != 0, sub2 = (sub & 2) != 0;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        W0[j] = sel(sub2, sel(sub1, L.C[j][3], L.C[j][2]), sel(sub1, L.C[j][1], L.C[j][0]));
+        W1[j] = sel(sub2, sel(sub1, S(0), L.rl[j]), sel(sub1, L.C[j][5], L.C[j][4]));
+    }
+    solve3(L3, W0[0], W0[1], W0[2]);
+    solve3(L3, W1[0], W1[1], W1[2]);
 
     // ---- sum the trunk (and box) systems and the squared torques over the 16 lanes
-    constexpr int NV = n_summed<SCENE>();
-    {
-        S v[NV];
+    const bool keep = sub == 0;
+    if (plain) {
+        // the leg's values from its first lane and the eliminated parts from the lanes that have
+        // them: value by value the same sums as below, whose other terms are zeros
+        if (keep) {
+            S* o = red + leg * kLegPitch;
 #pragma unroll
-        for (int i = 0; i < 21; ++i) v[i] = Q[i];
+            for (int i = 0; i < 21; ++i) o[i] = Q[i];
 #pragma unroll
-        for (int i = 0; i < 6; ++i) v[21 + i] = rb[i];
-        v[27] = sel(keep, t2, S(0));
-        if constexpr (SCENE == 3) {
-#pragma unroll
-            for (int i = 0; i < 21; ++i) v[28 + i] = Qb[i];
-#pragma unroll
-            for (int i = 0; i < 6; ++i) v[49 + i] = rbx[i];
+            for (int i = 0; i < 6; ++i) o[21 + i] = rb[i];
+            o[27] = t2;
         }
+        {
+            S* o = red + kElimRow + leg * kElimPitch + sub;
 #pragma unroll
-        for (int e = 0; e < NV; ++e) red[e * kPitch + g] = v[e];
-    }
-    __syncthreads();
+            for (int i = 0; i < 6; ++i) {
+                if (i < 4) o[8 * i] = L.C[0][i] * W0[0] + L.C[1][i] * W0[1] + L.C[2][i] * W0[2];
+                o[8 * i + 4] = L.C[0][i] * W1[0] + L.C[1][i] * W1[1] + L.C[2][i] * W1[2];
+            }
+        }
+        if constexpr (SCENE == 3) {
+            // the box's corners against the ground (lanes 8-15)
+            S Qb[21], rbx[6];
 #pragma unroll
-    for (int m = 0; m < (NV + 15) / 16; ++m) {
-        const int e = g + 16 * m;
-        if (e < NV) sred[e] = sum16(red + e * kPitch);
-    }
-    __syncthreads();
+            for (int i = 0; i < 21; ++i) Qb[i] = S(0);
 #pragma unroll
-    for (int i = 0; i < 21; ++i) Q[i] = sred[i];
+            for (int i = 0; i < 6; ++i) rbx[i] = S(0);
+            if (__builtin_amdgcn_ballot_w64(hitG)) {
+                const R wgt = hitG ? R(1) : R(0);
+                const V3<R> n = hitG ? nG : v3(R(0), R(0), R(1));
+                contact_law(MR, hitG ? dG : R(0), n, hitG ? pose_point_vel(PB, x) : zero, F, eta);
+                F = wgt * F;
+                eta = wgt * eta;
+                body_contact(eta, wgt * MR.cc, cl, mulT(bf.Rb, n), mulT(bf.Rb, F), dt, Qb, rbx);
+            }
+            if (g >= 8) {
 #pragma unroll
-    for (int i = 0; i < 6; ++i) rb[i] = sred[21 + i];
-    tau2 = R(sred[27]);
-    if constexpr (SCENE == 3) {
+                for (int e = 0; e < 21; ++e) red[kBoxRow + e * kPitch + g] = Qb[e];
 #pragma unroll
-        for (int i = 0; i < 21; ++i) Qb[i] = sred[28 + i];
+                for (int e = 0; e < 6; ++e) red[kBoxRow + (21 + e) * kPitch + g] = rbx[e];
+            }
+        }
+        __syncthreads();
+        {
+            // every lane reads (lanes past the last value a valid one, unused), so that the
+            // reads wait together
+            const S* v = red + g;
+            const S* xe = red + kElimRow;
+            S s0[4], s1[4];
 #pragma unroll
-        for (int i = 0; i < 6; ++i) rbx[i] = sred[49 + i];
-    }
-
-    // ---- the trunk's own terms: inertia, total mass, gyroscopic and gravity bias
-    Q[s6(0, 0)] += MS.I0x; Q[s6(1, 1)] += MS.I0y; Q[s6(2, 2)] += MS.I0z;
-    Q[s6(3, 3)] += MS.mtot; Q[s6(4, 4)] += MS.mtot; Q[s6(5, 5)] += MS.mtot;
-    {
-        const V3<S> Iw = v3(MS.I0x * ws.x, MS.I0y * ws.y, MS.I0z * ws.z);
-        const V3<S> gy = cross(ws, Iw);
-        rb[0] -= dt * gy.x; rb[1] -= dt * gy.y; rb[2] -= dt * gy.z;
-        rb[3] += dt * MS.m0 * gbs.x; rb[4] += dt * MS.m0 * gbs.y; rb[5] += dt * MS.m0 * gbs.z;
-    }
-    if constexpr (SCENE != 3) {
-        chol6_solve(Q, rb);  // rb <- trunk increment [d omega; d v_b]
+            for (int l = 0; l < 4; ++l) {
+                s0[l] = v[l * kLegPitch] - xe[l * kElimPitch + eo0];
+                s1[l] = v[l * kLegPitch + 16] - xe[l * kElimPitch + eo1];
+            }
+            const S a0 = (s0[0] + s0[1]) + (s0[2] + s0[3]), a1 = (s1[0] + s1[1]) + (s1[2] + s1[3]);
+            [[maybe_unused]] S b0, b1;
+            if constexpr (SCENE == 3) {
+                b0 = sum8(red + kBoxRow + g * kPitch + 8);
+                b1 = sum8(red + kBoxRow + min(g + 16, 26) * kPitch + 8);
+                sred[28 + g] = b0;
+            }
+            sred[g] = a0;
+            if (g < 12) {
+                sred[g + 16] = a1;
+                if constexpr (SCENE == 3) sred[28 + 16 + min(g, 10)] = b1;
+            }
+        }
+        __syncthreads();
     } else {
-        // the box's own terms, then one 6x6 solve per lane: trunk on even lanes, box on
-        // odd lanes; neighbours swap their results
-        Qb[s6(0, 0)] += MS.bx_Ix; Qb[s6(1, 1)] += MS.bx_Iy; Qb[s6(2, 2)] += MS.bx_Iz;
-        Qb[s6(3, 3)] += MS.bx_m; Qb[s6(4, 4)] += MS.bx_m; Qb[s6(5, 5)] += MS.bx_m;
-        const V3<S> wbx = cv<S>(bx.w);
-        const V3<S> gyb = cross(wbx, v3(MS.bx_Ix * wbx.x, MS.bx_Iy * wbx.y, MS.bx_Iz * wbx.z));
-        const V3<S> gl = cv<S>((-MR.g) * v3(bf.Rb.m[6], bf.Rb.m[7], bf.Rb.m[8]));
-        rbx[0] -= dt * gyb.x; rbx[1] -= dt * gyb.y; rbx[2] -= dt * gyb.z;
-        rbx[3] += dt * MS.bx_m * gl.x; rbx[4] += dt * MS.bx_m * gl.y; rbx[5] += dt * MS.bx_m * gl.z;
-        const bool odd = (g & 1) != 0;
-        S Qs[21], rs[6];
-#pragma unroll
-        for (int i = 0; i < 21; ++i) Qs[i] = sel(odd, Qb[i], Q[i]);
-#pragma unroll
-        for (int i = 0; i < 6; ++i) rs[i] = sel(odd, rbx[i], rb[i]);
-        chol6_solve(Qs, rs);
+        // all columns in every lane, each lane's corner terms added to its own (the leg's values
+        // in its first lane), then the 16 lanes' values in a fixed order
+        S W[3][6];
 #pragma unroll
         for (int i = 0; i < 6; ++i) {
-            const S other = dpp<0xB1>(rs[i]);  // the neighbour's result (lanes 0<->1, 2<->3)
-            rb[i] = sel(odd, other, rs[i]);
-            rbx[i] = sel(odd, rs[i], other);
+            S x0 = L.C[0][i], x1 = L.C[1][i], x2 = L.C[2][i];
+            solve3(L3, x0, x1, x2);
+            W[0][i] = x0; W[1][i] = x1; W[2][i] = x2;
+        }
+        S y0 = L.rl[0], y1 = L.rl[1], y2 = L.rl[2];
+        solve3(L3, y0, y1, y2);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+#pragma unroll
+            for (int j = i; j < 6; ++j)
+                Q[s6(i, j)] -= L.C[0][i] * W[0][j] + L.C[1][i] * W[1][j] + L.C[2][i] * W[2][j];
+            rb[i] -= L.C[0][i] * y0 + L.C[1][i] * y1 + L.C[2][i] * y2;
+        }
+#pragma unroll
+        for (int i = 0; i < 21; ++i) Q[i] = sel(keep, Q[i], S(0));
+#pragma unroll
+        for (int i = 0; i < 6; ++i) rb[i] = sel(keep, rb[i], S(0));
+        [[maybe_unused]] S Qb[21], rbx[6];
+        if constexpr (SCENE != 3) {
+            if (hitG) {
+                const V3<R> n = mulT(Rm, nG);
+                contact_law(MR, dG, n, vb + cross(w, rloc), F, eta);
+                body_contact(eta, MR.cc, rloc, n, F, dt, Q, rb);
+            }
+            if constexpr (SCENE == 2) {
+                if (hitP) {
+                    const V3<R> n = mulT(Rm, nlq);
+                    contact_law(MR, dP, n, vb + cross(w, rloc), F, eta);
+                    body_contact(eta, MR.cc, rloc, n, F, dt, Q, rb);
+                }
+            }
+        } else {
+            // A corner of body P (the trunk on lanes 0-7, the box on lanes 8-15) against the
+            // other body Q (a point inside Q's box, normal out of Q's nearest face) and against
+            // the terrain.  The same code serves both roles: each contact adds its terms to the
+            // trunk's and the box's 6x6 systems in their own frames, with zero weight where a
+            // body is not part of the contact.
+#pragma unroll
+            for (int i = 0; i < 21; ++i) Qb[i] = S(0);
+#pragma unroll
+            for (int i = 0; i < 6; ++i) rbx[i] = S(0);
+            body_contact(sel(keep, fb_eta, R(0)), sel(keep, fb_c, R(0)), fb_r, fb_n, selv(keep, fb_F, zero), dt, Qb, rbx);
+            const Pose<R> own = sel_pose(own_trunk, PT, PB), oth = sel_pose(own_trunk, PB, PT);
+            const int cnt = int(hitP) + int(hitG);
+            if (__builtin_amdgcn_ballot_w64(cnt > 0)) {
+                const V3<R> vP = pose_point_vel(own, x), vQ = pose_point_vel(oth, x);
+                const V3<R> nPw = mul(oth.Rt, nlq);
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {
+                    if (!__builtin_amdgcn_ballot_w64(it < cnt)) break;
+                    const bool pair = (it == 0) && hitP;  // pass 0: the pair if touching, else the terrain
+                    // a lane without a contact in this pass takes a neutral one (zero depth and
+                    // velocity, zero weight), so nothing it adds can be non-finite
+                    const bool on = it < cnt;
+                    const R wgt = on ? R(1) : R(0);
+                    const R wq = pair ? wgt : R(0);
+                    const V3<R> n = on ? selv(pair, nPw, nG) : v3(R(0), R(0), R(1));
+                    contact_law(MR, on ? (pair ? dP : dG) : R(0), n, on ? selv(pair, vP - vQ, vP) : zero, F, eta);
+                    F = wgt * F;
+                    eta = wgt * eta;
+                    // P's side in P's frame (force +F), Q's side in Q's frame (force -F)
+                    const V3<R> nP = mulT(own.Rt, n), FP = mulT(own.Rt, F);
+                    const V3<R> FQ = R(-1) * mulT(oth.Rt, F);
+                    const R cP = wgt * MR.cc, cQ = wq * MR.cc, eQ = wq * eta;
+                    body_contact(sel(own_trunk, eta, eQ), sel(own_trunk, cP, cQ), selv(own_trunk, cl, lq),
+                                 selv(own_trunk, nP, nlq), selv(own_trunk, FP, wq * FQ), dt, Q, rb);
+                    body_contact(sel(own_trunk, eQ, eta), sel(own_trunk, cQ, cP), selv(own_trunk, lq, cl),
+                                 selv(own_trunk, nlq, nP), selv(own_trunk, wq * FQ, FP), dt, Qb, rbx);
+                }
+            }
+        }
+        constexpr int NV = n_summed<SCENE>();
+        {
+            S v[NV];
+#pragma unroll
+            for (int i = 0; i < 21; ++i) v[i] = Q[i];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) v[21 + i] = rb[i];
+            v[27] = sel(keep, t2, S(0));
+            if constexpr (SCENE == 3) {
+#pragma unroll
+                for (int i = 0; i < 21; ++i) v[28 + i] = Qb[i];
+#pragma unroll
+                for (int i = 0; i < 6; ++i) v[49 + i] = rbx[i];
+            }
+#pragma unroll
+            for (int e = 0; e < NV; ++e) red[e * kPitch + g] = v[e];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < (NV + 15) / 16; ++m) {
+            const int e = g + 16 * m;
+            if (e < NV) sred[e] = sum16(red + e * kPitch);
+        }
+        __syncthreads();
+    }
+
+    // ---- the body's system: sums, own inertia, mass, gyroscopic and gravity bias; one 6x6
+    // solve per lane: the trunk's, in the pushing scene on odd lanes the box's
+    tau2 = R(sred[27]);
+    const bool odd = SCENE == 3 && (g & 1) != 0;
+    {
+        const S* s = sred + (odd ? 28 : 0);
+#pragma unroll
+        for (int i = 0; i < 21; ++i) Q[i] = s[i];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) rb[i] = s[21 + i];
+        V3<S> I = v3(MS.I0x, MS.I0y, MS.I0z), wo = ws, go = gbs;
+        S mo = MS.m0, mt = MS.mtot;
+        if constexpr (SCENE == 3) {
+            I = selv(odd, v3(MS.bx_Ix, MS.bx_Iy, MS.bx_Iz), I);
+            wo = selv(odd, cv<S>(bx.w), ws);
+            go = selv(odd, cv<S>((-MR.g) * v3(bf.Rb.m[6], bf.Rb.m[7], bf.Rb.m[8])), gbs);
+            mo = sel(odd, MS.bx_m, mo);
+            mt = sel(odd, MS.bx_m, mt);
+        }
+        Q[s6(0, 0)] += I.x; Q[s6(1, 1)] += I.y; Q[s6(2, 2)] += I.z;
+        Q[s6(3, 3)] += mt; Q[s6(4, 4)] += mt; Q[s6(5, 5)] += mt;
+        const V3<S> gy = cross(wo, v3(I.x * wo.x, I.y * wo.y, I.z * wo.z));
+        rb[0] -= dt * gy.x; rb[1] -= dt * gy.y; rb[2] -= dt * gy.z;
+        rb[3] += dt * mo * go.x; rb[4] += dt * mo * go.y; rb[5] += dt * mo * go.z;
+    }
+    chol6_solve(Q, rb);  // rb <- the body's increment [d omega; d v_b]
+    [[maybe_unused]] S rbx[6];
+    if constexpr (SCENE == 3) {
+        // lanes 0 and 1 of every quad hold the trunk's and the box's increments
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            rbx[i] = dpp<0x55>(rb[i]);
+            rb[i] = dpp<0x00>(rb[i]);
         }
     }
 
     // ---- back-substitute the leg and integrate (semi-implicit Euler): velocities add the
-    // increments in S, positions take dt times the new velocities in R
-    S dq[3] = {y0, y1, y2};
+    // increments in S, positions take dt times the new velocities in R.  The columns come from
+    // their lanes: in FP32 one after the other (the order of the terms is the rounding), in
+    // FP64 each lane adds its two and the quad adds the lanes.
+    S dq[3];
+    if constexpr (sizeof(S) == 4) {
 #pragma unroll
-    for (int j = 0; j < 3; ++j)
+        for (int j = 0; j < 3; ++j) {
+            dq[j] = dpp<0xAA>(W1[j]);
+            dq[j] -= dpp<0x00>(W0[j]) * rb[0];
+            dq[j] -= dpp<0x55>(W0[j]) * rb[1];
+            dq[j] -= dpp<0xAA>(W0[j]) * rb[2];
+            dq[j] -= dpp<0xFF>(W0[j]) * rb[3];
+            dq[j] -= dpp<0x00>(W1[j]) * rb[4];
+            dq[j] -= dpp<0x55>(W1[j]) * rb[5];
+        }
+    } else {
+        const S x0 = sel(sub2, sel(sub1, rb[3], rb[2]), sel(sub1, rb[1], rb[0]));
+        const S x1 = sel(sub2, sel(sub1, S(0), S(-1)), sel(sub1, rb[5], rb[4]));
 #pragma unroll
-        for (int i = 0; i < 6; ++i) dq[j] -= W[j][i] * rb[i];
+        for (int j = 0; j < 3; ++j) dq[j] = -quad_sum(W0[j] * x0 + W1[j] * x1);
+    }
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
         lg.qd[j] = R(S(lg.qd[j]) + dq[j]);
@@ -523,7 +675,8 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
 #pragma unroll
     for (int i = 0; i < 9; ++i) Rs.m[i] = S(Rm.m[i]);
     b.w = cv<R>(ws + v3(rb[0], rb[1], rb[2]));
-    b.vw = cv<R>(cv<S>(b.vw) + mul(Rs, v3(rb[3], rb[4], rb[5])));
+    if constexpr (SCENE == 3) b.vw = cv<R>(cv<S>(b.vw) + mul_ordered(Rs, v3(rb[3], rb[4], rb[5])));
+    else b.vw = cv<R>(cv<S>(b.vw) + mul(Rs, v3(rb[3], rb[4], rb[5])));
     b.p = b.p + dtr * b.vw;
     if constexpr (SCENE != 3) {
         quat_step(b.qw, b.qx, b.qy, b.qz, b.w, dtr);
@@ -532,18 +685,15 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
 #pragma unroll
         for (int i = 0; i < 9; ++i) Rbs.m[i] = S(bf.Rb.m[i]);
         bx.w = cv<R>(cv<S>(bx.w) + v3(rbx[0], rbx[1], rbx[2]));
-        bx.vw = cv<R>(cv<S>(bx.vw) + mul(Rbs, v3(rbx[3], rbx[4], rbx[5])));
+        bx.vw = cv<R>(cv<S>(bx.vw) + mul_ordered(Rbs, v3(rbx[3], rbx[4], rbx[5])));
         bx.p = bx.p + dtr * bx.vw;
         // one quaternion step per lane: the trunk's on even lanes, the box's on odd lanes
-        const bool odd = (g & 1) != 0;
         R q[4] = {sel(odd, bx.qw, b.qw), sel(odd, bx.qx, b.qx), sel(odd, bx.qy, b.qy), sel(odd, bx.qz, b.qz)};
-        quat_step(q[0], q[1], q[2], q[3], selv(odd, bx.w, b.w), dtr);
-        R o[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = dpp<0xB1>(q[i]);
-        b.qw = sel(odd, o[0], q[0]); b.qx = sel(odd, o[1], q[1]); b.qy = sel(odd, o[2], q[2]); b.qz = sel(odd, o[3], q[3]);
-        bx.qw = sel(odd, q[0], o[0]); bx.qx = sel(odd, q[1], o[1]); bx.qy = sel(odd, q[2], o[2]);
-        bx.qz = sel(odd, q[3], o[3]);
+        const V3<R> ph = (R(0.5) * dtr) * selv(odd, bx.w, b.w);
+        // in a stated order (see mul_ordered)
+        quat_turn(q[0], q[1], q[2], q[3], ph, m_sqrt(fma(ph.z, ph.z, fma(ph.y, ph.y, ph.x * ph.x))));
+        b.qw = dpp<0x00>(q[0]); b.qx = dpp<0x00>(q[1]); b.qy = dpp<0x00>(q[2]); b.qz = dpp<0x00>(q[3]);
+        bx.qw = dpp<0x55>(q[0]); bx.qx = dpp<0x55>(q[1]); bx.qy = dpp<0x55>(q[2]); bx.qz = dpp<0x55>(q[3]);
     }
 }
 
@@ -564,23 +714,7 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
 //   * in the pushing scene each lane reads the sums of the one body whose 6x6 system it solves.
 // Per call, step16 / here (MI355X): heightfield walk K = 1024, H = 50: 318 / 197 us; box push
 // K = 4096, H = 60: 560 / 343 us; flat walk K = 64, H = 25, whole control step: 135 / 96 us.
-// LDS per sample in doubles: [0, 560) a region used in turn for the trunk corners' rows
-// (27 x kPitch), then the legs' values (4 x kLegPitch) and eliminated columns (4 x
-// kElimPitch); in the pushing scene the box's rows follow at kBoxRow (27 x kPitch).
 // ------------------------------------------------------------------------------
-constexpr int kLegPitch = 28, kElimPitch = 50, kElimRow = 4 * kLegPitch, kBoxRow = 28 * kPitch;
-
-// where lane g's summed values g and g + 16 of the trunk's 28 (21 + 6 + torque^2) stand in a
-// leg's eliminated columns (6 rows x 8 columns; column 6 is the right side, 7 zeros)
-__device__ __forceinline__ int elim_slot(int e)
-{
-    if (e >= 27) return 7;
-    if (e >= 21) return (e - 21) * 8 + 6;
-    int i = 0, first = 0;
-    while (e - first >= 6 - i) first += 6 - i++;
-    return i * 8 + i + (e - first);
-}
-
 // the model in LDS through an offset (always zero) that the compiler takes to depend on the
 // step's number, so that a step reads its constants where it uses them instead of keeping
 // about 35 doubles in registers over the whole step loop
@@ -659,7 +793,7 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
             double dP = 0.0;
             V3<double> lq = zero, nlq = zero;
             const V3<double> dc = b.p - bx.p;
-            if (__builtin_amdgcn_ballot_w64(dot(dc, dc) <= 2.0 * (dot(th, th) + dot(bh, bh)))) {
+            if (__builtin_amdgcn_ballot_w64(dot(dc, dc) <= kNear * (dot(th, th) + dot(bh, bh)))) {
                 lq = selv(own_trunk, mulT(Rb, x - bx.p), mulT(Rm, x - b.p));
                 hitP = point_aabox(lq, selv(own_trunk, bh, th), dP, nlq);
             }
@@ -739,10 +873,10 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
         if constexpr (SCENE == 2)
             hitB = sphere_aabox64(pfw - v3(M.sb_cx, M.sb_cy, M.sb_cz), M.foot_r, v3(M.sb_hx, M.sb_hy, M.sb_hz), dB, nB);
         if constexpr (SCENE == 3) {
-            // outside the sphere around the box there is no contact ((r + |h|)^2 <= 2 (r^2 + |h|^2))
+            // outside the sphere around the box there is no contact
             const V3<double> d = pfw - bx.p;
             const V3<double> bh = v3(M.bx_hx, M.bx_hy, M.bx_hz);
-            if (__builtin_amdgcn_ballot_w64(dot(d, d) <= 2.0 * (M.foot_r * M.foot_r + dot(bh, bh)))) {
+            if (__builtin_amdgcn_ballot_w64(dot(d, d) <= kNear * (M.foot_r * M.foot_r + dot(bh, bh)))) {
                 V3<double> nl = up;
                 hitB = sphere_aabox64(mulT(Rb, d), M.foot_r, bh, dB, nl);
                 nB = mul(Rb, nl);  // box -> foot (world)
@@ -972,8 +1106,14 @@ __global__ __launch_bounds__(64) void rollout16_kernel(ModelT<R> Mr, ModelT<S> M
         sMs = Ms;
     }
     if constexpr (SCENE == 1) {
-        const int cells = Mr.hf_nx * Mr.hf_ny;
-        for (int i = threadIdx.x; i < cells; i += blockDim.x) sHF[i] = ghf[i];
+        // 16 bytes a lane and several loads in flight (both sides are 16-byte aligned): one
+        // value at a time, the 64 x 64 field took 64 round trips
+        const int cells = Mr.hf_nx * Mr.hf_ny, quads = cells >> 2;
+        const r16::Quad* __restrict__ src = reinterpret_cast<const r16::Quad*>(ghf);
+        r16::Quad* dst = reinterpret_cast<r16::Quad*>(sHF);
+#pragma unroll 8
+        for (int i = threadIdx.x; i < quads; i += 64) dst[i] = src[i];
+        for (int i = 4 * quads + threadIdx.x; i < cells; i += 64) sHF[i] = ghf[i];
     }
     __syncthreads();
     const ModelT<R>& MR = sMr;
@@ -1066,7 +1206,8 @@ __global__ __launch_bounds__(64) void rollout16_kernel(ModelT<R> Mr, ModelT<S> M
             r16::step16_64<SCENE>(k, r16::fresh_model(&sMs, k), sHF, dt, kp, kd, g, eo0, eo1, b, lg, bx, uj, my_red,
                                   my_sum, tau2);
         else
-            r16::step16<SCENE, R, S>(MR, MS, sHF, dt, kp, kd, g, b, lg, bx, uj, my_red, my_sum, tau2);
+            r16::step16<SCENE, R, S>(MR, MS, sHF, dt, kp, kd, g, eo0, eo1, b, lg, bx, uj, my_red, my_sum,
+                                        tau2);
         if constexpr (!DIRECT) {
             const double* nrow = gB + min(k + 1, P.H - 1) * nk;
 #pragma unroll
