@@ -33,6 +33,16 @@ __device__ __forceinline__ float dsilu(float z)
     return s * (1.f + z * (1.f - s));
 }
 
+// The BF16 copies W^T are stored in the order in which the matrix instruction takes them:
+// blocks of 16 rows (n) by 32 columns (k), k-blocks of a row panel consecutive, and in a block
+// the 8 k-values of row l mod 16 and columns 8 (l / 16) .. +7 at place l.  A wave's fragment is
+// 1 KiB in a row (read from rows of W^T it touched 16 lines for half a line each).
+// frag_offset: element offset of row n, column k (a multiple of 8) of a matrix of K columns.
+__device__ __forceinline__ size_t frag_offset(int n, int k, int K)
+{
+    return ((size_t)(n >> 4) * (K >> 5) + (k >> 5)) * 512 + ((n & 15) + 16 * ((k >> 3) & 3)) * 8;
+}
+
 // ---------------------------------------------------------------------------------
 // GEMM: 256 threads = 4 waves in a 2 x 2 grid, each wave a (BM/2) x (BN/2) block of
 // 16 x 16 accumulator tiles fed by v_mfma_f32_16x16x32_bf16.  Operand fragments: lane l
@@ -61,7 +71,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g)
     const int mt = blockIdx.x, m0 = mt * BM, n0 = blockIdx.y * BN;
     const size_t kb = (size_t)blockIdx.z * g.K;
     const __bf16* A = g.A + (size_t)m0 * g.lda + kb;
-    const __bf16* B = g.B + (size_t)n0 * g.ldb + kb;
+    // the forward products' B is W^T in fragment order (ldb columns), the others' in rows
+    constexpr bool kFrag = EPI == EPI_HIDDEN || EPI == EPI_OUT;
+    const __bf16* B = kFrag ? g.B : g.B + (size_t)n0 * g.ldb + kb;
 
     // register-staged prefetch kPF k-tiles deep: stage s of the ring holds k-tile
     // (k / BK) with (k / BK) mod kPF = s; each k-tile is stored to LDS, consumed, and its
@@ -76,8 +88,11 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g)
         }                                                                                                  \
         _Pragma("unroll") for (int c = 0; c < CB; ++c)                                                     \
         {                                                                                                  \
-            const int idx = tid + 256 * c, row = idx >> 3, col = (idx & 7) * 8;                            \
-            rb[s][c] = *reinterpret_cast<const u32x4*>(B + (size_t)row * g.ldb + (k0) + col);              \
+            const int idx = tid + 256 * c;                                                                 \
+            const int row = kFrag ? 16 * (idx >> 7) + (idx & 15) : idx >> 3;                               \
+            const int col = kFrag ? 32 * ((idx >> 6) & 1) + 8 * ((idx >> 4) & 3) : (idx & 7) * 8;          \
+            rb[s][c] = *reinterpret_cast<const u32x4*>(                                                    \
+                B + (kFrag ? frag_offset(n0 + row, (k0) + col, g.ldb) : (size_t)row * g.ldb + (k0) + col)); \
         }                                                                                                  \
     } while (0)
 
@@ -103,7 +118,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g)
             }
 #pragma unroll
             for (int c = 0; c < CB; ++c) {
-                const int idx = tid + 256 * c, row = idx >> 3, col = (idx & 7) * 8;
+                const int idx = tid + 256 * c;
+                const int row = kFrag ? 16 * (idx >> 7) + (idx & 15) : idx >> 3;
+                const int col = kFrag ? 32 * ((idx >> 6) & 1) + 8 * ((idx >> 4) & 3) : (idx & 7) * 8;
                 *reinterpret_cast<u32x4*>(sB + row * LDK + col) = rb[s][c];
             }
             __syncthreads();
@@ -279,8 +296,183 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a)
     a.X0t[(size_t)c * a.Bp + r] = b;
 }
 
+// ---------------------------------------------------------------------------------
+// The forward pass in one launch: a workgroup takes kNetRows rows through every layer, its
+// activations in LDS, each of its 8 waves 64 of a hidden layer's 512 columns.  What bounds it
+// is the stream of weights from L2, 1.75 MB for every workgroup whatever its rows: the waves
+// read their fragments straight from memory (no other wave of the workgroup needs them), four
+// 64-wide k-tiles ahead of the products (two: 22.6 us for 256 rows against 20.8).  16 rows, the
+// matrix instruction's height, give the most workgroups: one row block's time is the pass's
+// time up to 4096 rows (one a compute unit), where a launch for every layer paid its start and
+// its drain six times.  The products are those of gemm_kernel in the same order, so the results
+// are the same bits.
+// Launches per layer / here, us a pass: 1 row 29.3 / 19.9, 256 rows 29.4 / 21.3, 2000 rows
+// 31.2 / 21.5, 4096 rows 40.0 / 24.1; with three policies in turn (their weights together
+// exceed an XCD's L2) 29.3 / 20.3, 30.1 / 22.0, 33.0 / 22.8, 41.4 / 32.6.
+// ---------------------------------------------------------------------------------
+constexpr int kNetRows = 16, kNetThreads = 512, kNetLd = kHidden + 8;
+
+__device__ __forceinline__ bf16x8 ld8(const __bf16* p) { return *reinterpret_cast<const bf16x8*>(p); }
+
+// the fragments of a wave's column tiles in flight: kNetDepth k-tiles of 64
+constexpr int kNetDepth = 4;
+template <int TN>
+struct NetFrags {
+    bf16x8 w[kNetDepth][TN][2];
+};
+
+// k-tile t of the TN column tiles at b (W^T in fragment order, K columns, tiles `step` apart)
+template <int K, int TN>
+__device__ __forceinline__ void net_load(const __bf16* b, int step, int t, NetFrags<TN>& f)
+{
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) f.w[t % kNetDepth][j][h] = ld8(b + (size_t)j * step * K * 16 + (2 * t + h) * 512);
+}
+template <int K, int TN>
+__device__ __forceinline__ void net_start(const __bf16* b, int step, NetFrags<TN>& f)
+{
+#pragma unroll
+    for (int t = 0; t < kNetDepth; ++t)
+        if (t < K / 64) net_load<K, TN>(b, step, t, f);
+}
+
+// acc[j] = A (16 rows of LDS at sA, pitch kNetLd) x the column tiles, whose first fragments
+// net_start has put in flight
+template <int K, int TN>
+__device__ __forceinline__ void net_product(const __bf16* sA, const __bf16* b, int step, NetFrags<TN>& f, f32x4 acc[TN])
+{
+    constexpr int NT = K / 64;
+    const int lane = threadIdx.x & 63;
+    const __bf16* a = sA + (lane & 15) * kNetLd + (lane >> 4) * 8;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const bf16x8 av = ld8(a + 64 * t + 32 * h);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, f.w[t % kNetDepth][j][h], acc[j], 0, 0, 0);
+        }
+        if (t + kNetDepth < NT) net_load<K, TN>(b, step, t + kNetDepth, f);
+    }
+}
+
+// z = acc + b, silu(z) rounded to bf16 into the wave's columns of sH
+__device__ __forceinline__ void net_activate(const f32x4 acc[4], const float bv[4], __bf16* sH, int n0)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int n = n0 + 16 * j + (lane & 15);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sH[((lane >> 4) * 4 + r) * kNetLd + n] = (__bf16)silu(acc[j][r] + bv[j]);
+    }
+}
+
+// the output's TN column tiles j0, j0 + 8, whose first fragments are in flight
+template <int TN>
+__device__ __forceinline__ void net_output(const PrepArgs& p, const __bf16* sA, const __bf16* b, int j0, int r0,
+                                           NetFrags<TN>& f)
+{
+    const int lane = threadIdx.x & 63;
+    f32x4 acc[TN];
+    net_product<kHidden, TN>(sA, b, 8, f, acc);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int n = 16 * (j0 + 8 * j) + (lane & 15);
+        const float bv = p.net.bias[kLayers - 1][n];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = r0 + (lane >> 4) * 4 + r;
+            if (row < p.B) p.net.out[(size_t)row * kOut + n] = acc[j][r] + bv;
+        }
+    }
+}
+
+// Workgroups past the row blocks bring the weights into their XCD's L2 (workgroups go round the
+// XCDs), part `part` of kNetWarm each: a few row blocks alone fetch them with a compute unit's
+// misses in flight for each XCD, and a pass whose weights are not in L2 (several policies in
+// turn) waits for that: 256 rows, three policies in turn, 30.8 us without them, 22.0 with.  From
+// kNetWarmBlocks row blocks on (16 an XCD) those have as much in flight themselves.  The values
+// are not used.
+constexpr int kNetWarm = 8, kXcds = 8, kNetWarmBlocks = 128;
+__device__ __forceinline__ void net_warm(const PrepArgs& p, int part)
+{
+#pragma unroll 1
+    for (int l = 0; l < kLayers; ++l) {
+        const int bytes = (l ? kHidden : kInPad) * (l < kLayers - 1 ? kHidden : kOut) * 2 / kNetWarm;
+        const char* src = reinterpret_cast<const char*>(p.net.Wt[l]) + (size_t)part * bytes;
+#pragma unroll 8
+        for (int i = threadIdx.x * 16; i < bytes; i += kNetThreads * 16) {
+            const u32x4 v = *reinterpret_cast<const u32x4*>(src + i);
+            asm volatile("" ::"v"(v));
+        }
+    }
+}
+
+__global__ __launch_bounds__(kNetThreads, 2) void net_kernel(PrepArgs p)
+{
+    __shared__ __align__(16) __bf16 sH[2][kNetRows * kNetLd];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r0 = blockIdx.x * kNetRows;
+    if (r0 >= p.B) {
+        net_warm(p, (blockIdx.x / kXcds) % kNetWarm);
+        return;
+    }
+    const int n0 = wave * 64;
+    const size_t frag = lane * 8;
+    NetFrags<4> f;
+    f32x4 acc[4];
+    float bv[4];
+    // each layer's first fragments and biases are requested before the wait for its input
+    net_start<kInPad, 4>(p.net.Wt[0] + (size_t)n0 * kInPad + frag, 1, f);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bv[j] = p.net.bias[0][n0 + 16 * j + (lane & 15)];
+    for (int e = tid; e < kNetRows * kInPad; e += kNetThreads) {
+        const int rr = e / kInPad, c = e - rr * kInPad, r = r0 + rr;
+        float v = 0.f;
+        if (r < p.B && c < kIn) {
+            const int row = p.idx ? p.idx[r] : r;
+            v = (p.X[(size_t)row * kIn + c] - p.mean[c]) / p.std[c];
+        }
+        sH[0][rr * kNetLd + c] = (__bf16)v;
+    }
+    __syncthreads();
+    net_product<kInPad, 4>(sH[0], p.net.Wt[0] + (size_t)n0 * kInPad + frag, 1, f, acc);
+#pragma unroll 1
+    for (int l = 1; l < kLayers - 1; ++l) {
+        const __bf16* b = p.net.Wt[l] + (size_t)n0 * kHidden + frag;
+        net_start<kHidden, 4>(b, 1, f);
+        net_activate(acc, bv, sH[l & 1], n0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bv[j] = p.net.bias[l][n0 + 16 * j + (lane & 15)];
+        __syncthreads();
+        net_product<kHidden, 4>(sH[l & 1], b, 1, f, acc);
+    }
+    // the output's 9 column tiles: one a wave, the ninth by the first wave
+    const __bf16* sO = sH[(kLayers - 1) & 1];
+    const __bf16* b = p.net.Wt[kLayers - 1] + (size_t)wave * (kHidden * 16) + frag;
+    NetFrags<2> f2;
+    NetFrags<1> f1;
+    if (wave == 0) net_start<kHidden, 2>(b, 8, f2);
+    else net_start<kHidden, 1>(b, 8, f1);
+    net_activate(acc, bv, sH[(kLayers - 1) & 1], n0);
+    __syncthreads();
+    if (wave == 0) net_output<2>(p, sO, b, 0, r0, f2);
+    else net_output<1>(p, sO, b, wave, r0, f1);
+}
+
 hipError_t launch_prep(const PrepArgs& a, hipStream_t st)
 {
+    if (a.net.out) {
+        const int rows = (a.B + kNetRows - 1) / kNetRows;
+        const int warm = rows < kNetWarmBlocks ? kXcds * kNetWarm : 0;
+        hipLaunchKernelGGL(net_kernel, dim3(rows + warm), dim3(kNetThreads), 0, st, a);
+        return hipGetLastError();
+    }
     const int n = a.Bp * kInPad;
     hipLaunchKernelGGL(prep_kernel, dim3((n + 255) / 256), dim3(256), 0, st, a);
     return hipGetLastError();
@@ -466,7 +658,7 @@ __global__ __launch_bounds__(256) void param_pass_kernel(ReduceArgs r, AdamArgs 
         if constexpr (MODE != PASS_REDUCE) {
             __syncthreads();
             const int row = t >> 2, c = t & 3;  // 64 rows of W^T, 4 pieces of 8 each
-            *reinterpret_cast<bf16x8*>(a.Wt[l] + (size_t)(o0 + row) * fip + i0 + 8 * c) =
+            *reinterpret_cast<bf16x8*>(a.Wt[l] + frag_offset(o0 + row, i0 + 8 * c, fip)) =
                 *reinterpret_cast<const bf16x8*>(&sT[row][8 * c]);
         }
         return;

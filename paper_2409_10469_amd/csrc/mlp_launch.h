@@ -58,7 +58,16 @@ inline int gemm_tile_m(int M, int N, int splits)
 }
 hipError_t launch_gemm(int epi, const GemmArgs& g, int splits, hipStream_t st);
 
-// raw features (rows idx[r] of X, stride 40) -> standardised bf16 X0 [Bp x 64] and X0^T [64 x Bp]
+// The network of a fused forward pass: W^T [fop x fip] and bias of every layer, the output
+// rows (B x 144).
+struct NetArgs {
+    const __bf16* Wt[kLayers];
+    const float* bias[kLayers];
+    float* out;  // null: no forward pass
+};
+
+// raw features (rows idx[r] of X, stride 40) -> standardised bf16 X0 [Bp x 64] and X0^T
+// [64 x Bp]; with net.out set the whole forward pass instead (X0 and X0^T are not written)
 struct PrepArgs {
     const float* X;
     const int* idx;
@@ -67,6 +76,7 @@ struct PrepArgs {
     const float* std;
     __bf16* X0;
     __bf16* X0t;
+    NetArgs net;
 };
 hipError_t launch_prep(const PrepArgs& a, hipStream_t st);
 
@@ -105,8 +115,8 @@ struct ReduceArgs {
 };
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t st);
 
-// Adam (update = 1) or shadow refresh only (update = 0); bf16 shadows W^T [fop x fip] and
-// W [fip x fop] (layers >= 1) rewritten from the FP32 master weights
+// Adam (update = 1) or shadow refresh only (update = 0); bf16 shadows W^T (fop x fip, in
+// fragment order) and W [fip x fop] (layers >= 1) rewritten from the FP32 master weights
 struct AdamArgs {
     LayerGeom g;
     float* P;

@@ -151,10 +151,24 @@ mppi_status forward(mppi_policy* p, const float* d_in, const int* d_idx, int B, 
 {
     const int bp = pad64(B);
     PrepArgs pa{d_in, d_idx, B, bp, at<float>(p, p->o_norm), at<float>(p, p->o_norm) + 40,
-                at<__bf16>(p, p->o_X0), at<__bf16>(p, p->o_X0t)};
+                at<__bf16>(p, p->o_X0), at<__bf16>(p, p->o_X0t), {}};
     mppi_status s;
-    if ((s = phip(p, launch_prep(pa, st), "input launch"))) return s;
     const float* P = at<float>(p, p->o_P);
+    // Nothing but the output is wanted: the whole pass in one launch, in which a workgroup writes
+    // its output rows while others still read their inputs; an output over the input therefore
+    // takes the launches per layer, which have read all of it first.  (With indices the output is
+    // the workspace's own.)
+    const uintptr_t in0 = reinterpret_cast<uintptr_t>(d_in), out0 = reinterpret_cast<uintptr_t>(d_out);
+    const bool apart = d_idx || in0 + 4ull * B * kIn <= out0 || out0 + 4ull * B * kOut <= in0;
+    if (!keep && apart) {
+        for (int l = 0; l < kLayers; ++l) {
+            pa.net.Wt[l] = at<__bf16>(p, p->o_Wt[l]);
+            pa.net.bias[l] = P + p->geom.off[l] + kFi[l] * kFo[l];
+        }
+        pa.net.out = d_out;
+        return phip(p, launch_prep(pa, st), "forward launch");
+    }
+    if ((s = phip(p, launch_prep(pa, st), "input launch"))) return s;
     for (int l = 0; l < kLayers; ++l) {
         GemmArgs g{};
         g.A = l ? at<__bf16>(p, p->o_H[l - 1]) : at<__bf16>(p, p->o_X0);
