@@ -691,7 +691,7 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
         R q[4] = {sel(odd, bx.qw, b.qw), sel(odd, bx.qx, b.qx), sel(odd, bx.qy, b.qy), sel(odd, bx.qz, b.qz)};
         const V3<R> ph = (R(0.5) * dtr) * selv(odd, bx.w, b.w);
         // in a stated order (see mul_ordered)
-        quat_turn(q[0], q[1], q[2], q[3], ph, m_sqrt(fma(ph.z, ph.z, fma(ph.y, ph.y, ph.x * ph.x))));
+        quat_turn(q[0], q[1], q[2], q[3], ph, m_sqrt(R(fma(ph.z, ph.z, fma(ph.y, ph.y, ph.x * ph.x)))));
         b.qw = dpp<0x00>(q[0]); b.qx = dpp<0x00>(q[1]); b.qy = dpp<0x00>(q[2]); b.qz = dpp<0x00>(q[3]);
         bx.qw = dpp<0x55>(q[0]); bx.qx = dpp<0x55>(q[1]); bx.qy = dpp<0x55>(q[2]); bx.qz = dpp<0x55>(q[3]);
     }
