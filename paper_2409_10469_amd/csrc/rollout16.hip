@@ -501,7 +501,8 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
             sred[g] = a0;
             if (g < 12) {
                 sred[g + 16] = a1;
-                if constexpr (SCENE == 3) sred[28 + 16 + min(g, 10)] = b1;
+                if constexpr (SCENE == 3)
+                if (g < 11) sred[28 + 16 + g] = b1;
             }
         }
         __syncthreads();
@@ -995,7 +996,8 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
         sred[g] = s0;
         if (g < 12) {
             sred[g + 16] = s1;
-            if constexpr (SCENE == 3) sred[28 + 16 + min(g, 10)] = b1;
+            if constexpr (SCENE == 3)
+                if (g < 11) sred[28 + 16 + g] = b1;
         }
     }
     __syncthreads();
