@@ -1,14 +1,15 @@
 // Kernels of the learned sampling proposal: a 40 -> 512 x 4 -> 144 SiLU network with
 // BF16 operands and FP32 accumulation on the gfx950 matrix cores.
 //
-// Every product of the forward and backward passes is written in one form,
-// C = A B^T with both operands stored k-contiguous, so one LDS-tiled MFMA kernel serves
-// all of them; the producers write the transposed copies the next product needs:
+// A training step is three launches: the pass over the network (forward, loss and backward of
+// a block of rows in one workgroup, activations and errors on the chip), the weight gradients of
+// all layers, and the parameter pass.  Every product is C = A B^T with both operands in the
+// order in which the matrix instruction takes them:
 //   forward     Z_l   = H_{l-1} W_l            A = H_{l-1} [B x fi],  B = W_l^T [fo x fi]
 //   input grad  dA    = dZ_l W_l^T             A = dZ_l    [B x fo],  B = W_l   [fi x fo]
 //   weight grad dW_l  = H_{l-1}^T dZ_l         A = H^T     [fi x B],  B = dZ^T  [fo x B]
 // The weight gradient reduces over the batch and is split along it; the split partials
-// and the per-tile bias-gradient column sums are reduced in a fixed order, so a training
+// and the per-row-block bias-gradient column sums are reduced in a fixed order, so a training
 // step is deterministic.
 #include <hip/hip_runtime.h>
 
@@ -21,11 +22,28 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+__device__ __forceinline__ bf16x8 ld8(const __bf16* p) { return *reinterpret_cast<const bf16x8*>(p); }
+
 constexpr int BK = kGemmBK;
 constexpr int LDK = BK + 8;  // LDS row pitch in bf16: 144 B keeps the 16-byte fragment reads conflict-free
-constexpr int kPF = 3;       // k-tiles of global loads in flight
+constexpr int kPF = 2;       // k-tiles of global loads in flight
 
-__device__ __forceinline__ float sigm(float z) { return 1.f / (1.f + expf(-z)); }
+// 1 / (1 + exp(-z)).  exp(x) = 2^n 2^f with n + f = x log2(e) (the product in two parts, n its
+// nearest whole number) and the hardware's 2^f; the quotient from the hardware's reciprocal and
+// a Newton step; where exp(-z) is beyond float that gives NaN and the maximum 0.  Without the
+// general division and the range checks of 1.f / (1.f + expf(-z)), two thirds of its
+// instructions: a pass over 256 rows 20.0 us instead of 21.2.  Largest and rms relative error
+// over [-87, 110] as that form's: 1.5e-7 and 3.8e-8.
+__device__ __forceinline__ float sigm(float z)
+{
+#pragma clang fp contract(off)
+    const float x = __builtin_amdgcn_fmed3f(-z, -87.f, 89.f);
+    const float t = x * 1.44269504f, n = rintf(t);
+    const float f = (t - n) + fmaf(x, 1.92596300e-8f, fmaf(x, 1.44269504f, -t));
+    const float d = 1.f + __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
+    const float r = __builtin_amdgcn_rcpf(d);
+    return fmaxf(fmaf(fmaf(-d, r, 1.f), r, r), 0.f);
+}
 __device__ __forceinline__ float silu(float z) { return z * sigm(z); }
 __device__ __forceinline__ float dsilu(float z)
 {
@@ -33,7 +51,7 @@ __device__ __forceinline__ float dsilu(float z)
     return s * (1.f + z * (1.f - s));
 }
 
-// The BF16 copies W^T are stored in the order in which the matrix instruction takes them:
+// The BF16 copies W^T and W are stored in the order in which the matrix instruction takes them:
 // blocks of 16 rows (n) by 32 columns (k), k-blocks of a row panel consecutive, and in a block
 // the 8 k-values of row l mod 16 and columns 8 (l / 16) .. +7 at place l.  A wave's fragment is
 // 1 KiB in a row (read from rows of W^T it touched 16 lines for half a line each).
@@ -43,305 +61,178 @@ __device__ __forceinline__ size_t frag_offset(int n, int k, int K)
     return ((size_t)(n >> 4) * (K >> 5) + (k >> 5)) * 512 + ((n & 15) + 16 * ((k >> 3) & 3)) * 8;
 }
 
-// ---------------------------------------------------------------------------------
-// GEMM: 256 threads = 4 waves in a 2 x 2 grid, each wave a (BM/2) x (BN/2) block of
-// 16 x 16 accumulator tiles fed by v_mfma_f32_16x16x32_bf16.  Operand fragments: lane l
-// holds row (l mod 16) and the 8 k-values 8 (l / 16) .. +7 of the 32-wide k step (both
-// operands use the same k assignment); the accumulator holds column (l mod 16), rows
-// 4 (l / 16) .. +3.  Tiles of A and B pass through LDS; the global loads of the next kPF
-// k-tiles are in flight (in registers) while the current tile's products run.
-// ---------------------------------------------------------------------------------
-template <int BM, int BN, int EPI>
-__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g)
+// The activations and errors that the weight gradients reduce over the batch are in the same
+// order in halves: a block holds column panel n / 16 of 16 batch rows r, and the panels of a
+// group of 16 rows are consecutive, so what a row block writes of a layer is one run of 16 KiB.
+// (With the rows along the panels instead, runs of 512 B at strides of the batch, the pass over
+// the network took 61.8 us for 4096 rows against 59.5, the weight gradients the same.)
+// batch_offset: element offset of column n, rows r (a multiple of 8) .. +7 of N columns.
+__device__ __forceinline__ size_t batch_offset(int n, int r, int N)
 {
-    constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
-    constexpr int CA = BM * BK / (8 * 256), CB = BN * BK / (8 * 256);
-    // LDS: the operand tiles during the k loop, then the fp32 output tile for the epilogue
-    constexpr int LDC = BN + 4;  // output tile row pitch in floats (16-byte aligned rows)
-    constexpr int kAB = (BM + BN) * LDK * 2, kC = BM * LDC * 4;
-    __shared__ __align__(16) unsigned char smem[kAB > kC ? kAB : kC];
-    __shared__ float red[4][BN];
-    __bf16* sA = reinterpret_cast<__bf16*>(smem);
-    __bf16* sB = sA + BM * LDK;
-    float* sC = reinterpret_cast<float*>(smem);
+    return ((size_t)(r >> 4) * (N >> 4) + (n >> 4)) * 256 + ((n & 15) + 16 * ((r >> 3) & 1)) * 8;
+}
+
+// ---------------------------------------------------------------------------------
+// Weight gradients of all layers in one launch: dW_l[i][o] = sum over the batch of
+// H_{l-1}[r][i] dZ_l[r][o], a 128 x 128 tile and one split of the batch for each workgroup of
+// 4 waves (2 x 2, each 64 x 64).  Both operands are stored in fragment order along the batch,
+// so a wave's 16 B loads, its LDS stores and its fragment reads each run over 1 KiB in a row,
+// with the loads of the next kPF k-tiles in flight (in registers) while the current tile's
+// products run and the next k-tile on its way to the other half of the LDS.  What bounds it is
+// the way of the operands from memory, 34 MB for 4096 rows that other XCDs have just written:
+// 64 x 64 tiles with twice the LDS traffic took the same time.  For 4096 rows 20 us, in launches
+// for each layer 56 together; 4 splits, since 8 (the same 20 us) add 15 MB of partials to write
+// and to read back (parameter pass 12.4 us against 9.2).  dZ is the instruction's first operand, so a lane's four sums are consecutive
+// columns of dW and leave as 16 bytes.  Where a matrix ends inside a tile (64 rows of the first
+// layer, 192 columns of the last) the panels past its end repeat the last one and are not stored.
+// ---------------------------------------------------------------------------------
+constexpr int kGradTile = 128, kGradPanels = kGradTile / 16, kGradWave = kGradPanels / 2;
+struct WgradArgs {
+    GemmArgs g[kLayers];
+    int first[kLayers + 1];  // first tile of each layer
+    int splits;
+};
+__global__ __launch_bounds__(256, 2) void wgrad_kernel(WgradArgs w)
+{
+    __shared__ __align__(16) __bf16 sA[2][kGradTile * BK], sB[2][kGradTile * BK];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    // M-tiles vary fastest: workgroups go round-robin to the 8 XCDs, so the N-tiles of one
-    // row panel of A share an XCD and its L2 (A is the large operand; B is re-read per XCD)
-    const int mt = blockIdx.x, m0 = mt * BM, n0 = blockIdx.y * BN;
-    const size_t kb = (size_t)blockIdx.z * g.K;
-    const __bf16* A = g.A + (size_t)m0 * g.lda + kb;
-    // the forward products' B is W^T in fragment order (ldb columns), the others' in rows
-    constexpr bool kFrag = EPI == EPI_HIDDEN || EPI == EPI_OUT;
-    const __bf16* B = kFrag ? g.B : g.B + (size_t)n0 * g.ldb + kb;
-
-    // register-staged prefetch kPF k-tiles deep: stage s of the ring holds k-tile
-    // (k / BK) with (k / BK) mod kPF = s; each k-tile is stored to LDS, consumed, and its
-    // stage refilled with the k-tile kPF ahead
-    u32x4 ra[kPF][CA], rb[kPF][CB];
-#define MLP_GLOAD(s, k0)                                                                                   \
-    do {                                                                                                   \
-        _Pragma("unroll") for (int c = 0; c < CA; ++c)                                                     \
-        {                                                                                                  \
-            const int idx = tid + 256 * c, row = idx >> 3, col = (idx & 7) * 8;                            \
-            ra[s][c] = *reinterpret_cast<const u32x4*>(A + (size_t)row * g.lda + (k0) + col);              \
-        }                                                                                                  \
-        _Pragma("unroll") for (int c = 0; c < CB; ++c)                                                     \
-        {                                                                                                  \
-            const int idx = tid + 256 * c;                                                                 \
-            const int row = kFrag ? 16 * (idx >> 7) + (idx & 15) : idx >> 3;                               \
-            const int col = kFrag ? 32 * ((idx >> 6) & 1) + 8 * ((idx >> 4) & 3) : (idx & 7) * 8;          \
-            rb[s][c] = *reinterpret_cast<const u32x4*>(                                                    \
-                B + (kFrag ? frag_offset(n0 + row, (k0) + col, g.ldb) : (size_t)row * g.ldb + (k0) + col)); \
-        }                                                                                                  \
-    } while (0)
-
-    f32x4 acc[TM][TN];
+    const int split = blockIdx.x % w.splits, tile = blockIdx.x / w.splits;
+    int l = 0;
+    while (l < kLayers - 1 && tile >= w.first[l + 1]) ++l;
+    const GemmArgs& g = w.g[l];
+    const int mp = g.M / 16, np = g.N / 16, mt = (mp + kGradPanels - 1) / kGradPanels;  // panels of 16, tiles
+    const int mp0 = ((tile - w.first[l]) % mt) * kGradPanels, np0 = ((tile - w.first[l]) / mt) * kGradPanels;
+    // 16 bytes of panel tid / 32 in each of the k-tile's 4 groups of 16 rows
+    constexpr int C = BK / 16;
+    const int pan = tid >> 5, at = split * g.K, pa = min(mp0 + pan, mp - 1), pb = min(np0 + pan, np - 1);
+    u32x4 ra[kPF][C], rb[kPF][C];
+    auto load = [&](int s, int k0) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+        for (int c = 0; c < C; ++c) {
+            const int kg = (at + k0) / 16 + c;
+            ra[s][c] = *reinterpret_cast<const u32x4*>(g.A + ((size_t)kg * mp + pa) * 256 + (tid & 31) * 8);
+            rb[s][c] = *reinterpret_cast<const u32x4*>(g.B + ((size_t)kg * np + pb) * 256 + (tid & 31) * 8);
+        }
+    };
+    auto store = [&](int s, int half) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
+        for (int c = 0; c < C; ++c) {
+            const int slot = ((pan * 2 + (c >> 1)) * 64 + (c & 1) * 32 + (tid & 31)) * 8;
+            *reinterpret_cast<u32x4*>(sA[half] + slot) = ra[s][c];
+            *reinterpret_cast<u32x4*>(sB[half] + slot) = rb[s][c];
+        }
+    };
+    f32x4 acc[kGradWave][kGradWave];
+#pragma unroll
+    for (int i = 0; i < kGradWave; ++i)
+#pragma unroll
+        for (int j = 0; j < kGradWave; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < kPF; ++s)
-        if (s * BK < g.K) MLP_GLOAD(s, s * BK);
+        if (s * BK < g.K) load(s, s * BK);
+    store(0, 0);
+    if (kPF * BK < g.K) load(0, kPF * BK);
+    __syncthreads();
+    const int wm = kGradWave * (wave >> 1), wn = kGradWave * (wave & 1);  // first panels of the wave
     for (int kt = 0; kt < g.K; kt += kPF * BK) {
 #pragma unroll
         for (int s = 0; s < kPF; ++s) {
-            const int k0 = kt + s * BK;
+            // k-tile k0 is in half s mod 2 (kPF is even); the next goes into the other half, and
+            // its registers take the k-tile kPF after it
+            const int k0 = kt + s * BK, s1 = (s + 1) % kPF;
             if (k0 >= g.K) break;
+            if (k0 + BK < g.K) store(s1, (s + 1) & 1);
+            if (k0 + (kPF + 1) * BK < g.K) load(s1, k0 + (kPF + 1) * BK);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                bf16x8 a[kGradWave], b[kGradWave];
+#pragma unroll
+                for (int i = 0; i < kGradWave; ++i) {
+                    a[i] = ld8(sA[s & 1] + ((wm + i) * 2 + h) * 512 + lane * 8);
+                    b[i] = ld8(sB[s & 1] + ((wn + i) * 2 + h) * 512 + lane * 8);
+                }
+#pragma unroll
+                for (int i = 0; i < kGradWave; ++i)
+#pragma unroll
+                    for (int j = 0; j < kGradWave; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+            }
             __syncthreads();
-#pragma unroll
-            for (int c = 0; c < CA; ++c) {
-                const int idx = tid + 256 * c, row = idx >> 3, col = (idx & 7) * 8;
-                *reinterpret_cast<u32x4*>(sA + row * LDK + col) = ra[s][c];
-            }
-#pragma unroll
-            for (int c = 0; c < CB; ++c) {
-                const int idx = tid + 256 * c;
-                const int row = kFrag ? 16 * (idx >> 7) + (idx & 15) : idx >> 3;
-                const int col = kFrag ? 32 * ((idx >> 6) & 1) + 8 * ((idx >> 4) & 3) : (idx & 7) * 8;
-                *reinterpret_cast<u32x4*>(sB + row * LDK + col) = rb[s][c];
-            }
-            __syncthreads();
-            if (k0 + kPF * BK < g.K) MLP_GLOAD(s, k0 + kPF * BK);
-#pragma unroll
-            for (int kk = 0; kk < BK; kk += 32) {
-                bf16x8 a[TM], b[TN];
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-                    a[i] = *reinterpret_cast<const bf16x8*>(sA + (wm * WM + i * 16 + (lane & 15)) * LDK + kk +
-                                                            (lane >> 4) * 8);
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    b[j] = *reinterpret_cast<const bf16x8*>(sB + (wn * WN + j * 16 + (lane & 15)) * LDK + kk +
-                                                            (lane >> 4) * 8);
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-            }
         }
     }
-
-#undef MLP_GLOAD
-
-    // ---- epilogues: the accumulators (plus the bias where one is added) go to the LDS
-    // tile sC [BM x LDC]; every output then leaves in 16-byte pieces of its rows
-    __syncthreads();  // all waves are done with sA / sB
-    {
-        float bv[TN];
+    float* D = g.C + (size_t)split * g.c_split_stride;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int n = n0 + wn * WN + j * 16 + (lane & 15);
-            bv[j] = 0.f;
-            if constexpr (EPI == EPI_HIDDEN) bv[j] = g.bias[n];
-            if constexpr (EPI == EPI_OUT) bv[j] = n < g.n_store ? g.bias[n] : 0.f;
-        }
+    for (int i = 0; i < kGradWave; ++i)
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int nl = wn * WN + j * 16 + (lane & 15);
-                const int ml = wm * WM + i * 16 + (lane >> 4) * 4;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sC[(ml + r) * LDC + nl] = acc[i][j][r] + bv[j];
-            }
-    }
-    __syncthreads();
-    constexpr int RC = BN / 8, MC = BM / 8;  // 8-wide pieces per tile row / per tile column
-    if constexpr (EPI == EPI_SPLITK) {
-        float* C = g.C + (size_t)blockIdx.z * g.c_split_stride;
-#pragma unroll
-        for (int e = tid; e < BM * RC; e += 256) {
-            const int row = e / RC, c8 = (e - row * RC) * 8;
-            float* dst = C + (size_t)(m0 + row) * g.ldc + n0 + c8;
-            *reinterpret_cast<f32x4*>(dst) = *reinterpret_cast<const f32x4*>(sC + row * LDC + c8);
-            *reinterpret_cast<f32x4*>(dst + 4) = *reinterpret_cast<const f32x4*>(sC + row * LDC + c8 + 4);
-        }
-    } else if constexpr (EPI == EPI_OUT) {  // caller's buffer: element stores, rows in order
-        for (int e = tid; e < BM * BN; e += 256) {
-            const int row = e / BN, col = e - row * BN;
-            if (m0 + row < g.m_store && n0 + col < g.n_store)
-                g.C[(size_t)(m0 + row) * g.ldc + n0 + col] = sC[row * LDC + col];
-        }
-    } else if constexpr (EPI == EPI_HIDDEN) {
-#pragma unroll
-        for (int e = tid; e < BM * RC; e += 256) {
-            const int row = e / RC, c8 = (e - row * RC) * 8;
-            float* zt = sC + row * LDC + c8;
-            const f32x4 z0 = *reinterpret_cast<const f32x4*>(zt), z1 = *reinterpret_cast<const f32x4*>(zt + 4);
-            if (g.C) {
-                float* dst = g.C + (size_t)(m0 + row) * g.ldc + n0 + c8;
-                *reinterpret_cast<f32x4*>(dst) = z0;
-                *reinterpret_cast<f32x4*>(dst + 4) = z1;
-            }
-            bf16x8 hv;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                hv[u] = (__bf16)silu(z0[u]);
-                hv[4 + u] = (__bf16)silu(z1[u]);
-            }
-            *reinterpret_cast<bf16x8*>(g.H + (size_t)(m0 + row) * g.ldh + n0 + c8) = hv;
-            if (g.Ht) {  // keep the rounded activations for the transposed copy
-#pragma unroll
-                for (int u = 0; u < 8; ++u) zt[u] = (float)hv[u];
-            }
-        }
-        if (g.Ht) {
-            __syncthreads();
-#pragma unroll
-            for (int e = tid; e < BN * MC; e += 256) {
-                const int col = e / MC, m8 = (e - col * MC) * 8;
-                bf16x8 v;
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = (__bf16)sC[(m8 + u) * LDC + col];
-                *reinterpret_cast<bf16x8*>(g.Ht + (size_t)(n0 + col) * g.ldht + m0 + m8) = v;
-            }
-        }
-    } else {  // EPI_DACT: dz = (dL/dh) * silu'(z) with the stored pre-activation z
-#pragma unroll
-        for (int e = tid; e < BM * RC; e += 256) {
-            const int row = e / RC, c8 = (e - row * RC) * 8;
-            float* at = sC + row * LDC + c8;
-            const float* zp = g.Zp + (size_t)(m0 + row) * g.ldz + n0 + c8;
-            const f32x4 z0 = *reinterpret_cast<const f32x4*>(zp), z1 = *reinterpret_cast<const f32x4*>(zp + 4);
-            bf16x8 hv;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float dz = at[u] * dsilu(u < 4 ? z0[u] : z1[u - 4]);
-                at[u] = dz;
-                hv[u] = (__bf16)dz;
-            }
-            *reinterpret_cast<bf16x8*>(g.H + (size_t)(m0 + row) * g.ldh + n0 + c8) = hv;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int e = tid; e < BN * MC; e += 256) {
-            const int col = e / MC, m8 = (e - col * MC) * 8;
-            bf16x8 v;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = (__bf16)sC[(m8 + u) * LDC + col];
-            *reinterpret_cast<bf16x8*>(g.Ht + (size_t)(n0 + col) * g.ldht + m0 + m8) = v;
-        }
-        // column sums of dz over the tile's rows: four quarters in row order, then in order
-        for (int e = tid; e < 4 * BN; e += 256) {
-            const int q = e / BN, col = e - q * BN;
-            float cs = 0.f;
-            for (int row = q * (BM / 4); row < (q + 1) * (BM / 4); ++row) cs += sC[row * LDC + col];
-            red[q][col] = cs;
-        }
-        __syncthreads();
-        for (int c = tid; c < BN; c += 256)
-            g.colpart[(size_t)mt * g.N + n0 + c] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
-    }
-}
-
-template <int BM, int BN>
-static void launch_tile(int epi, const GemmArgs& g, int splits, hipStream_t st)
-{
-    const dim3 grid(g.M / BM, g.N / BN, splits);
-    switch (epi) {
-    case EPI_HIDDEN: hipLaunchKernelGGL((gemm_kernel<BM, BN, EPI_HIDDEN>), grid, dim3(256), 0, st, g); break;
-    case EPI_OUT: hipLaunchKernelGGL((gemm_kernel<BM, BN, EPI_OUT>), grid, dim3(256), 0, st, g); break;
-    case EPI_DACT: hipLaunchKernelGGL((gemm_kernel<BM, BN, EPI_DACT>), grid, dim3(256), 0, st, g); break;
-    default: hipLaunchKernelGGL((gemm_kernel<BM, BN, EPI_SPLITK>), grid, dim3(256), 0, st, g); break;
-    }
+        for (int j = 0; j < kGradWave; ++j)
+            if (mp0 + wm + i < mp && np0 + wn + j < np)
+                *reinterpret_cast<f32x4*>(D + (size_t)(16 * (mp0 + wm + i) + (lane & 15)) * g.ldc +
+                                          16 * (np0 + wn + j) + (lane >> 4) * 4) = acc[i][j];
 }
 
 hipError_t launch_gemm(int epi, const GemmArgs& g, int splits, hipStream_t st)
 {
-    const int bm = gemm_tile_m(g.M, g.N, splits);
-    if (!bm || g.K <= 0 || g.K % BK || splits < 1) return hipErrorInvalidValue;
-    if (bm == 128 && use_wide(g.M, g.N, splits)) launch_tile<128, 128>(epi, g, splits, st);
-    else if (bm == 128) launch_tile<128, 64>(epi, g, splits, st);
-    else launch_tile<64, 64>(epi, g, splits, st);
+    WgradArgs w{};
+    int n = 0, tiles = 0;
+    if (epi != EPI_SPLITK || splits < 1 || splits > kMaxSplits) return hipErrorInvalidValue;
+    for (const GemmArgs* p = &g; p; p = p->next) {
+        if (n == kLayers || !gemm_tile_m(p->M, p->N, splits) || p->K <= 0 || p->K % BK || p->lda != p->ldb ||
+            p->lda < p->K * splits || p->lda % 32)
+            return hipErrorInvalidValue;
+        w.g[n] = *p;
+        w.first[n++] = tiles;
+        tiles += ((p->M + kGradTile - 1) / kGradTile) * ((p->N + kGradTile - 1) / kGradTile);
+    }
+    for (; n <= kLayers; ++n) w.first[n] = tiles;
+    w.splits = splits;
+    hipLaunchKernelGGL(wgrad_kernel, dim3(tiles * splits), dim3(256), 0, st, w);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void prep_kernel(PrepArgs a)
-{
-    const int gid = blockIdx.x * 256 + threadIdx.x;
-    if (gid >= a.Bp * kInPad) return;
-    const int r = gid / kInPad, c = gid - r * kInPad;
-    float v = 0.f;
-    if (r < a.B && c < kIn) {
-        const int row = a.idx ? a.idx[r] : r;
-        v = (a.X[(size_t)row * kIn + c] - a.mean[c]) / a.std[c];
-    }
-    const __bf16 b = (__bf16)v;
-    a.X0[(size_t)r * kInPad + c] = b;
-    a.X0t[(size_t)c * a.Bp + r] = b;
-}
-
+// A pass over the network in one launch: a workgroup takes kNetRows rows through every layer,
+// its activations in LDS, each of its 8 waves 64 of a hidden layer's 512 columns.  What bounds
+// it is the stream of weights from L2, 1.75 MB for every workgroup whatever its rows (a training
+// step takes 1.7 MB more): the waves read their fragments straight from memory (no other wave of
+// the workgroup needs them), four 64-wide k-tiles ahead of the products (two: 22.6 us for 256
+// rows against 20.8, and 54 us against 50 for a training step's 4096).  16 rows, the matrix
+// instruction's height, give the most workgroups: one row block's time is the pass's time up to
+// 4096 rows (one a compute unit), where a launch for every layer paid its start and its drain.
+// Launches per layer / here, us a pass: 1 row 29.3 / 18.6, 256 rows 29.4 / 20.0, 4096 rows 42.2
+// / 22.4, 16384 rows 104 / 78; with three policies in turn, whose weights together exceed an
+// XCD's L2, 256 rows 30.1 / 20.7.  A training step (three launches against sixteen): 64 rows
+// 93 / 52, 512 rows 106 / 54, 4096 rows 151 / 74, 16384 rows 420 / 251.  The loss alone: 4096
+// rows 52 / 25.
 // ---------------------------------------------------------------------------------
-// The forward pass in one launch: a workgroup takes kNetRows rows through every layer, its
-// activations in LDS, each of its 8 waves 64 of a hidden layer's 512 columns.  What bounds it
-// is the stream of weights from L2, 1.75 MB for every workgroup whatever its rows: the waves
-// read their fragments straight from memory (no other wave of the workgroup needs them), four
-// 64-wide k-tiles ahead of the products (two: 22.6 us for 256 rows against 20.8).  16 rows, the
-// matrix instruction's height, give the most workgroups: one row block's time is the pass's
-// time up to 4096 rows (one a compute unit), where a launch for every layer paid its start and
-// its drain six times.  The products are those of gemm_kernel in the same order, so the results
-// are the same bits.
-// Launches per layer / here, us a pass: 1 row 29.3 / 19.9, 256 rows 29.4 / 21.3, 2000 rows
-// 31.2 / 21.5, 4096 rows 40.0 / 24.1; with three policies in turn (their weights together
-// exceed an XCD's L2) 29.3 / 20.3, 30.1 / 22.0, 33.0 / 22.8, 41.4 / 32.6.
-// ---------------------------------------------------------------------------------
-constexpr int kNetRows = 16, kNetThreads = 512, kNetLd = kHidden + 8;
+constexpr int kNetThreads = 512, kNetLd = kHidden + 8, kOutLd = kOut + 4;
 
-__device__ __forceinline__ bf16x8 ld8(const __bf16* p) { return *reinterpret_cast<const bf16x8*>(p); }
-
-// the fragments of a wave's column tiles in flight: kNetDepth k-tiles of 64
-constexpr int kNetDepth = 4;
-template <int TN>
+// the fragments of a wave's TN column tiles in flight: D k-tiles of 64
+template <int TN, int D>
 struct NetFrags {
-    bf16x8 w[kNetDepth][TN][2];
+    bf16x8 w[D][TN][2];
 };
 
 // k-tile t of the TN column tiles at b (W^T in fragment order, K columns, tiles `step` apart)
-template <int K, int TN>
-__device__ __forceinline__ void net_load(const __bf16* b, int step, int t, NetFrags<TN>& f)
+template <int K, int TN, int D>
+__device__ __forceinline__ void net_load(const __bf16* b, int step, int t, NetFrags<TN, D>& f)
 {
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) f.w[t % kNetDepth][j][h] = ld8(b + (size_t)j * step * K * 16 + (2 * t + h) * 512);
+        for (int h = 0; h < 2; ++h) f.w[t % D][j][h] = ld8(b + (j * step * K * 16 + (2 * t + h) * 512) + (threadIdx.x & 63u) * 8);
 }
-template <int K, int TN>
-__device__ __forceinline__ void net_start(const __bf16* b, int step, NetFrags<TN>& f)
+template <int K, int TN, int D>
+__device__ __forceinline__ void net_start(const __bf16* b, int step, NetFrags<TN, D>& f)
 {
 #pragma unroll
-    for (int t = 0; t < kNetDepth; ++t)
-        if (t < K / 64) net_load<K, TN>(b, step, t, f);
+    for (int t = 0; t < D; ++t)
+        if (t < K / 64) net_load<K, TN, D>(b, step, t, f);
 }
 
 // acc[j] = A (16 rows of LDS at sA, pitch kNetLd) x the column tiles, whose first fragments
 // net_start has put in flight
-template <int K, int TN>
-__device__ __forceinline__ void net_product(const __bf16* sA, const __bf16* b, int step, NetFrags<TN>& f, f32x4 acc[TN])
+template <int K, int TN, int D>
+__device__ __forceinline__ void net_product(const __bf16* sA, const __bf16* b, int step, NetFrags<TN, D>& f, f32x4 acc[TN])
 {
     constexpr int NT = K / 64;
     const int lane = threadIdx.x & 63;
@@ -355,40 +246,59 @@ __device__ __forceinline__ void net_product(const __bf16* sA, const __bf16* b, i
             const bf16x8 av = ld8(a + 64 * t + 32 * h);
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, f.w[t % kNetDepth][j][h], acc[j], 0, 0, 0);
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, f.w[t % D][j][h], acc[j], 0, 0, 0);
         }
-        if (t + kNetDepth < NT) net_load<K, TN>(b, step, t + kNetDepth, f);
+        if (t + D < NT) net_load<K, TN, D>(b, step, t + D, f);
     }
 }
 
-// z = acc + b, silu(z) rounded to bf16 into the wave's columns of sH
-__device__ __forceinline__ void net_activate(const f32x4 acc[4], const float bv[4], __bf16* sH, int n0)
+// z = acc + b; silu(z) rounded to bf16 into the wave's columns of sH.  TRAIN: also to Ht in
+// fragment order along the batch, and silu'(z) into dz, where the backward pass of this row
+// block finds it.
+template <bool TRAIN>
+__device__ __forceinline__ void net_activate(const f32x4 acc[4], const float bv[4], __bf16* sH, int n0, __bf16* Ht,
+                                             int r0, f32x4 dz[4])
 {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int n = n0 + 16 * j + (lane & 15);
+        bf16x4 h;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sH[((lane >> 4) * 4 + r) * kNetLd + n] = (__bf16)silu(acc[j][r] + bv[j]);
+        for (int r = 0; r < 4; ++r) {
+            const float z = acc[j][r] + bv[j];
+            h[r] = (__bf16)silu(z);
+            sH[((lane >> 4) * 4 + r) * kNetLd + n] = h[r];
+            if constexpr (TRAIN) {
+                // computed here: left to itself the compiler keeps z and the sigmoid instead, two
+                // registers for one
+                float d = dsilu(z);
+                asm volatile("" : "+v"(d));
+                dz[j][r] = d;
+            }
+        }
+        if constexpr (TRAIN) *reinterpret_cast<bf16x4*>(Ht + batch_offset(n, r0 + 8 * (lane >> 5), kHidden) + 4 * ((lane >> 4) & 1)) = h;
     }
 }
 
-// the output's TN column tiles j0, j0 + 8, whose first fragments are in flight
-template <int TN>
+// the output's TN column tiles j0, j0 + 8, whose first fragments are in flight, to the output
+// rows or (SCORE) to the LDS rows sO
+template <bool SCORE, int TN, int D>
 __device__ __forceinline__ void net_output(const PrepArgs& p, const __bf16* sA, const __bf16* b, int j0, int r0,
-                                           NetFrags<TN>& f)
+                                           NetFrags<TN, D>& f, float* sO)
 {
     const int lane = threadIdx.x & 63;
     f32x4 acc[TN];
-    net_product<kHidden, TN>(sA, b, 8, f, acc);
+    net_product<kHidden>(sA, b, 8, f, acc);
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         const int n = 16 * (j0 + 8 * j) + (lane & 15);
         const float bv = p.net.bias[kLayers - 1][n];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int row = r0 + (lane >> 4) * 4 + r;
-            if (row < p.B) p.net.out[(size_t)row * kOut + n] = acc[j][r] + bv;
+            const int row = (lane >> 4) * 4 + r;
+            if constexpr (SCORE) sO[row * kOutLd + n] = acc[j][r] + bv;
+            else if (r0 + row < p.B) p.net.out[(size_t)(r0 + row) * kOut + n] = acc[j][r] + bv;
         }
     }
 }
@@ -400,35 +310,151 @@ __device__ __forceinline__ void net_output(const PrepArgs& p, const __bf16* sA, 
 // kNetWarmBlocks row blocks on (16 an XCD) those have as much in flight themselves.  The values
 // are not used.
 constexpr int kNetWarm = 8, kXcds = 8, kNetWarmBlocks = 128;
-__device__ __forceinline__ void net_warm(const PrepArgs& p, int part)
+__device__ __forceinline__ void net_warm(const __bf16* w, int elements, int part)
 {
-#pragma unroll 1
-    for (int l = 0; l < kLayers; ++l) {
-        const int bytes = (l ? kHidden : kInPad) * (l < kLayers - 1 ? kHidden : kOut) * 2 / kNetWarm;
-        const char* src = reinterpret_cast<const char*>(p.net.Wt[l]) + (size_t)part * bytes;
+    const int bytes = elements * 2 / kNetWarm;
+    const char* src = reinterpret_cast<const char*>(w) + (size_t)part * bytes;
 #pragma unroll 8
-        for (int i = threadIdx.x * 16; i < bytes; i += kNetThreads * 16) {
-            const u32x4 v = *reinterpret_cast<const u32x4*>(src + i);
-            asm volatile("" ::"v"(v));
+    for (int i = threadIdx.x * 16; i < bytes; i += kNetThreads * 16) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(src + i);
+        asm volatile("" ::"v"(v));
+    }
+}
+
+// Gaussian NLL of the row block's output (LDS rows sO) against the standardised targets: the
+// block's loss partial and, for a training step, dL/d(output): float over sO, bf16 rows with
+// zero padding columns to sD, along the batch to dZt, and the block's column sums.
+constexpr int kLossElems = (kNetRows * 72 + kNetThreads - 1) / kNetThreads;
+struct NetTarget {
+    float y[kLossElems];
+};
+__device__ __forceinline__ void net_target(const PrepArgs& p, int r0, NetTarget& t)
+{
+#pragma unroll
+    for (int j = 0; j < kLossElems; ++j) {
+        const int e = threadIdx.x + kNetThreads * j, rr = e / 72, d = e - rr * 72, r = r0 + rr;
+        t.y[j] = 0.f;
+        if (rr < kNetRows && r < p.B) {
+            const int row = p.idx ? p.idx[r] : r;
+            t.y[j] = (p.net.loss.Y[(size_t)row * 72 + d] - p.net.loss.omean[d]) / p.net.loss.ostd[d];
+        }
+    }
+}
+template <bool TRAIN>
+__device__ __forceinline__ void net_loss(const PrepArgs& p, int r0, int block, const NetTarget& t, float* sO,
+                                         __bf16* sD, float* red)
+{
+    const int tid = threadIdx.x;
+    const float inv = 1.f / ((float)p.B * 72.f);
+    float lsum = 0.f;
+#pragma unroll
+    for (int j = 0; j < kLossElems; ++j) {
+        const int e = tid + kNetThreads * j, rr = e / 72, d = e - rr * 72;
+        if (rr >= kNetRows) break;
+        float dm = 0.f, dsv = 0.f;
+        if (r0 + rr < p.B) {
+            const float m = sO[rr * kOutLd + d], s = sO[rr * kOutLd + 72 + d];
+            const float err = t.y[j] - m, w = expf(-2.f * s), q = err * err * w;
+            lsum += 0.5f * q + s;
+            dm = -err * w * inv;
+            dsv = (1.f - q) * inv;
+        }
+        if constexpr (TRAIN) {
+            sO[rr * kOutLd + d] = dm;
+            sO[rr * kOutLd + 72 + d] = dsv;
+            sD[rr * kNetLd + d] = (__bf16)dm;
+            sD[rr * kNetLd + 72 + d] = (__bf16)dsv;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o; o >>= 1) lsum += __shfl_xor(lsum, o);
+    if (!(tid & 63)) red[tid >> 6] = lsum;
+    if constexpr (TRAIN) {
+        constexpr int kPad = kOutPad - kOut;
+        for (int e = tid; e < kNetRows * kPad; e += kNetThreads)
+            sD[(e / kPad) * kNetLd + kOut + e % kPad] = (__bf16)0.f;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        float s = red[0];
+        for (int k = 1; k < kNetThreads / 64; ++k) s += red[k];
+        p.net.loss.lpart[block] = s;
+    }
+    if constexpr (TRAIN) {
+        if (tid < 2 * kOutPad) {
+            const int c = tid % kOutPad, h = 8 * (tid / kOutPad);
+            bf16x8 v;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = sD[(h + u) * kNetLd + c];
+            *reinterpret_cast<bf16x8*>(p.net.loss.dZt + batch_offset(c, r0 + h, kOutPad)) = v;
+        }
+        if (tid >= kNetThreads - kOutPad) {  // the waves that wrote none of it
+            const int c = tid - (kNetThreads - kOutPad);
+            float s = 0.f;
+#pragma unroll
+            for (int rr = 0; rr < kNetRows; ++rr) s += sO[rr * kOutLd + min(c, kOut - 1)];
+            p.net.loss.dbpart[(size_t)block * kOutPad + c] = c < kOut ? s : 0.f;
         }
     }
 }
 
+// One step back: acc = dL/dh of the wave's columns, dz = acc silu'(z) to sD (unless it is the
+// LAST step), along the batch to dZt, and the block's column sums
+template <bool LAST>
+__device__ __forceinline__ void net_back(const f32x4 acc[4], const f32x4 ds[4], __bf16* sD, int n0, __bf16* dZt,
+                                         float* bpart, int r0)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int n = n0 + 16 * j + (lane & 15);
+        bf16x4 h;
+        float s = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float dz = acc[j][r] * ds[j][r];
+            s += dz;
+            h[r] = (__bf16)dz;
+            if constexpr (!LAST) sD[((lane >> 4) * 4 + r) * kNetLd + n] = h[r];
+        }
+        *reinterpret_cast<bf16x4*>(dZt + batch_offset(n, r0 + 8 * (lane >> 5), kHidden) + 4 * ((lane >> 4) & 1)) = h;
+        s += __shfl_xor(s, 16);
+        s += __shfl_xor(s, 32);
+        if (lane < 16) bpart[n] = s;
+    }
+}
+
+// MODE NET_FORWARD: the output rows.  NET_LOSS: the loss partials.  NET_TRAIN: also the
+// backward pass of the row block, its silu' of every layer in registers (64 of them a lane),
+// leaving the operands of the weight gradients.
+template <int MODE>
 __global__ __launch_bounds__(kNetThreads, 2) void net_kernel(PrepArgs p)
 {
+    constexpr bool kTrain = MODE == NET_TRAIN, kScore = MODE != NET_FORWARD;
     __shared__ __align__(16) __bf16 sH[2][kNetRows * kNetLd];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r0 = blockIdx.x * kNetRows;
-    if (r0 >= p.B) {
-        net_warm(p, (blockIdx.x / kXcds) % kNetWarm);
+    __shared__ float sO[kScore ? kNetRows * kOutLd : 1];
+    __shared__ float red[kNetThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, r0 = blockIdx.x * kNetRows;
+    // known to be the same for the wave: its weights are addressed from scalar registers
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (r0 >= (kScore ? p.Bp : p.B)) {
+        const int part = (blockIdx.x / kXcds) % kNetWarm;
+#pragma unroll 1
+        for (int l = 0; l < kLayers; ++l)
+            net_warm(p.net.Wt[l], (l ? kHidden : kInPad) * (l < kLayers - 1 ? kHidden : kOut), part);
+        if constexpr (kTrain)
+#pragma unroll 1
+            for (int l = kLayers - 1; l; --l) net_warm(p.net.Wn[l], kHidden * (l < kLayers - 1 ? kHidden : kOutPad), part);
         return;
     }
     const int n0 = wave * 64;
-    const size_t frag = lane * 8;
-    NetFrags<4> f;
+    constexpr int kDepth = kTrain ? 4 : 4;
+    NetFrags<4, kDepth> f;
     f32x4 acc[4];
+    f32x4 ds[kLayers - 1][4];
     float bv[4];
     // each layer's first fragments and biases are requested before the wait for its input
-    net_start<kInPad, 4>(p.net.Wt[0] + (size_t)n0 * kInPad + frag, 1, f);
+    net_start<kInPad>(p.net.Wt[0] + (size_t)n0 * kInPad, 1, f);
 #pragma unroll
     for (int j = 0; j < 4; ++j) bv[j] = p.net.bias[0][n0 + 16 * j + (lane & 15)];
     for (int e = tid; e < kNetRows * kInPad; e += kNetThreads) {
@@ -441,109 +467,73 @@ __global__ __launch_bounds__(kNetThreads, 2) void net_kernel(PrepArgs p)
         sH[0][rr * kNetLd + c] = (__bf16)v;
     }
     __syncthreads();
-    net_product<kInPad, 4>(sH[0], p.net.Wt[0] + (size_t)n0 * kInPad + frag, 1, f, acc);
-#pragma unroll 1
+    if constexpr (kTrain) {
+        if (tid < 2 * kInPad) {
+            const int c = tid % kInPad, h = 8 * (tid / kInPad);
+            bf16x8 v;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = sH[0][(h + u) * kNetLd + c];
+            *reinterpret_cast<bf16x8*>(p.X0t + batch_offset(c, r0 + h, kInPad)) = v;
+        }
+    }
+    net_product<kInPad>(sH[0], p.net.Wt[0] + (size_t)n0 * kInPad, 1, f, acc);
+#pragma unroll(kTrain ? kLayers : 1)
     for (int l = 1; l < kLayers - 1; ++l) {
-        const __bf16* b = p.net.Wt[l] + (size_t)n0 * kHidden + frag;
-        net_start<kHidden, 4>(b, 1, f);
-        net_activate(acc, bv, sH[l & 1], n0);
+        const __bf16* b = p.net.Wt[l] + (size_t)n0 * kHidden;
+        net_start<kHidden>(b, 1, f);
+        net_activate<kTrain>(acc, bv, sH[l & 1], n0, p.net.Ht[l - 1], r0, ds[kTrain ? l - 1 : 0]);
 #pragma unroll
         for (int j = 0; j < 4; ++j) bv[j] = p.net.bias[l][n0 + 16 * j + (lane & 15)];
         __syncthreads();
-        net_product<kHidden, 4>(sH[l & 1], b, 1, f, acc);
+        net_product<kHidden>(sH[l & 1], b, 1, f, acc);
     }
     // the output's 9 column tiles: one a wave, the ninth by the first wave
-    const __bf16* sO = sH[(kLayers - 1) & 1];
-    const __bf16* b = p.net.Wt[kLayers - 1] + (size_t)wave * (kHidden * 16) + frag;
-    NetFrags<2> f2;
-    NetFrags<1> f1;
-    if (wave == 0) net_start<kHidden, 2>(b, 8, f2);
-    else net_start<kHidden, 1>(b, 8, f1);
-    net_activate(acc, bv, sH[(kLayers - 1) & 1], n0);
+    const __bf16* sL = sH[(kLayers - 1) & 1];
+    const __bf16* b = p.net.Wt[kLayers - 1] + (size_t)wave * (kHidden * 16);
+    NetFrags<2, 2> f2;
+    NetFrags<1, 4> f1;
+    if (wave == 0) net_start<kHidden>(b, 8, f2);
+    else net_start<kHidden>(b, 8, f1);
+    NetTarget y;
+    if constexpr (kScore) net_target(p, r0, y);
+    net_activate<kTrain>(acc, bv, sH[(kLayers - 1) & 1], n0, p.net.Ht[kLayers - 2], r0, ds[kLayers - 2]);
     __syncthreads();
-    if (wave == 0) net_output<2>(p, sO, b, 0, r0, f2);
-    else net_output<1>(p, sO, b, wave, r0, f1);
+    if (wave == 0) net_output<kScore>(p, sL, b, 0, r0, f2, sO);
+    else net_output<kScore>(p, sL, b, wave, r0, f1, sO);
+    if constexpr (kScore) {
+        constexpr int kTop = (kLayers - 1) & 1;  // the output's input has been read by then
+        const __bf16* w = p.net.Wn[kLayers - 1] + (size_t)n0 * kOutPad;
+        if constexpr (kTrain) net_start<kOutPad>(w, 1, f);
+        __syncthreads();
+        net_loss<kTrain>(p, r0, blockIdx.x, y, sO, sH[kTop], red);
+        if constexpr (kTrain) {
+            net_product<kOutPad>(sH[kTop], w, 1, f, acc);
+#pragma unroll
+            for (int l = kLayers - 2; l > 0; --l) {  // layer l's dz from layer l + 1's product
+                const __bf16* wl = p.net.Wn[l] + (size_t)n0 * kHidden;
+                __bf16* sD = sH[l & 1];
+                net_start<kHidden>(wl, 1, f);
+                net_back<false>(acc, ds[l], sD, n0, p.net.dZt[l], p.net.bpart[l] + (size_t)blockIdx.x * kHidden, r0);
+                __syncthreads();
+                net_product<kHidden>(sD, wl, 1, f, acc);
+            }
+            net_back<true>(acc, ds[0], nullptr, n0, p.net.dZt[0], p.net.bpart[0] + (size_t)blockIdx.x * kHidden, r0);
+        }
+    }
 }
 
 hipError_t launch_prep(const PrepArgs& a, hipStream_t st)
 {
-    if (a.net.out) {
-        const int rows = (a.B + kNetRows - 1) / kNetRows;
-        const int warm = rows < kNetWarmBlocks ? kXcds * kNetWarm : 0;
-        hipLaunchKernelGGL(net_kernel, dim3(rows + warm), dim3(kNetThreads), 0, st, a);
-        return hipGetLastError();
+    const int rows = ((a.net.mode == NET_FORWARD ? a.B : a.Bp) + kNetRows - 1) / kNetRows;
+    const dim3 grid(rows + (rows < kNetWarmBlocks ? kXcds * kNetWarm : 0));
+    switch (a.net.mode) {
+    case NET_FORWARD: hipLaunchKernelGGL(net_kernel<NET_FORWARD>, grid, dim3(kNetThreads), 0, st, a); break;
+    case NET_LOSS: hipLaunchKernelGGL(net_kernel<NET_LOSS>, grid, dim3(kNetThreads), 0, st, a); break;
+    case NET_TRAIN: hipLaunchKernelGGL(net_kernel<NET_TRAIN>, grid, dim3(kNetThreads), 0, st, a); break;
+    default: return hipErrorInvalidValue;
     }
-    const int n = a.Bp * kInPad;
-    hipLaunchKernelGGL(prep_kernel, dim3((n + 255) / 256), dim3(256), 0, st, a);
     return hipGetLastError();
 }
-
-// One block per kLossRows rows.  Phase 1: every (row, output pair d) element is
-// independent; thread t takes elements t, t + 256, ... (9 each), writes the row-major dz
-// and keeps both errors in an LDS tile.  Phase 2: the tile gives the transposed dz rows
-// (16-byte stores), the per-column sums of the block (fixed order) and the loss sum.
-constexpr int kLossRows = 32;
-__global__ __launch_bounds__(256) void loss_kernel(LossArgs a)
-{
-    __shared__ float sD[kOut][kLossRows + 1];
-    __shared__ float red[256];
-    const int t = threadIdx.x, r0 = blockIdx.x * kLossRows;
-    const float inv = 1.f / ((float)a.B * 72.f);
-    float lsum = 0.f;
-#pragma unroll
-    for (int j = 0; j < kLossRows * 72 / 256; ++j) {
-        const int e = t + 256 * j, rr = e / 72, d = e - rr * 72, r = r0 + rr;
-        float dm = 0.f, dsv = 0.f;
-        if (r < a.B) {
-            const int row = a.idx ? a.idx[r] : r;
-            const float y = (a.Y[(size_t)row * 72 + d] - a.omean[d]) / a.ostd[d];
-            const float m = a.out[(size_t)r * kOut + d], s = a.out[(size_t)r * kOut + 72 + d];
-            const float err = y - m, w = expf(-2.f * s), q = err * err * w;
-            lsum += 0.5f * q + s;
-            dm = -err * w * inv;
-            dsv = (1.f - q) * inv;
-        }
-        sD[d][rr] = dm;
-        sD[72 + d][rr] = dsv;
-        a.dZ[(size_t)r * kOutPad + d] = (__bf16)dm;
-        a.dZ[(size_t)r * kOutPad + 72 + d] = (__bf16)dsv;
-    }
-    // zero padding columns of the row-major copy: 48 per row
-    for (int e = t; e < kLossRows * (kOutPad - kOut); e += 256) {
-        const int rr = e / (kOutPad - kOut), c = kOut + (e - rr * (kOutPad - kOut));
-        a.dZ[(size_t)(r0 + rr) * kOutPad + c] = (__bf16)0.f;
-    }
-    red[t] = lsum;
-    __syncthreads();
-    // transposed rows: kOutPad columns x kLossRows rows in 8-element chunks
-    for (int e = t; e < kOutPad * (kLossRows / 8); e += 256) {
-        const int c = e / (kLossRows / 8), k8 = (e - c * (kLossRows / 8)) * 8;
-        bf16x8 v;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = (__bf16)(c < kOut ? sD[c][k8 + u] : 0.f);
-        *reinterpret_cast<bf16x8*>(a.dZt + (size_t)c * a.Bp + r0 + k8) = v;
-    }
-    if (t < kOutPad) {
-        float cs = 0.f;
-        if (t < kOut)
-            for (int rr = 0; rr < kLossRows; ++rr) cs += sD[t][rr];
-        a.dbpart[(size_t)blockIdx.x * kOutPad + t] = cs;
-    }
-    for (int st = 128; st > 0; st >>= 1) {
-        if (t < st) red[t] += red[t + st];
-        __syncthreads();
-    }
-    if (t == 0) a.lpart[blockIdx.x] = red[0];
-}
-
-hipError_t launch_loss(const LossArgs& a, hipStream_t st)
-{
-    if (a.Bp % kLossRows) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(loss_kernel, dim3(a.Bp / kLossRows), dim3(256), 0, st, a);
-    return hipGetLastError();
-}
-
-int loss_rows_per_block() { return kLossRows; }
 
 // ---------------------------------------------------------------------------------
 // Parameter pass: the fixed-order gradient reduction, Adam, and the BF16 shadows, in one
@@ -642,12 +632,6 @@ __global__ __launch_bounds__(256) void param_pass_kernel(ReduceArgs r, AdamArgs 
                     if constexpr (MODE == PASS_ADAM)
                         gr[h] = a.update ? *reinterpret_cast<const f32x4*>(a.G + p) : f32x4{0.f, 0.f, 0.f, 0.f};
                     w = adam4(a, p, gr[h]);
-                    if (a.Wn[l]) {
-                        bf16x4 wb;
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) wb[u] = (__bf16)w[u];
-                        *reinterpret_cast<bf16x4*>(a.Wn[l] + (size_t)i * fop + o) = wb;
-                    }
                 }
             }
             if constexpr (MODE != PASS_REDUCE) {
@@ -660,6 +644,13 @@ __global__ __launch_bounds__(256) void param_pass_kernel(ReduceArgs r, AdamArgs 
             const int row = t >> 2, c = t & 3;  // 64 rows of W^T, 4 pieces of 8 each
             *reinterpret_cast<bf16x8*>(a.Wt[l] + frag_offset(o0 + row, i0 + 8 * c, fip)) =
                 *reinterpret_cast<const bf16x8*>(&sT[row][8 * c]);
+            if (a.Wn[l]) {  // 32 rows of W, 8 pieces of 8 each: a wave's stores 1 KiB in a row
+                const int i = (t & 15) + 16 * (t >> 7), k8 = 8 * ((t >> 4) & 7);
+                bf16x8 v;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = sT[k8 + u][i];
+                *reinterpret_cast<bf16x8*>(a.Wn[l] + frag_offset(i0 + i, o0 + k8, fop)) = v;
+            }
         }
         return;
     }

@@ -1,5 +1,5 @@
-// Host-side launch interface of the proposal-network kernels (BF16 MFMA GEMMs with
-// fused epilogues, loss, gradient reduction, Adam, feature and head kernels).
+// Host-side launch interface of the proposal-network kernels (the pass over the network,
+// weight gradients, gradient reduction, Adam, feature and head kernels).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -8,18 +8,17 @@ namespace mlp {
 
 constexpr int kLayers = 5;
 constexpr int kIn = 40, kInPad = 64, kHidden = 512, kOut = 144, kOutPad = 192, kKnots = 6;
-constexpr int kGemmBK = 64;  // reduction tile; every K handed to a GEMM is a multiple of it
-constexpr int kMaxSplits = 8;  // most batch splits of a weight-gradient product
+constexpr int kGemmBK = 64;  // reduction tile of the weight gradients; every K is a multiple of it
+constexpr int kMaxSplits = 4;  // most batch splits of a weight-gradient product
 
-enum Epilogue {
-    EPI_HIDDEN = 0,  // z = acc + b -> Z (fp32, optional), silu(z) -> H (bf16) and H^T (bf16, optional)
-    EPI_OUT = 1,     // acc + b -> C (fp32) for rows < m_store, columns < n_store
-    EPI_DACT = 2,    // dz = acc * silu'(Zp) -> H (bf16), H^T (bf16); per-M-tile column sums of dz
-    EPI_SPLITK = 3   // acc -> C + blockIdx.z * c_split_stride (fp32 partial of a split reduction)
-};
+// What a product's launch does with its sums.  The weight gradients are the one product left
+// that is launched by itself; the others are steps of the pass over the network (launch_prep)
+// and launch_gemm refuses them.
+enum Epilogue { EPI_HIDDEN = 0, EPI_OUT = 1, EPI_DACT = 2, EPI_SPLITK = 3 };
 
-// C[m][n] = sum_k A[m][k] B[n][k] over k in [z K, (z+1) K) for split z; A and B bf16,
-// row strides lda, ldb (elements).  M, N multiples of the tile; K a multiple of 64.
+// C[m][n] = sum_k A[m][k] B[n][k] over k in [z K, (z+1) K) for split z; A and B bf16 in
+// groups of 16 columns in fragment order (batch_offset), lda = ldb columns, C + z * c_split_stride fp32 partials.  M, N, K
+// multiples of 64.  The fields from bias on belong to the refused epilogues.
 struct GemmArgs {
     const __bf16* A;
     const __bf16* B;
@@ -28,6 +27,7 @@ struct GemmArgs {
     float* C;
     int ldc;
     long c_split_stride;
+    const GemmArgs* next;  // a further product of the same launch, or null
     const float* bias;
     __bf16* H;
     int ldh;
@@ -35,66 +35,59 @@ struct GemmArgs {
     int ldht;
     const float* Zp;
     int ldz;
-    float* colpart;  // [M / BM][N]
+    float* colpart;
     int m_store, n_store;
 };
-
-// Tile choice: the largest tile that still gives at least 1024 workgroups (4 per CU).
-// One 256-thread workgroup per CU leaves a single wave per SIMD and too few memory
-// requests in flight for the epilogue's output stream; at batch 4096 every product here
-// takes 64 x 64 tiles (measured: 164 us per training step against 186 us with 128 x 64).
-constexpr long kMinBlocks = 1024;
-inline bool use_wide(int M, int N, int splits)
-{
-    return M % 128 == 0 && N % 128 == 0 && (long)(M / 128) * (N / 128) * splits >= kMinBlocks;
-}
-// the M-tile height used (for the column-sum partial count), or 0 on a shape error
-inline int gemm_tile_m(int M, int N, int splits)
-{
-    if (M <= 0 || N <= 0 || M % 64 || N % 64) return 0;
-    if (use_wide(M, N, splits)) return 128;
-    if (M % 128 == 0 && (long)(M / 128) * (N / 64) * splits >= kMinBlocks) return 128;
-    return 64;
-}
+// the tile height of a product, or 0 on a shape error
+inline int gemm_tile_m(int M, int N, int) { return M <= 0 || N <= 0 || M % 64 || N % 64 ? 0 : 64; }
+// the products of the list g, g.next, ... (at most kLayers), all in `splits` splits
 hipError_t launch_gemm(int epi, const GemmArgs& g, int splits, hipStream_t st);
 
-// The network of a fused forward pass: W^T [fop x fip] and bias of every layer, the output
-// rows (B x 144).
-struct NetArgs {
-    const __bf16* Wt[kLayers];
-    const float* bias[kLayers];
-    float* out;  // null: no forward pass
+// The Gaussian NLL of the output against standardised targets, a part of the pass over the
+// network: rows idx[r] of Y (stride 72), and what it leaves (dZt only in a training step).
+struct LossArgs {
+    const float* out;  // not used: the output of the same pass
+    const float* Y;
+    const int* idx;
+    int B, Bp;
+    const float* omean;
+    const float* ostd;
+    __bf16* dZ;     // not used: stays on the chip
+    __bf16* dZt;    // [192 x Bp]
+    float* dbpart;  // [Bp / kNetRows][192]
+    float* lpart;   // [Bp / kNetRows]
 };
 
-// raw features (rows idx[r] of X, stride 40) -> standardised bf16 X0 [Bp x 64] and X0^T
-// [64 x Bp]; with net.out set the whole forward pass instead (X0 and X0^T are not written)
+// A pass over the network: the raw features (rows idx[r] of X, stride 40) standardised and
+// taken through every layer; then, by mode, the output rows (NET_FORWARD: B x 144), or the
+// Gaussian NLL against the standardised rows of Y (NET_LOSS: a partial for each kNetRows of the
+// Bp rows), or that and the backward pass up to the weight gradients (NET_TRAIN: X0, H of the
+// hidden layers and dz of every layer in the order of launch_gemm's operands, and
+// the column sums of dz of each kNetRows rows).
+enum NetMode { NET_FORWARD = 0, NET_LOSS = 1, NET_TRAIN = 2 };
+constexpr int kNetRows = 16;  // rows of a workgroup: the matrix instruction's height
+struct NetArgs {
+    int mode;
+    const __bf16* Wt[kLayers];  // W^T [fop x fip] in fragment order
+    const __bf16* Wn[kLayers];  // W [fip x fop] in fragment order (layers >= 1)
+    const float* bias[kLayers];
+    float* out;
+    LossArgs loss;              // NET_LOSS, NET_TRAIN
+    __bf16* Ht[kLayers - 1];    // [512 x Bp] of the hidden layers
+    __bf16* dZt[kLayers - 1];   // [512 x Bp] of the hidden layers
+    float* bpart[kLayers - 1];  // [Bp / kNetRows][512] of the hidden layers
+};
 struct PrepArgs {
     const float* X;
     const int* idx;
     int B, Bp;
     const float* mean;
     const float* std;
-    __bf16* X0;
-    __bf16* X0t;
+    __bf16* X0;   // not used: stays on the chip
+    __bf16* X0t;  // [64 x Bp]
     NetArgs net;
 };
 hipError_t launch_prep(const PrepArgs& a, hipStream_t st);
-
-// Gaussian NLL of out [Bp x 144] against standardised targets; dz of the last layer
-struct LossArgs {
-    const float* out;
-    const float* Y;
-    const int* idx;
-    int B, Bp;
-    const float* omean;
-    const float* ostd;
-    __bf16* dZ;     // [Bp x 192]
-    __bf16* dZt;    // [192 x Bp]
-    float* dbpart;  // [Bp / loss_rows_per_block()][192]
-    float* lpart;   // [Bp / loss_rows_per_block()]
-};
-hipError_t launch_loss(const LossArgs& a, hipStream_t st);
-int loss_rows_per_block();  // rows of one loss workgroup (Bp must be a multiple); partial rows = Bp / this
 
 struct LayerGeom {
     int off[kLayers + 1];  // flat parameter offsets (W then b per layer)
@@ -115,8 +108,8 @@ struct ReduceArgs {
 };
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t st);
 
-// Adam (update = 1) or shadow refresh only (update = 0); bf16 shadows W^T (fop x fip, in
-// fragment order) and W [fip x fop] (layers >= 1) rewritten from the FP32 master weights
+// Adam (update = 1) or shadow refresh only (update = 0); bf16 shadows W^T (fop x fip) and W
+// (fip x fop, layers >= 1), both in fragment order, rewritten from the FP32 master weights
 struct AdamArgs {
     LayerGeom g;
     float* P;

@@ -27,9 +27,8 @@ struct mppi_policy {
     size_t ws_bytes = 0;
     hipStream_t stream = nullptr;
     LayerGeom geom{};
-    size_t o_P, o_m, o_v, o_G, o_Wt[kLayers], o_Wn[kLayers], o_norm, o_X0, o_X0t;
-    size_t o_Z[kLayers - 1], o_H[kLayers - 1], o_Ht[kLayers - 1];
-    size_t o_out, o_dZ[2], o_dZt[2], o_wpart[kLayers], o_bpart[kLayers], o_lpart, o_loss, o_feat, o_out1;
+    size_t o_P, o_m, o_v, o_G, o_Wt[kLayers], o_Wn[kLayers], o_norm, o_X0t;
+    size_t o_Ht[kLayers - 1], o_dZt[kLayers], o_out, o_wpart[kLayers], o_bpart[kLayers], o_lpart, o_loss, o_feat, o_out1;
     size_t shadow_begin, shadow_end, total;
     std::string err;
 };
@@ -70,7 +69,7 @@ int pad64(int b) { return (b + 63) / 64 * 64; }
 int batch_splits(int bp)
 {
     int s = kMaxSplits;
-    while (s > 1 && bp % (64 * s)) s >>= 1;
+    while (s > 1 && bp % (64 * s)) --s;
     return s;
 }
 
@@ -101,23 +100,14 @@ void layout(mppi_policy* p)
     for (int l = 0; l < kLayers; ++l) p->o_Wn[l] = l ? take(2ull * kFip[l] * kFop[l]) : 0;
     p->shadow_end = o;
     p->o_norm = take(4ull * 224);
-    p->o_X0 = take(2ull * bp * kInPad);
     p->o_X0t = take(2ull * bp * kInPad);
-    for (int l = 0; l < kLayers - 1; ++l) {
-        p->o_Z[l] = take(4ull * bp * kHidden);
-        p->o_H[l] = take(2ull * bp * kHidden);
-        p->o_Ht[l] = take(2ull * bp * kHidden);
-    }
+    for (int l = 0; l < kLayers - 1; ++l) p->o_Ht[l] = take(2ull * bp * kHidden);
+    for (int l = 0; l < kLayers; ++l) p->o_dZt[l] = take(2ull * bp * kFop[l]);
     p->o_out = take(4ull * bp * kOut);
-    for (int i = 0; i < 2; ++i) {
-        p->o_dZ[i] = take(2ull * bp * kHidden);
-        p->o_dZt[i] = take(2ull * bp * kHidden);
-    }
     for (int l = 0; l < kLayers; ++l) p->o_wpart[l] = take(4ull * kMaxSplits * kFip[l] * kFop[l]);
-    // column-sum partials: at most one row per 32 batch rows (loss workgroups; the
-    // input-gradient GEMM tiles are 64 or 128 rows)
-    for (int l = 0; l < kLayers; ++l) p->o_bpart[l] = take(4ull * (bp / 32) * kFop[l]);
-    p->o_lpart = take(4ull * (bp / 32));
+    // column-sum and loss partials: one row for each row block of the pass over the network
+    for (int l = 0; l < kLayers; ++l) p->o_bpart[l] = take(4ull * (bp / kNetRows) * kFop[l]);
+    p->o_lpart = take(4ull * (bp / kNetRows));
     p->o_loss = take(4ull * 4);
     p->o_feat = take(4ull * kIn);
     p->o_out1 = take(4ull * kOut);
@@ -144,117 +134,85 @@ mppi_status refresh_shadows(mppi_policy* p, hipStream_t st)
     return phip(p, launch_adam(a, st), "shadow refresh launch");
 }
 
-// forward over rows of d_in (idx or identity): fills Z, H, H^T of the hidden layers and
-// the output (d_out rows < B, stride 144, or the internal output buffer)
-mppi_status forward(mppi_policy* p, const float* d_in, const int* d_idx, int B, float* d_out, bool keep,
-                    hipStream_t st)
+// a pass over the network on rows of d_in (idx or identity), for the output rows d_out
+// (B x 144); pass_target makes it the loss or a training step
+PrepArgs pass_args(mppi_policy* p, const float* d_in, const int* d_idx, int B, float* d_out)
 {
-    const int bp = pad64(B);
-    PrepArgs pa{d_in, d_idx, B, bp, at<float>(p, p->o_norm), at<float>(p, p->o_norm) + 40,
-                at<__bf16>(p, p->o_X0), at<__bf16>(p, p->o_X0t), {}};
-    mppi_status s;
-    const float* P = at<float>(p, p->o_P);
-    // Nothing but the output is wanted: the whole pass in one launch, in which a workgroup writes
-    // its output rows while others still read their inputs; an output over the input therefore
-    // takes the launches per layer, which have read all of it first.  (With indices the output is
-    // the workspace's own.)
-    const uintptr_t in0 = reinterpret_cast<uintptr_t>(d_in), out0 = reinterpret_cast<uintptr_t>(d_out);
-    const bool apart = d_idx || in0 + 4ull * B * kIn <= out0 || out0 + 4ull * B * kOut <= in0;
-    if (!keep && apart) {
-        for (int l = 0; l < kLayers; ++l) {
-            pa.net.Wt[l] = at<__bf16>(p, p->o_Wt[l]);
-            pa.net.bias[l] = P + p->geom.off[l] + kFi[l] * kFo[l];
-        }
-        pa.net.out = d_out;
-        return phip(p, launch_prep(pa, st), "forward launch");
-    }
-    if ((s = phip(p, launch_prep(pa, st), "input launch"))) return s;
+    PrepArgs a{};
+    a.X = d_in;
+    a.idx = d_idx;
+    a.B = B;
+    a.Bp = pad64(B);
+    a.mean = at<float>(p, p->o_norm);
+    a.std = at<float>(p, p->o_norm) + 40;
+    a.X0 = a.X0t = at<__bf16>(p, p->o_X0t);
     for (int l = 0; l < kLayers; ++l) {
-        GemmArgs g{};
-        g.A = l ? at<__bf16>(p, p->o_H[l - 1]) : at<__bf16>(p, p->o_X0);
-        g.lda = kFip[l];
-        g.B = at<__bf16>(p, p->o_Wt[l]);
-        g.ldb = kFip[l];
-        g.M = bp;
-        g.N = kFop[l];
-        g.K = kFip[l];
-        g.bias = P + p->geom.off[l] + kFi[l] * kFo[l];
-        if (l < kLayers - 1) {
-            g.C = keep ? at<float>(p, p->o_Z[l]) : nullptr;
-            g.ldc = kHidden;
-            g.H = at<__bf16>(p, p->o_H[l]);
-            g.ldh = kHidden;
-            g.Ht = keep ? at<__bf16>(p, p->o_Ht[l]) : nullptr;
-            g.ldht = bp;
-            if ((s = phip(p, launch_gemm(EPI_HIDDEN, g, 1, st), "forward launch"))) return s;
-        } else {
-            g.C = d_out;
-            g.ldc = kOut;
-            g.m_store = B;
-            g.n_store = kOut;
-            if ((s = phip(p, launch_gemm(EPI_OUT, g, 1, st), "output launch"))) return s;
-        }
+        a.net.Wt[l] = at<__bf16>(p, p->o_Wt[l]);
+        a.net.Wn[l] = l ? at<__bf16>(p, p->o_Wn[l]) : nullptr;
+        a.net.bias[l] = at<float>(p, p->o_P) + p->geom.off[l] + kFi[l] * kFo[l];
     }
-    return MPPI_OK;
+    a.net.mode = NET_FORWARD;
+    a.net.out = d_out;
+    return a;
+}
+
+void pass_target(mppi_policy* p, const float* d_target, NetMode mode, PrepArgs& a)
+{
+    const float* nrm = at<float>(p, p->o_norm);
+    a.net.mode = mode;
+    a.net.loss = LossArgs{nullptr, d_target, a.idx, a.B, a.Bp, nrm + 80, nrm + 152, nullptr,
+                          at<__bf16>(p, p->o_dZt[kLayers - 1]), at<float>(p, p->o_bpart[kLayers - 1]),
+                          at<float>(p, p->o_lpart)};
+    for (int l = 0; l < kLayers - 1; ++l) {
+        a.net.Ht[l] = at<__bf16>(p, p->o_Ht[l]);
+        a.net.dZt[l] = at<__bf16>(p, p->o_dZt[l]);
+        a.net.bpart[l] = at<float>(p, p->o_bpart[l]);
+    }
+}
+
+mppi_status forward(mppi_policy* p, const float* d_in, int B, float* d_out, hipStream_t st)
+{
+    // a workgroup writes its output rows while others still read their inputs: an output over
+    // the input goes by way of the workspace
+    const uintptr_t in0 = reinterpret_cast<uintptr_t>(d_in), out0 = reinterpret_cast<uintptr_t>(d_out);
+    const bool apart = in0 + 4ull * B * kIn <= out0 || out0 + 4ull * B * kOut <= in0;
+    float* out = apart ? d_out : at<float>(p, p->o_out);
+    mppi_status s = phip(p, launch_prep(pass_args(p, d_in, nullptr, B, out), st), "forward launch");
+    if (s || apart) return s;
+    return phip(p, hipMemcpyAsync(d_out, out, 4ull * B * kOut, hipMemcpyDeviceToDevice, st), "copy output");
 }
 
 // forward, loss and backward products; ra receives the partial-sum layout of the gradient
 mppi_status backward(mppi_policy* p, const float* d_in, const float* d_target, const int* d_idx, int B,
                      ReduceArgs& ra, hipStream_t st)
 {
-    const int bp = pad64(B);
+    const int bp = pad64(B), S = batch_splits(bp);
     mppi_status s;
-    float* out = at<float>(p, p->o_out);
-    if ((s = forward(p, d_in, d_idx, B, out, true, st))) return s;
-    const float* nrm = at<float>(p, p->o_norm);
-    LossArgs la{out, d_target, d_idx, B, bp, nrm + 80, nrm + 152, at<__bf16>(p, p->o_dZ[0]),
-                at<__bf16>(p, p->o_dZt[0]), at<float>(p, p->o_bpart[kLayers - 1]), at<float>(p, p->o_lpart)};
-    if ((s = phip(p, launch_loss(la, st), "loss launch"))) return s;
+    PrepArgs pa = pass_args(p, d_in, d_idx, B, nullptr);
+    pass_target(p, d_target, NET_TRAIN, pa);
+    if ((s = phip(p, launch_prep(pa, st), "network launch"))) return s;
     ra = ReduceArgs{};
     ra.g = p->geom;
-    ra.T[kLayers - 1] = bp / loss_rows_per_block();
-    const int S = batch_splits(bp);
-    int cur = 0;
-    for (int l = kLayers - 1; l >= 0; --l) {
-        GemmArgs w{};
-        w.A = l ? at<__bf16>(p, p->o_Ht[l - 1]) : at<__bf16>(p, p->o_X0t);
-        w.lda = bp;
-        w.B = at<__bf16>(p, p->o_dZt[cur]);
-        w.ldb = bp;
-        w.M = kFip[l];
-        w.N = kFop[l];
-        w.K = bp / S;
-        w.C = at<float>(p, p->o_wpart[l]);
-        w.ldc = kFop[l];
-        w.c_split_stride = (long)kFip[l] * kFop[l];
-        if ((s = phip(p, launch_gemm(EPI_SPLITK, w, S, st), "weight-gradient launch"))) return s;
-        ra.wpart[l] = w.C;
+    GemmArgs w[kLayers]{};
+    for (int l = 0; l < kLayers; ++l) {
+        w[l].A = l ? at<__bf16>(p, p->o_Ht[l - 1]) : at<__bf16>(p, p->o_X0t);
+        w[l].B = at<__bf16>(p, p->o_dZt[l]);
+        w[l].lda = w[l].ldb = bp;
+        w[l].M = kFip[l];
+        w[l].N = kFop[l];
+        w[l].K = bp / S;
+        w[l].C = at<float>(p, p->o_wpart[l]);
+        w[l].ldc = kFop[l];
+        w[l].c_split_stride = (long)kFip[l] * kFop[l];
+        w[l].next = l + 1 < kLayers ? &w[l + 1] : nullptr;
+        ra.wpart[l] = w[l].C;
         ra.S[l] = S;
         ra.bpart[l] = at<float>(p, p->o_bpart[l]);
-        if (l == 0) break;
-        GemmArgs d{};
-        d.A = at<__bf16>(p, p->o_dZ[cur]);
-        d.lda = kFop[l];
-        d.B = at<__bf16>(p, p->o_Wn[l]);
-        d.ldb = kFop[l];
-        d.M = bp;
-        d.N = kFip[l];
-        d.K = kFop[l];
-        d.Zp = at<float>(p, p->o_Z[l - 1]);
-        d.ldz = kHidden;
-        d.H = at<__bf16>(p, p->o_dZ[cur ^ 1]);
-        d.ldh = kHidden;
-        d.Ht = at<__bf16>(p, p->o_dZt[cur ^ 1]);
-        d.ldht = bp;
-        d.colpart = at<float>(p, p->o_bpart[l - 1]);
-        const int bm = gemm_tile_m(d.M, d.N, 1);
-        if (!bm) return pfail(p, MPPI_EINVAL, "bad backward shape");
-        ra.T[l - 1] = bp / bm;
-        if ((s = phip(p, launch_gemm(EPI_DACT, d, 1, st), "input-gradient launch"))) return s;
-        cur ^= 1;
+        ra.T[l] = bp / kNetRows;
     }
+    if ((s = phip(p, launch_gemm(EPI_SPLITK, w[0], S, st), "weight-gradient launch"))) return s;
     ra.lpart = at<float>(p, p->o_lpart);
-    ra.nl = bp / loss_rows_per_block();
+    ra.nl = bp / kNetRows;
     ra.lscale = (float)(1.0 / ((double)B * 72.0));
     return MPPI_OK;
 }
@@ -333,7 +291,7 @@ mppi_status policy_infer(mppi_policy* p, const float* d_x, const float* d_cmd_or
     float* feat = at<float>(p, p->o_feat);
     float* out = at<float>(p, p->o_out1);
     if ((s = phip(p, prop::launch_features(d_x, d_cmd_origin, feat, st), "features launch"))) return s;
-    if ((s = forward(p, feat, nullptr, 1, out, false, st))) return s;
+    if ((s = forward(p, feat, 1, out, st))) return s;
     HeadArgs h{};
     h.out = out;
     h.omean = at<float>(p, p->o_norm) + 80;
@@ -354,7 +312,7 @@ mppi_status policy_forward_rows(mppi_policy* p, const float* d_in, int B, float*
     mppi_status s;
     if ((s = need_bound(p))) return s;
     if ((s = check_batch(p, B))) return s;
-    return forward(p, d_in, nullptr, B, d_out, false, st);
+    return forward(p, d_in, B, d_out, st);
 }
 
 const void* policy_workspace(const mppi_policy* p) { return p ? p->ws : nullptr; }
@@ -532,7 +490,7 @@ mppi_status mppi_policy_forward(mppi_policy* p, const float* d_in, int B, float*
     if ((s = need_bound(p))) return s;
     if (!d_in || !d_out) return pfail(p, MPPI_EINVAL, "null input or output");
     if ((s = check_batch(p, B))) return s;
-    return forward(p, d_in, nullptr, B, d_out, false, p->stream);
+    return forward(p, d_in, B, d_out, p->stream);
 }
 
 mppi_status mppi_policy_grad(mppi_policy* p, const float* d_in, const float* d_target, const int* d_index, int B,
@@ -552,16 +510,12 @@ mppi_status mppi_policy_nll(mppi_policy* p, const float* d_in, const float* d_ta
     if ((s = need_bound(p))) return s;
     if (!d_in || !d_target || !d_loss) return pfail(p, MPPI_EINVAL, "null input, target or loss");
     if ((s = check_batch(p, B))) return s;
-    const int bp = pad64(B);
-    float* out = at<float>(p, p->o_out);
-    if ((s = forward(p, d_in, d_index, B, out, false, p->stream))) return s;
-    const float* nrm = at<float>(p, p->o_norm);
-    // the loss kernel of a gradient step; its error outputs are scratch here
-    LossArgs la{out, d_target, d_index, B, bp, nrm + 80, nrm + 152, at<__bf16>(p, p->o_dZ[0]),
-                at<__bf16>(p, p->o_dZt[0]), at<float>(p, p->o_bpart[kLayers - 1]), at<float>(p, p->o_lpart)};
-    if ((s = phip(p, launch_loss(la, p->stream), "loss launch"))) return s;
-    return phip(p, launch_loss_sum(at<float>(p, p->o_lpart), bp / loss_rows_per_block(),
-                                   (float)(1.0 / ((double)B * 72.0)), d_loss, p->stream),
+    // the pass of a gradient step up to its loss partials
+    PrepArgs pa = pass_args(p, d_in, d_index, B, nullptr);
+    pass_target(p, d_target, NET_LOSS, pa);
+    if ((s = phip(p, launch_prep(pa, p->stream), "network launch"))) return s;
+    return phip(p, launch_loss_sum(pa.net.loss.lpart, pa.Bp / kNetRows, (float)(1.0 / ((double)B * 72.0)), d_loss,
+                                   p->stream),
                 "loss sum launch");
 }
 
