@@ -136,6 +136,87 @@ __device__ __forceinline__ V3<R> mul_ordered(const M33<R>& A, V3<R> a)
               R(fma(A.m[8], a.z, fma(A.m[7], a.y, A.m[6] * a.x))));
 }
 
+// Vector operations with the zeros of ex = (1, 0, 0), ey = (0, cos, sin) and the hip (x, y, 0)
+// left out, which the compiler has to multiply by (0 times an infinity is not 0): about 90 of a
+// step's 1500 instructions and more.  Every product and sum is rounded as in the full form, whose
+// order is stated: fma of the first product on the second, sums from the left, and a product whose
+// other terms were zeros by itself (`lone`, never fused into a sum).  Full form / here, MI355X:
+// climbing K = 1001, H = 47, mixed, 212 / 206 us; pushing K = 4096, H = 60, FP32, whole control
+// step, 274 / 264; terrain walk with a proposal, K = 1024 + 256, H = 50, FP32, 221 / 214.
+template <typename R>
+__device__ __forceinline__ R lone(R a, R b)
+{
+#pragma clang fp contract(off)
+    return a * b;
+}
+template <typename R>
+__device__ __forceinline__ R mad(R a, R b, R c)
+{
+    return R(fma(a, b, c));
+}
+template <typename R>
+__device__ __forceinline__ V3<R> lonev(R a, V3<R> b)
+{
+    return v3(lone(a, b.x), lone(a, b.y), lone(a, b.z));
+}
+template <typename R>
+__device__ __forceinline__ V3<R> madv(R a, V3<R> b, V3<R> c)
+{
+    return v3(mad(a, b.x, c.x), mad(a, b.y, c.y), mad(a, b.z, c.z));
+}
+template <typename R>
+__device__ __forceinline__ V3<R> crossf(V3<R> a, V3<R> b)
+{
+    return v3(mad(a.y, b.z, -lone(a.z, b.y)), mad(a.z, b.x, -lone(a.x, b.z)), mad(a.x, b.y, -lone(a.y, b.x)));
+}
+template <typename R>
+__device__ __forceinline__ R dotf(V3<R> a, V3<R> b)
+{
+    return mad(a.z, b.z, mad(a.x, b.x, lone(a.y, b.y)));
+}
+template <typename R>
+__device__ __forceinline__ V3<R> ex_cross(V3<R> a)  // ex x a
+{
+    return v3(R(0), -a.z, a.y);
+}
+template <typename R>
+__device__ __forceinline__ V3<R> x0_cross(V3<R> e, V3<R> a)  // e x a, e.x = 0
+{
+    return v3(mad(e.y, a.z, -lone(e.z, a.y)), lone(e.z, a.x), -lone(e.y, a.x));
+}
+template <typename R>
+__device__ __forceinline__ V3<R> cross_x0(V3<R> a, V3<R> e)  // a x e, e.x = 0
+{
+    return v3(mad(a.y, e.z, -lone(a.z, e.y)), -lone(a.x, e.z), lone(a.x, e.y));
+}
+template <typename R>
+__device__ __forceinline__ V3<R> cross_z0(V3<R> a, V3<R> h)  // a x h, h.z = 0
+{
+    return v3(-lone(a.z, h.y), lone(a.z, h.x), mad(a.x, h.y, -lone(a.y, h.x)));
+}
+template <typename R>
+__device__ __forceinline__ V3<R> hip_cross(V3<R> h, V3<R> e)  // h x e, h.z = e.x = 0
+{
+    return v3(lone(h.y, e.z), -lone(h.x, e.z), lone(h.x, e.y));
+}
+template <typename R>
+__device__ __forceinline__ R dot_x0(V3<R> e, V3<R> a)  // e . a, e.x = 0
+{
+    return mad(e.z, a.z, lone(e.y, a.y));
+}
+// (I - d d^T) applied to ex and to e (e.x = 0): rod_I without its factor
+template <typename R>
+__device__ __forceinline__ V3<R> rod_ex(V3<R> d)
+{
+    return v3(mad(-d.x, d.x, R(1)), -lone(d.x, d.y), -lone(d.x, d.z));
+}
+template <typename R>
+__device__ __forceinline__ V3<R> rod_x0(V3<R> d, V3<R> e)
+{
+    const R t = dot_x0(d, e);
+    return v3(-lone(t, d.x), mad(-t, d.y, e.y), mad(-t, d.z, e.z));
+}
+
 // a contact on the leg's calf with weight wgt (1: applied, 0: nothing added).  The contact
 // velocity and the law are evaluated in the geometry type R; the force and damping terms
 // on the trunk's base rows and on the leg's joint rows accumulate in the system type S.
@@ -146,7 +227,10 @@ __device__ __forceinline__ void leg_contact_w(const ModelT<R>& M, const LegGeo<R
 {
     const V3<R> ex = v3(R(1), R(0), R(0));
     const V3<R> ja = cross(ex, r - G.h), jf = cross(G.ey, r - G.h), jk = cross(G.ey, r - G.pk);
-    const V3<R> vc = vb + cross(w, r) + qd[0] * ja + qd[1] * jf + qd[2] * jk - vo;
+    V3<R> vc = vb + crossf(w, r);
+    vc.y = mad(qd[0], ja.y, vc.y);
+    vc.z = mad(qd[0], ja.z, vc.z);
+    vc = madv(qd[2], jk, madv(qd[1], jf, vc)) - vo;
     contact_law(M, delta, n, vc, F, eta);
     F = wgt * F;
     eta = wgt * eta;
@@ -158,24 +242,27 @@ __device__ __forceinline__ void leg_contact_w(const ModelT<R>& M, const LegGeo<R
     // into the operands
     const S de = dt * e;
     const V3<S> jv[3] = {cv<S>(ja), cv<S>(jf), cv<S>(jk)};
-    const S gj[3] = {dot(jv[0], ns), dot(jv[1], ns), dot(jv[2], ns)};
+    const S gj[3] = {dot_x0(jv[0], ns), dotf(jv[1], ns), dotf(jv[2], ns)};
     const S dg[3] = {dt * ce * gj[0], dt * ce * gj[1], dt * ce * gj[2]};
     const V3<S> gA = cross(rs, ns);
     const S g0[6] = {gA.x, gA.y, gA.z, ns.x, ns.y, ns.z};
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        const V3<S> rxj = cross(rs, jv[j]);
+        const V3<S> rxj = j ? crossf(rs, jv[j]) : cross_x0(rs, jv[j]);
         const S jb[6] = {rxj.x, rxj.y, rxj.z, jv[j].x, jv[j].y, jv[j].z};
 #pragma unroll
-        for (int i = 0; i < 6; ++i) L.C[j][i] += de * jb[i] + dg[j] * g0[i];
-        L.rl[j] += dt * dot(jv[j], Fs);
+        for (int i = 0; i < 6; ++i) {
+            const S t = lone(dg[j], g0[i]);
+            L.C[j][i] += j == 0 && i == 3 ? t : mad(de, jb[i], t);
+        }
+        L.rl[j] = mad(dt, j ? dotf(jv[j], Fs) : dot_x0(jv[j], Fs), L.rl[j]);
     }
-    L.A00 += de * dot(jv[0], jv[0]) + dg[0] * gj[0];
-    L.A01 += de * dot(jv[0], jv[1]) + dg[0] * gj[1];
-    L.A02 += de * dot(jv[0], jv[2]) + dg[0] * gj[2];
-    L.A11 += de * dot(jv[1], jv[1]) + dg[1] * gj[1];
-    L.A12 += de * dot(jv[1], jv[2]) + dg[1] * gj[2];
-    L.A22 += de * dot(jv[2], jv[2]) + dg[2] * gj[2];
+    L.A00 += mad(de, dot_x0(jv[0], jv[0]), lone(dg[0], gj[0]));
+    L.A01 += mad(de, dot_x0(jv[0], jv[1]), lone(dg[0], gj[1]));
+    L.A02 += mad(de, dot_x0(jv[0], jv[2]), lone(dg[0], gj[2]));
+    L.A11 += mad(de, dotf(jv[1], jv[1]), lone(dg[1], gj[1]));
+    L.A12 += mad(de, dotf(jv[1], jv[2]), lone(dg[1], gj[2]));
+    L.A22 += mad(de, dotf(jv[2], jv[2]), lone(dg[2], gj[2]));
 }
 
 // contact terms of a force F at body-frame point r with normal n and secant eta (all in
@@ -261,43 +348,46 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
     }
     LegSys<S> L;
     {
-        const V3<S> ua1 = cross(ex, c1 - h), ua2 = cross(ex, c2 - h);
-        const V3<S> uf1 = cross(ey, c1 - h), uf2 = cross(ey, c2 - h);
-        const V3<S> uk2 = cross(ey, c2 - pk);
-        const V3<S> Pa = MS.m1 * ua1 + MS.m2 * ua2;
-        const V3<S> La =
-            MS.m1 * cross(c1, ua1) + MS.m2 * cross(c2, ua2) + rod_I(MS.k1, d1, ex) + rod_I(MS.k2, d2, ex);
-        const V3<S> Pf = MS.m1 * uf1 + MS.m2 * uf2;
-        const V3<S> Lf =
-            MS.m1 * cross(c1, uf1) + MS.m2 * cross(c2, uf2) + rod_I(MS.k1, d1, ey) + rod_I(MS.k2, d2, ey);
-        const V3<S> Pk = MS.m2 * uk2;
-        const V3<S> Lk = MS.m2 * cross(c2, uk2) + rod_I(MS.k2, d2, ey);
+        const V3<S> ua1 = ex_cross(c1 - h), ua2 = ex_cross(c2 - h);
+        const V3<S> uf1 = x0_cross(ey, c1 - h), uf2 = x0_cross(ey, c2 - h);
+        const V3<S> uk2 = x0_cross(ey, c2 - pk), z2 = rod_x0(d2, ey);
+        const V3<S> Pa = madv(MS.m1, ua1, lonev(MS.m2, ua2));
+        const V3<S> La = madv(MS.k2, rod_ex(d2), madv(MS.k1, rod_ex(d1), madv(MS.m1, cross_x0(c1, ua1),
+                                                                              lonev(MS.m2, cross_x0(c2, ua2)))));
+        const V3<S> Pf = madv(MS.m1, uf1, lonev(MS.m2, uf2));
+        const V3<S> Lf = madv(MS.k2, z2, madv(MS.k1, rod_x0(d1, ey), madv(MS.m1, crossf(c1, uf1),
+                                                                          lonev(MS.m2, crossf(c2, uf2)))));
+        const V3<S> Pk = lonev(MS.m2, uk2);
+        const V3<S> Lk = madv(MS.m2, crossf(c2, uk2), lonev(MS.k2, z2));
         const V3<S> Ls[3] = {La, Lf, Lk}, Ps[3] = {Pa, Pf, Pk};
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
             L.C[j][0] = Ls[j].x; L.C[j][1] = Ls[j].y; L.C[j][2] = Ls[j].z;
             L.C[j][3] = Ps[j].x; L.C[j][4] = Ps[j].y; L.C[j][5] = Ps[j].z;
         }
-        const V3<S> oxa_a = cross(h, ex), oxa_f = cross(h, ey), oxa_k = cross(pk, ey);
-        L.A00 = dot(ex, La) + dot(oxa_a, Pa);
-        L.A01 = dot(ex, Lf) + dot(oxa_a, Pf);
-        L.A02 = dot(ex, Lk) + dot(oxa_a, Pk);
-        L.A11 = dot(ey, Lf) + dot(oxa_f, Pf);
-        L.A12 = dot(ey, Lk) + dot(oxa_f, Pk);
-        L.A22 = dot(ey, Lk) + dot(oxa_k, Pk);
+        // ex . L + (h x ex) . P and ey . L + (o x ey) . P
+        const V3<S> oxa_f = hip_cross(h, ey), oxa_k = cross_x0(pk, ey);
+        L.A00 = La.x - lone(h.y, Pa.z);
+        L.A01 = Lf.x - lone(h.y, Pf.z);
+        L.A02 = Lk.x - lone(h.y, Pk.z);
+        L.A11 = dot_x0(ey, Lf) + dotf(oxa_f, Pf);
+        L.A12 = dot_x0(ey, Lk) + dotf(oxa_f, Pk);
+        L.A22 = dot_x0(ey, Lk) + dotf(oxa_k, Pk);
     }
 
     // ---- bias forces of the leg (zero generalized acceleration, gravity)
     S rb[6];
     {
-        const V3<S> w1 = ws + dqa * ex + dqf * ey;
-        const V3<S> al1 = dqa * cross(ws, ex) + dqf * cross(ws + dqa * ex, ey);
-        const V3<S> ah = cross(ws, cross(ws, h));
+        const V3<S> wa = v3(ws.x + dqa, ws.y, ws.z);
+        const V3<S> w1 = v3(wa.x, mad(dqf, ey.y, wa.y), mad(dqf, ey.z, wa.z));
+        const V3<S> we = cross_x0(wa, ey);
+        const V3<S> al1 = v3(lone(dqf, we.x), mad(dqa, ws.z, lone(dqf, we.y)), mad(dqa, -ws.y, lone(dqf, we.z)));
+        const V3<S> ah = crossf(ws, cross_z0(ws, h));
         const V3<S> r1 = c1 - h, rk = pk - h;
         const V3<S> ac1 = ah + cross(al1, r1) + cross(w1, cross(w1, r1));
         const V3<S> apk = ah + cross(al1, rk) + cross(w1, cross(w1, rk));
-        const V3<S> w2 = w1 + dqk * ey;
-        const V3<S> al2 = al1 + dqk * cross(w1, ey);
+        const V3<S> w2 = v3(w1.x, mad(dqk, ey.y, w1.y), mad(dqk, ey.z, w1.z));
+        const V3<S> al2 = madv(dqk, cross_x0(w1, ey), al1);
         const V3<S> r2 = c2 - pk;
         const V3<S> ac2 = apk + cross(al2, r2) + cross(w2, cross(w2, r2));
         const V3<S> F1 = MS.m1 * (ac1 - gbs), F2 = MS.m2 * (ac2 - gbs);
@@ -309,9 +399,9 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
         const V3<S> Fb = F1 + F2;
         rb[0] = -dt * Tb.x; rb[1] = -dt * Tb.y; rb[2] = -dt * Tb.z;
         rb[3] = -dt * Fb.x; rb[4] = -dt * Fb.y; rb[5] = -dt * Fb.z;
-        L.rl[0] = dt * (tau[0] - dot(ex, Th));
-        L.rl[1] = dt * (tau[1] - dot(ey, Th));
-        L.rl[2] = dt * (tau[2] - dot(ey, Tk));
+        L.rl[0] = dt * (tau[0] - Th.x);
+        L.rl[1] = dt * (tau[1] - dot_x0(ey, Th));
+        L.rl[2] = dt * (tau[2] - dot_x0(ey, Tk));
     }
     L.A00 += dt * kd; L.A11 += dt * kd; L.A22 += dt * kd;
 
@@ -501,8 +591,7 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
             sred[g] = a0;
             if (g < 12) {
                 sred[g + 16] = a1;
-                if constexpr (SCENE == 3)
-                if (g < 11) sred[28 + 16 + g] = b1;
+                if constexpr (SCENE == 3) sred[28 + 16 + g] = b1;  // the twelfth to a place that is not read
             }
         }
         __syncthreads();
@@ -996,8 +1085,7 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
         sred[g] = s0;
         if (g < 12) {
             sred[g + 16] = s1;
-            if constexpr (SCENE == 3)
-                if (g < 11) sred[28 + 16 + g] = b1;
+            if constexpr (SCENE == 3) sred[28 + 16 + g] = b1;  // the twelfth to a place that is not read
         }
     }
     __syncthreads();
