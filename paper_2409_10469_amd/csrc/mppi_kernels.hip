@@ -135,8 +135,10 @@ __device__ __forceinline__ void rollout_samples(typename ModelRef<R>::Ptr M, con
     const R dt = P.dt, kp = P.kp, kd = P.kd;
     R L = R(0);
     for (int k = 0; k < P.H; ++k) {
-        // all eight terms (those past the last knot are zero), so that the reads wait together
-        // instead of knot by knot
+        // all eight reads together instead of knot by knot; in FP64 all eight terms (those past
+        // the last knot are zero).  The FP32 sum keeps its conditions: as one block with the step
+        // the compiler orders the products of the terrain's interpolation differently, and a
+        // rollout in contact carries the last bit far.
         R u[3], bk[kMaxKnots];
 #pragma unroll
         for (int i = 0; i < kMaxKnots; ++i) bk[i] = sB[k * nk + min(i, nk - 1)];
@@ -144,7 +146,8 @@ __device__ __forceinline__ void rollout_samples(typename ModelRef<R>::Ptr M, con
         for (int j = 0; j < 3; ++j) {
             R s = R(0);
 #pragma unroll
-            for (int i = 0; i < kMaxKnots; ++i) s += bk[i] * th[j * kMaxKnots + i];
+            for (int i = 0; i < kMaxKnots; ++i)
+                if (sizeof(R) == 8 || i < nk) s += bk[i] * th[j * kMaxKnots + i];
             u[j] = s;
         }
         R tau2;
