@@ -96,14 +96,12 @@ __device__ __forceinline__ void m_sincos(float x, float* sn, float* cs)
     *sn = (q & 2) ? -s0 : s0;
     *cs = ((q + 1) & 2) ? -c0 : c0;
 }
-__device__ __forceinline__ void m_sincos(double x, double* s, double* c) { sincos(x, s, c); }
 
 // tanh(s) / s for s >= 0 (the friction law's secant factor).  FP32: below s = 1/2 its
 // Taylor series in s^2 through s^14 (coefficients 1, -1/3, 2/15, -17/315, 62/2835,
 // -1382/155925, 21844/6081075, -929569/638512875; the next term is under 1e-8), else
 // (1 - e^-2s) / ((1 + e^-2s) s), where e^-2s <= 0.37 keeps the difference well
 // conditioned; both are evaluated and one selected, so lanes do not diverge (about 3 ulp).
-// FP64: the device library's tanh, and the series' first two terms below 1e-4.
 __device__ __forceinline__ float tanh_ratio(float s)
 {
     const float s2 = s * s;
@@ -118,28 +116,19 @@ __device__ __forceinline__ float tanh_ratio(float s)
     const float big = (1.f - t) / ((1.f + t) * s);
     return s < 0.5f ? ser : big;
 }
-__device__ __forceinline__ double tanh_ratio(double s)
-{
-    return (s < 1e-4) ? 1.0 - s * s * (1.0 / 3.0) : tanh(s) / s;
-}
 __device__ __forceinline__ float m_log(float x) { return logf(x); }
 __device__ __forceinline__ double m_log(double x) { return log(x); }
 __device__ __forceinline__ void m_sincospi(float x, float* s, float* c) { sincospif(x, s, c); }
 __device__ __forceinline__ void m_sincospi(double x, double* s, double* c) { sincospi(x, s, c); }
 
-// sin(a)/a and cos(a) for the quaternion exponential.  FP32: one sine-cosine evaluation,
-// sin(a)/a from its series below a = 1e-2; FP64: the library's sin and cos.
+// sin(a)/a and cos(a) for the quaternion exponential: one sine-cosine evaluation, sin(a)/a
+// from its series below a = 1e-2.  (FP64: mppi_step64.h.)
 __device__ __forceinline__ void quat_exp(float a, float* sinc, float* c)
 {
     float s;
     m_sincos(a, &s, c);
     const float a2 = a * a;
     *sinc = (a < 1e-2f) ? 1.f - a2 * (1.f / 6.f) + a2 * a2 * (1.f / 120.f) : s / a;
-}
-__device__ __forceinline__ void quat_exp(double a, double* sinc, double* c)
-{
-    *sinc = (a > 0.0) ? sin(a) / a : 1.0;
-    *c = cos(a);
 }
 
 // ------------------------------------------------------------------------------

@@ -13,12 +13,12 @@
 //     corner g, lane g >= 8 box corner g - 8 (the quad kernel takes two of each per lane);
 //   * the two 6x6 solves of the pushing scene: even lanes solve the trunk's system, odd
 //     lanes the box's, from selected operands, and swap results with their neighbour.
-// The leg's kinematics, mass-matrix and bias terms, its foot contacts and the elimination
-// of its 3x3 block run in all four lanes of the leg (only lane 0's copy enters the
-// sums).  The trunk and box systems (Sec. III-A's dynamics step: (M + dt D) dv = dt f,
-// the legs eliminated first) are summed over the 16 lanes through LDS: every lane writes
-// its partial terms, lane g adds entries g, g + 16, ... of all 16 lanes in a fixed order,
-// and every lane reads the sums back.  The results do not depend on timing.
+// The leg's kinematics, mass-matrix and bias terms and its foot contacts run in all four
+// lanes of the leg; each lane eliminates two of the leg's columns.  The trunk and box systems
+// (Sec. III-A's dynamics step: (M + dt D) dv = dt f, the legs eliminated first) are summed over
+// the 16 lanes through LDS in a fixed order: one lane writes a leg's terms and each lane its
+// columns', or, while a wave has a rare contact, every lane all its terms.  The results do not
+// depend on timing.
 //
 // The step computes the same discretisation as the quad kernel in the same arithmetic
 // type R (the state is FP32 between steps); only summation orders differ.
@@ -239,6 +239,8 @@ __device__ __forceinline__ void leg_contact_w(const ModelT<R>& M, const LegGeo<R
                                               const R qd[3], R delta, V3<R> n, V3<R> r, V3<R> vo, S dt, R wgt, S* Q,
                                               S* rb, LegSys<S>& L, V3<R>& F, R& eta)
 {
+    // ja in full: with its zeros left out, FP32 contacts were rounded differently (the cause was
+    // not found)
     const V3<R> ex = v3(R(1), R(0), R(0));
     const V3<R> ja = cross(ex, r - G.h), jf = cross(G.ey, r - G.h), jk = cross(G.ey, r - G.pk);
     V3<R> vc = vb + crossf(w, r);
@@ -807,16 +809,15 @@ __device__ __forceinline__ void step16(const ModelT<R>& MR, const ModelT<S>& MS,
 //   * the leg is written in its own frame (mppi_step64.h), with divisions, square roots and
 //     elementary functions without branches;
 //   * lane `sub` of a leg eliminates two columns of the trunk's system, sub and sub + 4 (the
-//     fifth and sixth velocity, the right side, and a zero column), where step16 eliminates
-//     all seven in each of the four lanes; the back-substitution adds the four lanes' parts;
+//     fifth and sixth velocity, the right side, and a zero column); the back-substitution adds
+//     the four lanes' parts;
 //   * the leg's own terms and the eliminated parts go to the sum from where they are: one
-//     lane writes a leg's 28 values, each lane its two columns, so lane g adds 4 legs where
-//     step16 adds 16 lanes, most of them zeros;
+//     lane writes a leg's 28 values, each lane its two columns, so lane g adds 4 legs;
 //   * corner contacts of the trunk are rare (a fallen robot, the box against the trunk):
 //     their 16-lane sum runs only in steps in which some lane of the wave has one, and the
 //     tests of trunk against box only while their bounding spheres overlap;
 //   * in the pushing scene each lane reads the sums of the one body whose 6x6 system it solves.
-// Per call, step16 / here (MI355X): heightfield walk K = 1024, H = 50: 318 / 197 us; box push
+// Per call, step16 with all columns in every lane / here (MI355X): heightfield walk K = 1024, H = 50: 318 / 197 us; box push
 // K = 4096, H = 60: 560 / 343 us; flat walk K = 64, H = 25, whole control step: 135 / 96 us.
 // ------------------------------------------------------------------------------
 // the model in LDS through an offset (always zero) that the compiler takes to depend on the
