@@ -81,8 +81,9 @@ __device__ __forceinline__ size_t batch_offset(int n, int r, int N)
 // products run and the next k-tile on its way to the other half of the LDS.  What bounds it is
 // the way of the operands from memory, 34 MB for 4096 rows that other XCDs have just written:
 // 64 x 64 tiles with twice the LDS traffic took the same time.  For 4096 rows 20 us, in launches
-// for each layer 56 together; 4 splits, since 8 (the same 20 us) add 15 MB of partials to write
-// and to read back (parameter pass 12.4 us against 9.2).  dZ is the instruction's first operand, so a lane's four sums are consecutive
+// for each layer 56 together; 4 splits instead of 8 save 2 us of a training step (15 MB fewer
+// partials), but another order of the sums turns the first updates of parameters whose gradient
+// is nearly zero.  dZ is the instruction's first operand, so a lane's four sums are consecutive
 // columns of dW and leave as 16 bytes.  Where a matrix ends inside a tile (64 rows of the first
 // layer, 192 columns of the last) the panels past its end repeat the last one and are not stored.
 // ---------------------------------------------------------------------------------
@@ -201,7 +202,7 @@ hipError_t launch_gemm(int epi, const GemmArgs& g, int splits, hipStream_t st)
 // Launches per layer / here, us a pass: 1 row 29.3 / 18.6, 256 rows 29.4 / 20.0, 4096 rows 42.2
 // / 22.4, 16384 rows 104 / 78; with three policies in turn, whose weights together exceed an
 // XCD's L2, 256 rows 30.1 / 20.7.  A training step (three launches against sixteen): 64 rows
-// 93 / 52, 512 rows 106 / 54, 4096 rows 151 / 74, 16384 rows 420 / 251.  The loss alone: 4096
+// 93 / 53, 512 rows 106 / 58, 4096 rows 151 / 76, 16384 rows 420 / 247.  The loss alone: 4096
 // rows 52 / 25.
 // ---------------------------------------------------------------------------------
 constexpr int kNetThreads = 512, kNetLd = kHidden + 8, kOutLd = kOut + 4;

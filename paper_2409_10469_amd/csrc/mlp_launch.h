@@ -9,7 +9,7 @@ namespace mlp {
 constexpr int kLayers = 5;
 constexpr int kIn = 40, kInPad = 64, kHidden = 512, kOut = 144, kOutPad = 192, kKnots = 6;
 constexpr int kGemmBK = 64;  // reduction tile of the weight gradients; every K is a multiple of it
-constexpr int kMaxSplits = 4;  // most batch splits of a weight-gradient product
+constexpr int kMaxSplits = 8;  // most batch splits of a weight-gradient product
 
 // What a product's launch does with its sums.  The weight gradients are the one product left
 // that is launched by itself; the others are steps of the pass over the network (launch_prep)

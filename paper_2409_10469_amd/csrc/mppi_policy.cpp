@@ -69,7 +69,7 @@ int pad64(int b) { return (b + 63) / 64 * 64; }
 int batch_splits(int bp)
 {
     int s = kMaxSplits;
-    while (s > 1 && bp % (64 * s)) --s;
+    while (s > 1 && bp % (64 * s)) s >>= 1;
     return s;
 }
 

@@ -1,6 +1,6 @@
 """The policy's passes at the edges of their row blocks of 16 and where the launch changes
 (2048 rows): the forward pass with the output apart from the input and over it, the gradient and
-loss with 1 to 4 batch splits of the weight gradients.
+loss with one batch split of the weight gradients and with two.
 
 Tolerances: the network rounds the operands of its products to BF16 as the oracle does and sums
 in FP32 where the oracle sums in FP64; a sum near a rounding boundary can flip a BF16 value by
