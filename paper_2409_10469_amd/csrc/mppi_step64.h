@@ -103,10 +103,43 @@ __device__ __forceinline__ double rcp(double x)
 // sqrt of x >= 0, and 1/sqrt with 0 -> a large finite value
 __device__ __forceinline__ double rsq_pos(double x) { return rsq(m_max(x, 1e-300)); }
 
+// |x| from 2^40, the end of sincos64's range, up to the largest finite value, by its leading bits
+// (as numbers in a table the bounds would be a wait for memory at the head of a step; and a state
+// that is not finite, which stays so, takes no rare path)
+__device__ __forceinline__ bool is_far(double x)
+{
+    constexpr unsigned lo = 0x42700000u, inf = 0x7ff00000u;
+    return ((unsigned)__double2hiint(x) & 0x7fffffffu) - lo < inf - lo;
+}
+
+// An angle of the same sine and cosine as x, within 4, for an x beyond the range of sincos64:
+// x 2/pi mod 4 from 159 bits of 2/pi, which the hardware looks up by x's exponent in
+// segments of 53 (the bits before the first segment add multiples of 4), its products with x in
+// two parts each.  Holds for any angle that an FP32 state and time step give (below 2^945, where
+// the segments are scaled).
+__device__ __forceinline__ double near_angle(TabPtr t, double x)
+{
+#pragma clang fp contract(off)
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double p0 = __builtin_amdgcn_trig_preop(x, 0), p1 = __builtin_amdgcn_trig_preop(x, 1);
+    const double h0 = x * p0, l0 = fma(x, p0, -h0), h1 = x * p1, l1 = fma(x, p1, -h1);
+    const double a = fma(-4.0, rint(ldexp(h0, -2)), h0);
+    const double s = l0 + h1, v = s - l0, e = ((l0 - (s - v)) + (h1 - v)) + (l1 + x * __builtin_amdgcn_trig_preop(x, 2));
+    // quadrant k, the rest f + g of a quarter turn
+    const double k = rint(a + s), n = a - k, f = n + s, u = f - n, g = ((n - (f - u)) + (s - u)) + e;
+    const double r = fma(f, t[kRed + 1], fma(f, t[kRed + 2], g * t[kRed + 1]));
+    return fma(fma(-4.0, rint(ldexp(k, -2)), k), t[kRed + 1], r);
+#else
+    return atan2(sin(x), cos(x));
+#endif
+}
+
 // sine and cosine: x = k pi/2 + r with pi/2 in two parts (k pi/2's leading part leaves the
 // fused multiply-add exact before its rounding), then the Taylor series on |r| <= pi/4 up
 // to r^15 and r^16 (truncation below 6e-17 relative) and the quadrant's swap and signs.
-// Good to |x| of about 1e12, where the rounded quotient can miss its integer.
+// Good to |x| = 2^40; beyond it the rounded quotient misses its integer, r leaves the series'
+// range, and the caller passes near_angle(x): by one test for all the angles of a step, where
+// the code branches anyway (a test in each evaluation: 1-2% of a step).
 __device__ __forceinline__ void sincos64(TabPtr t, double x, double* sn, double* cs)
 {
     const double k = rint(x * t[kRed]);
@@ -171,7 +204,7 @@ __device__ __forceinline__ void quat_step64(TabPtr t, double& qw, double& qx, do
     if (!(z <= 0.25)) {
         const double a = sqrt(z);
         double s;
-        sincos64(t, a, &s, &dw);
+        sincos64(t, is_far(a) ? near_angle(t, a) : a, &s, &dw);
         sc = s / a;
     }
     const double dx = sc * ph.x, dy = sc * ph.y, dz = sc * ph.z;
@@ -553,9 +586,15 @@ __device__ __forceinline__ void quad_step64(int k, ConstModel& M, const float* _
             const V3<double> gb = (-M.g) * v3(Rm.m[6], Rm.m[7], Rm.m[8]);
             double sa, ca, sf, cf, s12, c12;
             const TabPtr t = fresh_table<0>(k);
-            sincos64(t, lg.q[0], &sa, &ca);
-            sincos64(t, lg.q[1], &sf, &cf);
-            sincos64(t, lg.q[1] + lg.q[2], &s12, &c12);
+            double qa = lg.q[0], qf = lg.q[1], q12 = lg.q[1] + lg.q[2];
+            if (is_far(qa) | is_far(qf) | is_far(q12)) {
+                if (is_far(qa)) qa = near_angle(t, qa);
+                if (is_far(qf)) qf = near_angle(t, qf);
+                if (is_far(q12)) q12 = near_angle(t, q12);
+            }
+            sincos64(t, qa, &sa, &ca);
+            sincos64(t, qf, &sf, &cf);
+            sincos64(t, q12, &s12, &c12);
             leg_terms(M, leg, sa, ca, sf, cf, s12, c12, lg.qd, tau, dt, dt * kd, w, vb, gb, G, S, Q, rb);
         }
         const V3<double> pfw = b.p + mul(Rm, foot_trunk(G));

@@ -847,6 +847,11 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
     [[maybe_unused]] M33<double> Rb;
     if constexpr (SCENE == 3) Rb = quat_R(bx.qw, bx.qx, bx.qy, bx.qz);
 
+    // lane `sub` evaluates angle sub of the leg; one beyond the range of sincos64 is brought into
+    // it where the step branches for its rare contacts
+    double ang = (sub == 0) ? lg.q[0] : (sub == 1) ? lg.q[1] : lg.q[1] + lg.q[2];
+    const bool far = is_far(ang);
+
     // ---- trunk corner g (g < 8) or box corner g - 8 (g >= 8), first, so that their terms leave
     // the registers before the leg's: the trunk's through a sum of their own where there are
     // any, the box's as rows of the sum below
@@ -870,7 +875,7 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
             bool hitB = false;
             if constexpr (SCENE == 2)
                 hitB = point_aabox(pw - v3(M.sb_cx, M.sb_cy, M.sb_cz), v3(M.sb_hx, M.sb_hy, M.sb_hz), dB, nB) && g < 8;
-            corner = __builtin_amdgcn_ballot_w64(hitT || hitB) != 0;
+            corner = __builtin_amdgcn_ballot_w64(hitT || hitB || far) != 0;
             if (corner) {
                 const V3<double> vc = vb + cross(w, rloc);
                 if (hitT) {
@@ -916,7 +921,7 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
                 body_terms(wgt * eta, wgt * M.cc, cl, n, wgt * F, dt, Qb, rbx);
             }
             // rare: the trunk's corners against the ground, and either body's in the other
-            corner = __builtin_amdgcn_ballot_w64(hitP || (hitG && own_trunk)) != 0;
+            corner = __builtin_amdgcn_ballot_w64(hitP || (hitG && own_trunk) || far) != 0;
             if (corner) {
                 const V3<double> lt = own_trunk ? cl : mulT(Rm, x - b.p), lb = own_trunk ? mulT(Rb, x - bx.p) : cl;
                 const V3<double> vtr = b.vw + mul(Rm, cross(w, lt)), vbx = bx.vw + mul(Rb, cross(bx.w, lb));
@@ -940,6 +945,7 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
             for (int e = 0; e < 6; ++e) red[kBoxRow + (21 + e) * kPitch + g] = rbx[e];
         }
         if (corner) {
+            if (far) ang = near_angle(fresh_table<0>(k), ang);
 #pragma unroll
             for (int e = 0; e < 21; ++e) red[e * kPitch + g] = Qc[e];
 #pragma unroll
@@ -962,7 +968,6 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
     {
         double Q[21], rb[6];
         double sn, cs;
-        const double ang = (sub == 0) ? lg.q[0] : (sub == 1) ? lg.q[1] : lg.q[1] + lg.q[2];
         sincos64(fresh_table<0>(k), ang, &sn, &cs);
         leg_terms(M, leg, dpp<0x00>(sn), dpp<0x00>(cs), dpp<0x55>(sn), dpp<0x55>(cs), dpp<0xAA>(sn), dpp<0xAA>(cs),
                   lg.qd, tau, dt, dt * kd, w, vb, gb, G, S, Q, rb);
