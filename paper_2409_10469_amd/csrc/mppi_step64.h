@@ -294,12 +294,23 @@ __device__ __forceinline__ void body_terms(double eta, double c, V3<double> r, V
 // 6x6 system: L D L^T of the packed upper triangle, solving Q x = r in place (Q is
 // overwritten).  Reciprocals of the pivots instead of square roots.
 // ------------------------------------------------------------------------------
+// the pivots' sign bits, gathered, and v or, where one was set, NaN: a system that its rounding
+// (a diverged sample) has made indefinite has no result, as with the square roots of a Cholesky
+// factorisation (a pivot of 0 gives NaN by its reciprocal)
+__device__ __forceinline__ int sign_of(double pivot) { return __double2hiint(pivot); }
+__device__ __forceinline__ double nan_if(int signs, double v)
+{
+    return __hiloint2double(__double2hiint(v) | (signs >> 31), __double2loint(v));
+}
+
 __device__ __forceinline__ void ldl6_solve(double* Q, double* r)
 {
     double inv[6];
+    int signs = 0;
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
         inv[j] = rcp(Q[s6(j, j)]);
+        signs |= sign_of(Q[s6(j, j)]);
         double l[6];
 #pragma unroll
         for (int i = j + 1; i < 6; ++i) l[i] = Q[s6(j, i)] * inv[j];
@@ -315,6 +326,7 @@ __device__ __forceinline__ void ldl6_solve(double* Q, double* r)
 #pragma unroll
     for (int i = 5; i >= 0; --i) {
         double s = r[i] * inv[i];
+        if (i == 5) s = nan_if(signs, s);
 #pragma unroll
         for (int k = i + 1; k < 6; ++k) s -= Q[s6(i, k)] * r[k];
         r[i] = s;
@@ -331,10 +343,12 @@ __device__ __forceinline__ Ldl3 ldl3(double a00, double a10, double a11, double 
     f.i0 = rcp(a00);
     f.l10 = a10 * f.i0;
     f.l20 = a20 * f.i0;
-    f.i1 = rcp(a11 - f.l10 * a10);
+    const double d1 = a11 - f.l10 * a10;
+    f.i1 = rcp(d1);
     const double t = a21 - f.l20 * a10;
     f.l21 = t * f.i1;
-    f.i2 = rcp(a22 - f.l20 * a20 - f.l21 * t);
+    const double d2 = a22 - f.l20 * a20 - f.l21 * t;
+    f.i2 = nan_if(sign_of(a00) | sign_of(d1) | sign_of(d2), rcp(d2));
     return f;
 }
 __device__ __forceinline__ void solve3(const Ldl3& f, double& b0, double& b1, double& b2)
