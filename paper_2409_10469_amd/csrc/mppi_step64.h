@@ -186,7 +186,8 @@ __device__ __forceinline__ double tanh_ratio64(TabPtr t, double s)
 
 // quaternion update q <- normalize(q (x) exp(dt w / 2)): sin(a)/a and cos(a) of the half
 // angle a by their Taylor series in a^2 while a <= 1/2 (up to a^12 and a^14, truncation
-// below 5e-17: any |w| up to 1/dt), by sincos64 beyond
+// below 5e-17: any |w| up to 1/dt), by sincos64 beyond (a rate that is not finite stays in the
+// series, to the same end)
 __device__ __forceinline__ void quat_step64(TabPtr t, double& qw, double& qx, double& qy, double& qz, V3<double> w,
                                             double dt)
 {
@@ -201,7 +202,7 @@ __device__ __forceinline__ void quat_step64(TabPtr t, double& qw, double& qx, do
     sc = fma(z, sc, 1.0);
     dw = fma(z, dw, -0.5);
     dw = fma(z, dw, 1.0);
-    if (!(z <= 0.25)) {
+    if (z > 0.25) {
         const double a = sqrt(z);
         double s;
         sincos64(t, is_far(a) ? near_angle(t, a) : a, &s, &dw);
