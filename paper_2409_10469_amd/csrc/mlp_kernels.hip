@@ -25,7 +25,6 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ bf16x8 ld8(const __bf16* p) { return *reinterpret_cast<const bf16x8*>(p); }
 
 constexpr int BK = kGemmBK;
-constexpr int LDK = BK + 8;  // LDS row pitch in bf16: 144 B keeps the 16-byte fragment reads conflict-free
 constexpr int kPF = 2;       // k-tiles of global loads in flight
 
 // 1 / (1 + exp(-z)).  exp(x) = 2^n 2^f with n + f = x log2(e) (the product in two parts, n its
@@ -449,8 +448,7 @@ __global__ __launch_bounds__(kNetThreads, 2) void net_kernel(PrepArgs p)
         return;
     }
     const int n0 = wave * 64;
-    constexpr int kDepth = kTrain ? 4 : 4;
-    NetFrags<4, kDepth> f;
+    NetFrags<4, 4> f;
     f32x4 acc[4];
     f32x4 ds[kLayers - 1][4];
     float bv[4];

@@ -168,6 +168,12 @@ __device__ __forceinline__ V3<R> cross(V3<R> a, V3<R> b)
 {
     return V3<R>{a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
 }
+// a where c, else b
+template <typename R>
+__device__ __forceinline__ V3<R> selv(bool c, V3<R> a, V3<R> b)
+{
+    return v3(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z);
+}
 // rod inertia about its centre, k (I - d d^T), applied to a
 template <typename R>
 __device__ __forceinline__ V3<R> rod_I(R k, V3<R> d, V3<R> a)

@@ -284,13 +284,6 @@ __device__ __forceinline__ bool sphere_aabox64(V3<double> l, double r, V3<double
     return true;
 }
 
-// a contact's damping block and force on a 6x6 body system (base_contact_folded)
-__device__ __forceinline__ void body_terms(double eta, double c, V3<double> r, V3<double> n, V3<double> F, double dt,
-                                           double* Q, double* rb)
-{
-    base_contact_folded(eta, c, r, n, F, dt, Q, rb);
-}
-
 // ------------------------------------------------------------------------------
 // 6x6 system: L D L^T of the packed upper triangle, solving Q x = r in place (Q is
 // overwritten).  Reciprocals of the pivots instead of square roots.
@@ -396,7 +389,7 @@ struct LegRows {
 
 // Mass-matrix, bias and joint-torque terms.  Q, rb receive the leg's share of the trunk
 // rows (Q overwritten; the linear block and the hip offsets' own inertia, which are
-// constant, are in the model's totals leg_I*).
+// constant, are in the model's totals tr_I*).
 template <typename MD>
 __device__ __forceinline__ void leg_terms(const MD& M, int leg, double sa, double ca, double sf, double cf,
                                           double s12, double c12, const double* qd, const double* tau, double dt,
@@ -501,7 +494,7 @@ __device__ __forceinline__ void foot_contact(TabPtr t, const MD& M, const LegFra
     const double c = wgt * M.cc;
     const double de = dt * eta, dce = dt * (c - eta);
     Ft = to_trunk(G, F);
-    body_terms(eta, c, foot_trunk(G) - M.foot_r * nt, nt, Ft, dt, Q, rb);
+    base_contact_folded(eta, c, foot_trunk(G) - M.foot_r * nt, nt, Ft, dt, Q, rb);
     // the joints' columns at the contact: abduction (0, -rz, ry), flexion (rz, 0, -rx),
     // knee (pz, 0, -px); D j = de j + dce (j . n) n
     const double gA = r.y * n.z - r.z * n.y, gF = r.z * n.x - r.x * n.z, gK = pz * n.x - px * n.z;
@@ -557,11 +550,6 @@ __device__ __forceinline__ ConstModel& fresh_const_model(ConstModel* m, int k)
 typedef const ModelT<double> ConstModel;
 __device__ __forceinline__ ConstModel& fresh_const_model(ConstModel* m, int) { return *m; }
 #endif
-
-__device__ __forceinline__ V3<double> pick(bool c, V3<double> a, V3<double> b)
-{
-    return v3(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z);
-}
 
 template <int SCENE>
 __device__ __forceinline__ void quad_step64(int k, ConstModel& M, const float* __restrict__ hf, double dt, double kp,
@@ -637,7 +625,7 @@ __device__ __forceinline__ void quad_step64(int k, ConstModel& M, const float* _
             if constexpr (SCENE == 0) {
                 n = v3(Rm.m[6], Rm.m[7], Rm.m[8]);
             } else {
-                const V3<double> nw = pick(isB, nB, nT);
+                const V3<double> nw = selv(isB, nB, nT);
                 if constexpr (SCENE == 3) {
                     if (isB) vo = mulT(Rm, box_vel(pfw - M.foot_r * nw));
                 }
@@ -692,14 +680,14 @@ __device__ __forceinline__ void quad_step64(int k, ConstModel& M, const float* _
         if (terrain64<SCENE>(M, hf, pw, 0.0, delta, nw)) {
             const V3<double> n = mulT(Rm, nw);
             contact_law64(fresh_table<3>(k), M, delta, n, vb + cross(w, r), F, eta);
-            body_terms(eta, M.cc, r, n, F, dt, Q, rb);
+            base_contact_folded(eta, M.cc, r, n, F, dt, Q, rb);
         }
         if constexpr (SCENE == 2) {
             if (point_aabox(pw - v3<double>(M.sb_cx, M.sb_cy, M.sb_cz), v3<double>(M.sb_hx, M.sb_hy, M.sb_hz), delta,
                             nw)) {
                 const V3<double> n = mulT(Rm, nw);
                 contact_law64(fresh_table<3>(k), M, delta, n, vb + cross(w, r), F, eta);
-                body_terms(eta, M.cc, r, n, F, dt, Q, rb);
+                base_contact_folded(eta, M.cc, r, n, F, dt, Q, rb);
             }
         }
         if constexpr (SCENE == 3) {
@@ -708,14 +696,14 @@ __device__ __forceinline__ void quad_step64(int k, ConstModel& M, const float* _
                 if (point_aabox(mulT(Rb, pw - bx.p), bh, delta, nl)) {
                     const V3<double> n = mulT(Rm, mul(Rb, nl));
                     contact_law64(fresh_table<3>(k), M, delta, n, vb + cross(w, r) - mulT(Rm, box_vel(pw)), F, eta);
-                    body_terms(eta, M.cc, r, n, F, dt, Q, rb);
+                    base_contact_folded(eta, M.cc, r, n, F, dt, Q, rb);
                 }
                 const V3<double> cl = v3(ci & 1 ? bh.x : -bh.x, ci & 2 ? bh.y : -bh.y, ci & 4 ? bh.z : -bh.z);
                 const V3<double> xw = bx.p + mul(Rb, cl), lt = mulT(Rm, xw - b.p);
                 if (point_aabox(lt, th, delta, nl)) {  // nl: trunk face normal, toward the box corner
                     contact_law64(fresh_table<3>(k), M, delta, -1.0 * nl, vb + cross(w, lt) - mulT(Rm, box_vel(xw)), F,
                                   eta);
-                    body_terms(eta, M.cc, lt, -1.0 * nl, F, dt, Q, rb);
+                    base_contact_folded(eta, M.cc, lt, -1.0 * nl, F, dt, Q, rb);
                 }
             }
         }
@@ -754,7 +742,7 @@ __device__ __forceinline__ void quad_step64(int k, ConstModel& M, const float* _
 #pragma unroll
         for (int i = 0; i < 6; ++i) rx[i] = 0.0;
         const V3<double> nz = v3(Rb.m[6], Rb.m[7], Rb.m[8]), vl = mulT(Rb, bx.vw);
-        if (fb) body_terms(fb_eta, fb_c, mulT(Rb, fb_x - bx.p), mulT(Rb, fb_n), mulT(Rb, fb_F), dt, Qb, rx);
+        if (fb) base_contact_folded(fb_eta, fb_c, mulT(Rb, fb_x - bx.p), mulT(Rb, fb_n), mulT(Rb, fb_F), dt, Qb, rx);
 #pragma unroll 1
         for (int cc = 0; cc < 2; ++cc) {
             const int ci = 2 * leg + cc;
@@ -762,7 +750,7 @@ __device__ __forceinline__ void quad_step64(int k, ConstModel& M, const float* _
             const V3<double> xw = bx.p + mul(Rb, cl);
             if (-xw.z > 0.0) {
                 contact_law64(fresh_table<5>(k), M, -xw.z, nz, vl + cross(bx.w, cl), F, eta);
-                body_terms(eta, M.cc, cl, nz, F, dt, Qb, rx);
+                base_contact_folded(eta, M.cc, cl, nz, F, dt, Qb, rx);
             }
             if (near_box) {
                 const V3<double> r = v3((ci & 1 ? 0.5 : -0.5) * M.tsx, (ci & 2 ? 0.5 : -0.5) * M.tsy,
@@ -773,13 +761,13 @@ __device__ __forceinline__ void quad_step64(int k, ConstModel& M, const float* _
                 if (point_aabox(lb, bh, delta, nl)) {
                     const V3<double> n = mulT(Rm, mul(Rb, nl));
                     contact_law64(fresh_table<5>(k), M, delta, n, vb + cross(w, r) - mulT(Rm, box_vel(pw)), F, eta);
-                    body_terms(eta, M.cc, lb, nl, mulT(Rb, -1.0 * mul(Rm, F)), dt, Qb, rx);
+                    base_contact_folded(eta, M.cc, lb, nl, mulT(Rb, -1.0 * mul(Rm, F)), dt, Qb, rx);
                 }
                 const V3<double> lt = mulT(Rm, xw - b.p);
                 if (point_aabox(lt, th, delta, nl)) {
                     contact_law64(fresh_table<5>(k), M, delta, -1.0 * nl, vb + cross(w, lt) - mulT(Rm, box_vel(xw)), F,
                                   eta);
-                    body_terms(eta, M.cc, cl, mulT(Rb, mul(Rm, nl)), mulT(Rb, -1.0 * mul(Rm, F)), dt, Qb, rx);
+                    base_contact_folded(eta, M.cc, cl, mulT(Rb, mul(Rm, nl)), mulT(Rb, -1.0 * mul(Rm, F)), dt, Qb, rx);
                 }
             }
         }
@@ -807,7 +795,7 @@ __device__ __forceinline__ void quad_step64(int k, ConstModel& M, const float* _
         // one quaternion step per lane: the trunk's on even lanes, the box's on odd lanes
         const bool odd = (leg & 1) != 0;
         double q0 = odd ? bx.qw : b.qw, q1 = odd ? bx.qx : b.qx, q2 = odd ? bx.qy : b.qy, q3 = odd ? bx.qz : b.qz;
-        quat_step64(fresh_table<2>(k), q0, q1, q2, q3, pick(odd, bx.w, b.w), dt);
+        quat_step64(fresh_table<2>(k), q0, q1, q2, q3, selv(odd, bx.w, b.w), dt);
         b.qw = dpp<0x00>(q0); b.qx = dpp<0x00>(q1); b.qy = dpp<0x00>(q2); b.qz = dpp<0x00>(q3);
         bx.qw = dpp<0x55>(q0); bx.qx = dpp<0x55>(q1); bx.qy = dpp<0x55>(q2); bx.qz = dpp<0x55>(q3);
     }

@@ -91,12 +91,6 @@ __device__ __forceinline__ R sel(bool c, R a, R b)
     return c ? a : b;
 }
 
-template <typename R>
-__device__ __forceinline__ V3<R> selv(bool c, V3<R> a, V3<R> b)
-{
-    return v3(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z);
-}
-
 // pose and velocity of a rigid body (the trunk or the free box): rotation to world,
 // position, world linear velocity, body-frame angular velocity
 template <typename R>
@@ -881,12 +875,12 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
                 if (hitT) {
                     const V3<double> n = mulT(Rm, nT);
                     contact_law64(fresh_table<3>(k), M, dT, n, vc, F, eta);
-                    body_terms(eta, M.cc, rloc, n, F, dt, Qc, rc);
+                    base_contact_folded(eta, M.cc, rloc, n, F, dt, Qc, rc);
                 }
                 if (hitB) {
                     const V3<double> n = mulT(Rm, nB);
                     contact_law64(fresh_table<3>(k), M, dB, n, vc, F, eta);
-                    body_terms(eta, M.cc, rloc, n, F, dt, Qc, rc);
+                    base_contact_folded(eta, M.cc, rloc, n, F, dt, Qc, rc);
                 }
             }
         } else {
@@ -918,7 +912,7 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
                 const V3<double> n = v3(Rb.m[6], Rb.m[7], Rb.m[8]);  // up, box frame
                 const V3<double> vc = mulT(Rb, bx.vw) + cross(bx.w, cl);
                 contact_law64(fresh_table<3>(k), M, wgt * dG, n, wgt * vc, F, eta);
-                body_terms(wgt * eta, wgt * M.cc, cl, n, wgt * F, dt, Qb, rbx);
+                base_contact_folded(wgt * eta, wgt * M.cc, cl, n, wgt * F, dt, Qb, rbx);
             }
             // rare: the trunk's corners against the ground, and either body's in the other
             corner = __builtin_amdgcn_ballot_w64(hitP || (hitG && own_trunk) || far) != 0;
@@ -928,15 +922,15 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
                 if (hitG && own_trunk) {
                     const V3<double> n = v3(Rm.m[6], Rm.m[7], Rm.m[8]);
                     contact_law64(fresh_table<3>(k), M, dG, n, mulT(Rm, vtr), F, eta);
-                    body_terms(eta, M.cc, lt, n, F, dt, Qc, rc);
+                    base_contact_folded(eta, M.cc, lt, n, F, dt, Qc, rc);
                 }
                 if (hitP) {
                     // force +F on the corner's body, -F on the other
                     const V3<double> n = selv(own_trunk, mul(Rb, nlq), mul(Rm, nlq));
                     contact_law64(fresh_table<3>(k), M, dP, n, selv(own_trunk, vtr - vbx, vbx - vtr), F, eta);
                     const double st = own_trunk ? 1.0 : -1.0;
-                    body_terms(eta, M.cc, lt, mulT(Rm, n), st * mulT(Rm, F), dt, Qc, rc);
-                    body_terms(eta, M.cc, lb, mulT(Rb, n), (-st) * mulT(Rb, F), dt, Qb, rbx);
+                    base_contact_folded(eta, M.cc, lt, mulT(Rm, n), st * mulT(Rm, F), dt, Qc, rc);
+                    base_contact_folded(eta, M.cc, lb, mulT(Rb, n), (-st) * mulT(Rb, F), dt, Qb, rbx);
                 }
             }
 #pragma unroll
@@ -1004,7 +998,7 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
 #pragma unroll
             for (int i = 0; i < 6; ++i) rf[i] = 0.0;
             const double wb = sub == 0 ? wgt : 0.0;
-            body_terms(wb * eta, wb * M.cc, mulT(Rb, pfw - M.foot_r * nw - bx.p), mulT(Rb, nw),
+            base_contact_folded(wb * eta, wb * M.cc, mulT(Rb, pfw - M.foot_r * nw - bx.p), mulT(Rb, nw),
                        mulT(Rb, (-wb) * mul(Rm, F)), dt, Qf, rf);
 #pragma unroll
             for (int e = 0; e < 21; ++e) red[kBoxRow + e * kPitch + g] += Qf[e];
