@@ -295,8 +295,11 @@ const char *mppi_last_error(const mppi_ctx *ctx);
 #define MPPI_BATCH_MAX_MODELS 8
 typedef struct mppi_batch mppi_batch;
 
-/* max_horizon and max_hf_cells size the LDS stage (8 B x max_horizon x 8 knots + 4 B x
- * max_hf_cells <= 64 KiB in FP64 arithmetic).  EINVAL on out-of-range limits. */
+/* max_horizon and max_hf_cells bound what an admitted instance may have: the horizon sizes
+ * the spline basis in LDS, the cells the instances' heightfields, which are read from device
+ * memory.  Together they stay within what a controller's rollout can stage (8 B x max_horizon
+ * x 8 knots + 12 KiB of knots + 4 B x max_hf_cells <= 64 KiB in FP64 arithmetic; half of the
+ * first two in FP32).  EINVAL on out-of-range limits. */
 mppi_status mppi_batch_create(int max_instances, int max_horizon, int max_hf_cells, int arith, mppi_batch **out);
 void mppi_batch_destroy(mppi_batch *b);
 size_t mppi_batch_control_bytes(int max_instances, int arith);

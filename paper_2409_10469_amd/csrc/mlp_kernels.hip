@@ -31,8 +31,9 @@ constexpr int kPF = 2;       // k-tiles of global loads in flight
 // nearest whole number) and the hardware's 2^f; the quotient from the hardware's reciprocal and
 // a Newton step; where exp(-z) is beyond float that gives NaN and the maximum 0.  Without the
 // general division and the range checks of 1.f / (1.f + expf(-z)), two thirds of its
-// instructions: a pass over 256 rows 20.0 us instead of 21.2.  Largest and rms relative error
-// over [-87, 110] as that form's: 1.5e-7 and 3.8e-8.
+// instructions: a pass over 256 rows 19.4 us instead of 20.6, a training step's over 4096 rows
+// 51 instead of 53.  Largest and rms relative error over [-87, 110] as that form's: 1.5e-7 and
+// 3.8e-8; below -87.3 the result is not above 1.2e-38 and may be 0.
 __device__ __forceinline__ float sigm(float z)
 {
 #pragma clang fp contract(off)
@@ -63,8 +64,8 @@ __device__ __forceinline__ size_t frag_offset(int n, int k, int K)
 // The activations and errors that the weight gradients reduce over the batch are in the same
 // order in halves: a block holds column panel n / 16 of 16 batch rows r, and the panels of a
 // group of 16 rows are consecutive, so what a row block writes of a layer is one run of 16 KiB.
-// (With the rows along the panels instead, runs of 512 B at strides of the batch, the pass over
-// the network took 61.8 us for 4096 rows against 59.5, the weight gradients the same.)
+// (With the rows along the panels instead, runs of 512 B at strides of the batch, a training
+// step's pass over 4096 rows, then 59.5 us and now 51, took 61.8, the weight gradients the same.)
 // batch_offset: element offset of column n, rows r (a multiple of 8) .. +7 of N columns.
 __device__ __forceinline__ size_t batch_offset(int n, int r, int N)
 {
@@ -79,7 +80,7 @@ __device__ __forceinline__ size_t batch_offset(int n, int r, int N)
 // with the loads of the next kPF k-tiles in flight (in registers) while the current tile's
 // products run and the next k-tile on its way to the other half of the LDS.  What bounds it is
 // the way of the operands from memory, 34 MB for 4096 rows that other XCDs have just written:
-// 64 x 64 tiles with twice the LDS traffic took the same time.  For 4096 rows 20 us, in launches
+// 64 x 64 tiles with twice the LDS traffic took the same time.  For 4096 rows 19 us, in launches
 // for each layer 56 together; 4 splits instead of 8 save 2 us of a training step (15 MB fewer
 // partials), but another order of the sums turns the first updates of parameters whose gradient
 // is nearly zero.  dZ is the instruction's first operand, so a lane's four sums are consecutive
@@ -194,15 +195,15 @@ hipError_t launch_gemm(int epi, const GemmArgs& g, int splits, hipStream_t st)
 // its activations in LDS, each of its 8 waves 64 of a hidden layer's 512 columns.  What bounds
 // it is the stream of weights from L2, 1.75 MB for every workgroup whatever its rows (a training
 // step takes 1.7 MB more): the waves read their fragments straight from memory (no other wave of
-// the workgroup needs them), four 64-wide k-tiles ahead of the products (two: 22.6 us for 256
-// rows against 20.8, and 54 us against 50 for a training step's 4096).  16 rows, the matrix
+// the workgroup needs them), four 64-wide k-tiles ahead of the products (two: the same for 256
+// rows, and 55 us against 51 for a training step's 4096).  16 rows, the matrix
 // instruction's height, give the most workgroups: one row block's time is the pass's time up to
 // 4096 rows (one a compute unit), where a launch for every layer paid its start and its drain.
-// Launches per layer / here, us a pass: 1 row 29.3 / 18.6, 256 rows 29.4 / 20.0, 4096 rows 42.2
-// / 22.4, 16384 rows 104 / 78; with three policies in turn, whose weights together exceed an
-// XCD's L2, 256 rows 30.1 / 20.7.  A training step (three launches against sixteen): 64 rows
-// 93 / 53, 512 rows 106 / 58, 4096 rows 151 / 76, 16384 rows 420 / 247.  The loss alone: 4096
-// rows 52 / 25.
+// Launches per layer / here, us a pass: 1 row 29.1 / 18.3, 256 rows 29.4 / 19.4, 4096 rows 39.9
+// / 21.5, 16384 rows 102 / 77; with three policies in turn, whose weights together exceed an
+// XCD's L2, 256 rows 30.2 / 19.8.  A training step (three launches against sixteen): 64 rows
+// 90 / 53, 512 rows 104 / 57, 4096 rows 150 / 75, 16384 rows 413 / 237.  The loss alone: 4096
+// rows 52 / 24.
 // ---------------------------------------------------------------------------------
 constexpr int kNetThreads = 512, kNetLd = kHidden + 8, kOutLd = kOut + 4;
 
@@ -306,7 +307,8 @@ __device__ __forceinline__ void net_output(const PrepArgs& p, const __bf16* sA, 
 // Workgroups past the row blocks bring the weights into their XCD's L2 (workgroups go round the
 // XCDs), part `part` of kNetWarm each: a few row blocks alone fetch them with a compute unit's
 // misses in flight for each XCD, and a pass whose weights are not in L2 (several policies in
-// turn) waits for that: 256 rows, three policies in turn, 30.8 us without them, 22.0 with.  From
+// turn, or after an update) waits for that: 256 rows, three policies in turn, 29.4 us without
+// them, 19.8 with; a training step of 64 rows 63 and 53.  From
 // kNetWarmBlocks row blocks on (16 an XCD) those have as much in flight themselves.  The values
 // are not used.
 constexpr int kNetWarm = 8, kXcds = 8, kNetWarmBlocks = 128;

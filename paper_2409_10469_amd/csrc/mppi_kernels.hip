@@ -480,7 +480,8 @@ __device__ __forceinline__ void instance_tail(const InstDesc& I, const DevParams
     // bound by the round trips it makes one after the other.  Each lane still adds its samples
     // in increasing order, dimension by dimension.  The last instances' tails end a batch step:
     // with the heightfield left out of LDS and this walk, a step of 48 mixed controllers went
-    // from 2317 to 1326 us in FP64 and from 2380 to 1165 us in FP32.
+    // from 2317 to 1326 us in FP64 and from 2380 to 1165 us in FP32 (a batch's first steps; as its
+    // robots move and fall the FP64 step takes 1480 us after 100 steps and 1620 after 500).
     for (int d0 = 0; d0 < D; d0 += kTailDims) {
         float acc[kTailDims];
 #pragma unroll
@@ -572,8 +573,10 @@ __device__ __forceinline__ void batch_exit(const BatchArgs<R>& a)
     }
 }
 
-// one persistent kernel per scene: its own queue of that scene's tiles (two waves per SIMD in
-// FP32, which fits, one in FP64, as below)
+// one persistent kernel per scene: its own queue of that scene's tiles.  FP32 is held to two
+// waves per SIMD, which fits without spills but in the pushing scene (16 registers, 60 B a lane):
+// a step of 16 pushing controllers, K = 2048, H = 40, takes 538 us so and 749 at one wave with 8
+// workgroups a CU, the same 749 either way with 4.  FP64 takes one, as below.
 template <int SCENE, typename R>
 __global__ __launch_bounds__(64, sizeof(R) == 4 ? 2 : 1) void batch_kernel(BatchArgs<R> a)
 {
@@ -627,7 +630,7 @@ __global__ __launch_bounds__(64, sizeof(R) == 4 ? 2 : 1) void batch_kernel(Batch
 // its scene's code (uniform over the workgroup).  In FP32 the four scenes' code together
 // needs a few registers more than half the file; it is held to two waves per SIMD (the
 // per-scene FP32 kernels' occupancy).  FP64 takes one: held to two, its pushing scene spills
-// 1.1 KB a lane and a step of 48 mixed controllers takes 2659 us against 1326.
+// 1.1 KB a lane and a step of 48 mixed controllers takes 2659 us against 1326 (first steps).
 template <typename R>
 __global__ __launch_bounds__(64, sizeof(R) == 4 ? 2 : 1) void batch_kernel_all(BatchArgs<R> a)
 {
