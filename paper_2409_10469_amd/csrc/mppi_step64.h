@@ -590,7 +590,7 @@ __device__ __forceinline__ void quad_step64(int k, ConstModel& M, const float* _
             double sa, ca, sf, cf, s12, c12;
             const TabPtr t = fresh_table<0>(k);
             double qa = lg.q[0], qf = lg.q[1], q12 = lg.q[1] + lg.q[2];
-            if (is_far(qa) | is_far(qf) | is_far(q12)) {
+            if (__builtin_amdgcn_ballot_w64(is_far(qa) | is_far(qf) | is_far(q12))) {  // a scalar branch
                 if (is_far(qa)) qa = near_angle(t, qa);
                 if (is_far(qf)) qf = near_angle(t, qf);
                 if (is_far(q12)) q12 = near_angle(t, q12);

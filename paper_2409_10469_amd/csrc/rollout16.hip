@@ -916,7 +916,7 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
             }
             // rare: the trunk's corners against the ground, and either body's in the other
             corner = __builtin_amdgcn_ballot_w64(hitP || (hitG && own_trunk) || far) != 0;
-            if (corner) {
+            if (__builtin_expect(corner, 0)) {  // out of the step's straight way
                 const V3<double> lt = own_trunk ? cl : mulT(Rm, x - b.p), lb = own_trunk ? mulT(Rb, x - bx.p) : cl;
                 const V3<double> vtr = b.vw + mul(Rm, cross(w, lt)), vbx = bx.vw + mul(Rb, cross(bx.w, lb));
                 if (hitG && own_trunk) {
@@ -938,7 +938,7 @@ __device__ __forceinline__ void step16_64(int k, const ModelT<double>& M, const 
 #pragma unroll
             for (int e = 0; e < 6; ++e) red[kBoxRow + (21 + e) * kPitch + g] = rbx[e];
         }
-        if (corner) {
+        if (__builtin_expect(corner, 0)) {
             if (far) ang = near_angle(fresh_table<0>(k), ang);
 #pragma unroll
             for (int e = 0; e < 21; ++e) red[e * kPitch + g] = Qc[e];

@@ -1,5 +1,7 @@
 // The FP64 step's small solvers, built for the host: 6x6 (packed upper triangle) and 3x3
 // systems in place.  Not a GPU build.
+#include <hip/hip_runtime.h>
+inline unsigned long long __builtin_amdgcn_ballot_w64(bool p) { return p; }  // named by the step, not called here
 #include "mppi_step64.h"
 
 extern "C" void solve_6x6(double* Q, double* r) { mppi::f64::ldl6_solve(Q, r); }
